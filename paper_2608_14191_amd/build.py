@@ -21,6 +21,8 @@ FLAGS = [
     # single-lane arrival counts stay plain atomics (the atomic optimizer would rewrite
     # them into wave scans that wait for the result at once).
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # the first scalar kernel arguments arrive in registers with the wave
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

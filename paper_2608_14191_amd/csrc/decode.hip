@@ -60,11 +60,12 @@ struct DecodeArgs {
   float* append_r;                // fused append: [rows][kAppStride] coefficients, bounds
   const Partial* seg;             // full-precision segment partials [rows][G], or null
   int64_t cap;
-  int n_q_heads, n_kv_heads, G, q_dtype;
-  int n_splits, n_blocks;         // splits per (sequence, KV head); rows x splits
+  int batch, n_q_heads, n_kv_heads, G, q_dtype;
+  int hg;                         // groups of query heads per KV head, a workgroup row each
+  int max_splits;                 // partial slots per row
   int rk, rv;                     // record bytes
   float scale_log2e;
-  int off_v, off_ak, off_av, off_ql, off_pb, off_ob, ob_stride, off_es;   // dynamic LDS layout
+  int off_v, off_ak, off_av, off_ql, off_qc, off_pb, off_ob, ob_stride, off_es;   // dynamic LDS
 };
 
 __device__ inline float load_q(const void* q, int dtype, int64_t idx) {
@@ -322,6 +323,21 @@ __device__ inline void wait_vmcnt(int n) {
 #undef AATC_VMW
 }
 
+// The same for small n (a larger one waits for all but the last 15).
+__device__ inline void wait_vmcnt_small(int n) {
+#define AATC_VMW(k)                                                                         \
+  case k:                                                                                  \
+    __builtin_amdgcn_s_waitcnt(((k) & 0xF) | (0x7 << 4) | (0xF << 8));                       \
+    break;
+  switch (__builtin_amdgcn_readfirstlane(n)) {
+    AATC_VMW(0) AATC_VMW(1) AATC_VMW(2) AATC_VMW(3) AATC_VMW(4) AATC_VMW(5) AATC_VMW(6)
+    AATC_VMW(7) AATC_VMW(8) AATC_VMW(9) AATC_VMW(10) AATC_VMW(11) AATC_VMW(12) AATC_VMW(13)
+    AATC_VMW(14)
+    default: __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0xF << 8)); break;
+  }
+#undef AATC_VMW
+}
+
 __device__ inline v4i mfma_i8(v4i a, v4i b, v4i c) {
   return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
@@ -398,7 +414,6 @@ struct TvMfma {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) load_step(hv, kk);
   }
-  // The operands of k-step kk only (the loads can be spread out).
   __device__ void load_step(const HeadParams* hv, int kk) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bf16x8* tp = reinterpret_cast<const bf16x8*>(hv->Tm);
@@ -575,9 +590,8 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
 // each output element (head h, channel c) takes its one more hook term and goes into the
 // B operands of o = T_V o~.
 // LDS: T_V B operands (8 KiB) | weights [2][NH][SB] | rescales [2][NH] | (M, L, bad) [NH]
-// | group sums [NG][NU] (16 B each).  TV_HELD: the caller has loaded tv (every split does,
-// during its value phase, so the merging one starts with T_V in registers); otherwise the
-// merge loads it after the partials.
+// | group sums [NG][NU] (16 B each).  Every run has loaded tv during its last value phase, so
+// the merging one starts with T_V in registers.
 template <int NTHR, int NH>
 struct WideMerge {
   static constexpr int NW = NTHR / 64;
@@ -599,11 +613,10 @@ struct WideMerge {
 template <int NTHR, int NH>
 constexpr size_t wide_merge_lds_bytes() { return WideMerge<NTHR, NH>::kFloats * sizeof(float); }
 
-template <int NTHR, int NH, bool TV_HELD, class Hook>
-__device__ __forceinline__ void merge_if_last_wide(const void* params_v, int kvh, int64_t row,
-                                                   int G, int n_splits, const Partial* partials,
-                                                   unsigned* counters, float* out_rows,
-                                                   float* lds, TvMfma<NTHR>& tv, Hook& hook) {
+template <int NTHR, int NH, class Hook>
+__device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Partial* parts,
+                                                   unsigned* counter, float* out_rows, float* lds,
+                                                   const TvMfma<NTHR>& tv, Hook& hook) {
   using WM = WideMerge<NTHR, NH>;
   constexpr int SU = WM::SU, SB = WM::SB, NU = WM::NU, NTW = WM::NTW, NHW = WM::NHW;
   __shared__ unsigned last_s;
@@ -611,11 +624,11 @@ __device__ __forceinline__ void merge_if_last_wide(const void* params_v, int kvh
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   __builtin_amdgcn_s_waitcnt(0);          // this thread's partial stores have completed
   __syncthreads();
-  unsigned prev = 0u;
-  if (tid == 0)
-    prev = __hip_atomic_fetch_add(&counters[row * kCtrStride], 1u, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-  if (tid == 0) last_s = (prev == (unsigned)n_splits - 1u) ? 1u : 0u;
+  if (tid == 0) {
+    const unsigned prev =
+        __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last_s = (prev == (unsigned)n_splits - 1u) ? 1u : 0u;
+  }
   __syncthreads();
   if (!last_s) return;
   hook.prefetch();
@@ -626,8 +639,7 @@ __device__ __forceinline__ void merge_if_last_wide(const void* params_v, int kvh
   float* sat = lds + WM::kSa;
   v4f* fin = reinterpret_cast<v4f*>(lds + WM::kFin);
   v4f* red = reinterpret_cast<v4f*>(lds + WM::kRed);
-  const __amdgpu_buffer_rsrc_t prs =
-      make_rsrc(partials + row * n_splits * G, (uint32_t)(n_splits * G * sizeof(Partial)));
+  const __amdgpu_buffer_rsrc_t prs = make_rsrc(parts, (uint32_t)(n_splits * G * sizeof(Partial)));
   // 32-bit offsets: the descriptor covers less than 2^31 bytes.
   const uint32_t step = (uint32_t)G * (uint32_t)sizeof(Partial);
   const int u = tid % NU, q = tid / NU, h = u / (kD / 4), c4 = u % (kD / 4);
@@ -738,16 +750,13 @@ __device__ __forceinline__ void merge_if_last_wide(const void* params_v, int kvh
       TvMfma<NTHR>::put(ob_hi, ob_lo, hh, c, f[2] != 0.f ? NAN : (Ls > 0.f ? a / Ls : 0.f));
     }
   }
-  // T_V (its L2 lines touched by every split) after the partials: a compute unit serves its
-  // loads in order, and T_V is needed last.
-  if constexpr (!TV_HELD) tv.load(head_params(params_v, kvh));
   __syncthreads();
   // o = T_V o~ (the partials are in the transformed domain).
   tv.apply(ob_hi, ob_lo, G, [&](int hh, int j0, v4f o) {
     *reinterpret_cast<v4f*>(out_rows + (int64_t)hh * kD + j0) = o;
   });
   hook.finish();
-  if (tid == 0) counters[row * kCtrStride] = 0u;
+  if (tid == 0) *counter = 0u;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -979,7 +988,7 @@ struct AppendHook {
   int e_b[2], e_off[2];                // their widths and first record bits
   bool e_mr;                           // the wave's tensor uses the midrise reading
   float e_s[2];                        // their scales s_c (value token)
-  float qk[2][NH];                     // Q_c of every head for them (key token)
+  const float* qc;                     // Q_c of every head [NH][kD] (LDS; key token)
   AppendScratch* sc;
   float r2[2];                         // their coefficients r_c = h_c / s_c
   float eh;                            // the wave's token: fixed-point error bound
@@ -1007,9 +1016,14 @@ struct AppendHook {
   }
   __device__ void encode() {
     if (!on) return;                   // uniform over the workgroup
+    float qk[2][NH];                   // (read here: no LDS round trip behind a branch later)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave < 2) {
       const int et = wave;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < NH; ++h) qk[i][h] = qc[h * kD + lane + 64 * i];
       if (lane < kMaxBudget / 32) sc->erec[et][lane] = 0u;
       // A token that is not exact in fixed point keeps its coefficients if the certificate
       // holds; otherwise (rarely) the exact routine recomputes them.
@@ -1286,8 +1300,73 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(
   }
 }
 
+// Deals the chunks of S tokens of a ragged batch to the workgroups: every workgroup computes
+// the same quota q, the smallest run length that a closed form finds to fit the grid (the
+// average, or with every row's last run taken as full), and finds its row and run from the
+// prefix sums over the sequences (64 per pass, one per lane).  A row has max(1, ceil(chunks /
+// q)) runs; workgroups past the last run return false.  The host gives the grid more
+// workgroups than rows.
+__device__ inline int clamped_chunks(int len, int64_t cap, int S, int app) {
+  return max(1, ((int)min<int64_t>(max(len, 0), cap) - app + S - 1) / S);
+}
+template <int S, bool APPEND>
+__device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batch, int rps, int lb,
+                                   int& vrow, int& split, int& ns, int& per, int& len_raw) {
+  const int lane = threadIdx.x & 63;                 // (rps: rows per sequence)
+  const int grid = (int)gridDim.x;
+  int nch = 0, len = 0, tot = 0;
+  auto load = [&](int b0) {                          // this lane's sequence b0 + lane
+    len = seq_len[min(b0 + lane, batch - 1)];
+    nch = b0 + lane < batch ? clamped_chunks(len, cap, S, APPEND ? 1 : 0) : 0;
+  };
+  for (int b0 = 0; b0 < batch; b0 += 64) {
+    load(b0);
+    tot += __builtin_amdgcn_readfirstlane(wave_sum_i32(nch));
+  }
+  tot *= rps;
+  int q = (tot + grid - 1) / grid;
+  {
+    int cnt = 0;                                     // workgroups that q takes
+    for (int b0 = 0; b0 < batch; b0 += 64) {
+      if (batch > 64) load(b0);
+      cnt += __builtin_amdgcn_readfirstlane(wave_sum_i32((nch + q - 1) / q));
+    }
+    // sum ceil(nch / q) <= tot / q + rows: this q always fits
+    if (cnt * rps > grid) q = (tot + grid - batch * rps - 1) / (grid - batch * rps);
+  }
+  int left = lb;
+  for (int b0 = 0; b0 < batch; b0 += 64) {
+    if (batch > 64) load(b0);
+    const int cnt = (nch + q - 1) / q * rps;
+    // inclusive prefix sums: within rows of 16 lanes by row shifts, then the row totals
+    int v = cnt;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    const int r0 = __builtin_amdgcn_readlane(v, 15), r1 = __builtin_amdgcn_readlane(v, 31),
+              r2 = __builtin_amdgcn_readlane(v, 47);
+    v += (lane >= 16 ? r0 : 0) + (lane >= 32 ? r1 : 0) + (lane >= 48 ? r2 : 0);
+    const unsigned long long past = __builtin_amdgcn_ballot_w64(v > left);
+    if (past) {
+      const int i = __builtin_ctzll(past);
+      const int cb = __builtin_amdgcn_readlane(cnt, i);
+      left -= __builtin_amdgcn_readlane(v, i) - cb;
+      ns = cb / rps;
+      vrow = (b0 + i) * rps + left / ns;
+      split = left % ns;
+      per = q;
+      len_raw = __builtin_amdgcn_readlane(len, i);
+      return true;
+    }
+    left -= __builtin_amdgcn_readlane(v, 63);
+  }
+  return false;
+}
+
 // ---------------------------------------------------------------------------------------
-// MFMA decode kernel (G <= 8 query heads per KV head, records of at most 64 bytes).
+// MFMA decode kernel (records of at most 128 bytes; up to 8 query heads of a KV head per
+// workgroup, more heads as further workgroups over the same cache).
 //
 // Both contractions run on v_mfma_i32_16x16x64_i8 over the bits of the codes.
 //  * Keys: D[token, (head, limb)] = sum_bits bit(token) * Qlimb[bit, (head, limb)].
@@ -1310,72 +1389,95 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(
 //
 // Every workgroup derives its query bit weights itself, while its cache loads are in
 // flight: q~ = T_K^T q (fp32), then per bit the 32-bit fixed-point limbs.
+//
+// Streaming.  A workgroup takes a run of consecutive S-token chunks of its (sequence, KV
+// head).  One chunk's compute (masks, products, softmax: about 4-6 us) is longer than its
+// 94 KB take to arrive, so a workgroup per chunk leaves the memory idle for most of its life
+// and repeats the query planes each time; a run builds them once, has the next chunk's
+// records in flight while it computes (the key region is refilled once the scores are
+// formed, the value region once the values are summed), and leaves one partial for the
+// whole run.
 // ---------------------------------------------------------------------------------------
-template <int NT, int NTILE, int NP, int NW, bool APPEND>
+template <int NT, int NTILE, int NP, bool APPEND>
 // At most two waves per SIMD ever share a compute unit with this kernel (LDS holds one
 // eight-wave workgroup), so it may use up to 256 VGPRs per lane.
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * NW, 64 * NW),
-                          amdgpu_waves_per_eu(2, 2)))
-void decode_mfma_kernel(const DecodeArgs a) {
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void* params_v,
+                        const void* q, int n_splits, int n_kv_heads, int batch, uint32_t shape,
+                        const DecodeArgs a) {
+  constexpr int NW = 8;               // waves per workgroup
   constexpr int NTHR = 64 * NW;       // threads per workgroup
   constexpr int NH = 4 * NT;          // head slots: 4 per column tile
   constexpr int TW = 16 * NTILE;      // tokens per wave
-  constexpr int S = NW * TW;          // tokens per workgroup
-  constexpr int NCH = S / 64;         // 64-token chunks per workgroup
-  constexpr int CPW = NTILE / 4;      // chunks per wave
-  constexpr int NLD = S * 64 / 16 / NTHR;   // 16-byte loads per thread per cache (64-byte records)
-  // With eight waves the cache streams straight into LDS, issued by the upper half of the
-  // waves; the lower half builds the query planes meanwhile (a wave whose loads wait for
-  // queue space can do nothing else).  With four, every wave loads into registers.
-  constexpr bool DMA = NW == 8;
-  constexpr int NWC = DMA ? NW / 2 : NW;    // waves that build the query planes
+  constexpr int S = NW * TW;          // tokens per chunk
+  constexpr int NCH = S / 64;         // 64-token blocks per chunk
+  constexpr int CPW = NTILE / 4;      // blocks per wave
+  // The cache streams straight into LDS.  For the first chunk the upper half of the waves
+  // issues the transfers; the lower half builds the query planes meanwhile (a wave whose
+  // loads wait for queue space can do nothing else).
+  constexpr int NWC = NW / 2;               // waves that build the query planes
   constexpr int NTC = 64 * NWC;             // their threads
   constexpr int NJQ = NTC / 32;       // row blocks of the query transform
   constexpr int RJ = kD / NJQ;        // rows per block
-  constexpr int AL = S / 8;           // 16-byte loads of one alpha array (one per thread)
   constexpr int NR = NH * kD / NTHR;  // (head, channel) items per thread
   constexpr int NRC = NH * kD / NTC;  // the same per plane-building thread
   constexpr int NPI = (NH * 4 * NP * 8 + NTC - 1) / NTC;    // plane items per thread
-  static_assert(NTILE % 4 == 0, "a wave owns whole 64-token chunks (and tile pairs)");
-  static_assert(kMaxNH * (kD / 4) <= 64 * NW, "the merge takes one (head, 4 columns) slot per thread");
-  static_assert(AL <= NTHR && NR >= 1, "thread mapping");
-  static_assert(!APPEND || NW == 8, "the fused append maps one tensor to 256 threads");
+  static_assert(NTILE % 4 == 0, "a wave owns whole 64-token blocks (and tile pairs)");
+  static_assert(kMaxNH * (kD / 4) <= NTHR, "the merge takes one (head, 4 columns) slot per thread");
+  static_assert(NR >= 1 && NCH % 2 == 0, "thread mapping");
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ unsigned qmx[NH];
   __shared__ int fexp_s[NH];
   __shared__ float wmax[NW][NH], wsum[NW][NH], wpa[NW][NH];
-  __shared__ int fv_s[NH];
+  __shared__ float mfin[NH];
   __shared__ float chs[NH];           // midrise: the half-step term of each head's scores
   __shared__ float wpav[NW][NH];      // sum of P alpha^V per wave and head
   __shared__ unsigned csync;          // arrivals of the plane-building waves
+  __shared__ int hdr_s[6];            // V budget, widest V code, V and K quantizer, record bytes
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4, hc = n >> 2, L = n & 3;
+  // The scalar arguments arrive in registers with the wave (kernel argument preloading); the
+  // first loads need nothing else.  `shape`: query heads
+  // per KV head (bits 0-7), their groups (8-15), evenly dealt (16), bf16 queries (17).
+  const int all_heads = (int)(shape & 0xff), hg = (int)((shape >> 8) & 0xff);
+  const bool even = (shape & 0x10000u) != 0, q_bf = (shape & 0x20000u) != 0;
   // XCD-aware order (grid a multiple of 8): workgroups are dealt to the 8 XCDs round
-  // robin, so consecutive splits of a (sequence, KV head) are given block ids that land
-  // on one XCD.  The grid is exactly rows x splits, so no workgroup exits early (an early
-  // exit would split the argument loads into dependent round trips).
+  // robin, so consecutive runs of a (sequence, KV head) are given block ids that land on
+  // one XCD.
   const int nb8 = (int)(gridDim.x >> 3);
   const int lb = (gridDim.x & 7) ? (int)blockIdx.x
                                  : (int)(blockIdx.x & 7) * nb8 + (int)(blockIdx.x >> 3);
-  const int row32 = lb / a.n_splits;                 // (32-bit: rows x splits < 2^30)
-  const int split = lb - row32 * a.n_splits;
-  const int seq = row32 / a.n_kv_heads, kvh = row32 - seq * a.n_kv_heads;
-  const int64_t row = row32;
-  const int len_raw = a.seq_len[seq];               // first: its round trip gates the cache loads
+  // The workgroup's row (sequence, KV head, group of NH query heads), its run of `per`
+  // chunks and the row's number of runs.  Evenly dealt: every row has the same number of
+  // workgroups (known without a load).  Otherwise by the lengths (assign_runs).
+  int vrow, split, ns, per, len_raw;
+  if (even) {
+    vrow = lb / n_splits;                            // (32-bit: rows x splits < 2^30)
+    split = lb - vrow * n_splits;
+    // (one sequence: known without a division)
+    len_raw = seq_len[batch == 1 ? 0 : vrow / (n_kv_heads * hg)];   // gates the cache loads
+  } else {
+    if (!assign_runs<S, APPEND>(seq_len, a.cap, batch, n_kv_heads * hg, lb, vrow, split, ns, per,
+                                len_raw))
+      return;
+  }
   __builtin_amdgcn_sched_barrier(0);
-  const int G = a.G, RK = a.rk, RV = a.rv;
+  const int row32 = hg == 1 ? vrow : vrow / hg, hgi = vrow - row32 * hg;
+  const int seq = batch == 1 ? 0 : row32 / n_kv_heads, kvh = row32 - seq * n_kv_heads;
+  const int64_t row = row32;
+  const int RK = a.rk, RV = a.rv;
+  const int G = min(NH, all_heads - NH * hgi);        // query heads of this workgroup
   const int RWK = RK >> 2;
-  const HeadParams* hk = head_params(a.params_k, kvh);
-  const HeadParams* hv = head_params(a.params_v, kvh);
-  const int t0 = split * S;
+  const HeadParams* hk = head_params(params_k, kvh);
+  const HeadParams* hv = head_params(params_v, kvh);
 
-  // (0) Loads that need nothing, by the plane-building threads (tc < NTC): the channel
-  //     tables of channel cq, T_K rows RJ jq .. RJ jq + RJ - 1 at columns 4 c4 .. + 3,
-  //     the bit descriptors, the queries, and (fused append) their share of the new
-  //     token's transform.  Loads are unconditional (clamped indices or empty
-  //     descriptors), so the wait counters stay exact.
-  const bool cw = !DMA || wave < NWC;                 // builds the query planes (per wave)
+  // (0) Loads that need nothing, by the plane-building threads (tc < NTC): T_K rows
+  //     RJ jq .. RJ jq + RJ - 1 at columns 4 c4 .. + 3, the bit descriptors, the queries, and
+  //     (fused append) their share of the new token's transform.  Loads are unconditional
+  //     (clamped indices or empty descriptors), so the wait counters stay exact.
+  const bool cw = wave < NWC;                         // builds the query planes (per wave)
   // The query transform: lane l of plane-building wave w holds T_K rows RJ jq .. + RJ - 1
   // (row block jq = l / 8) at columns 4 c4 .. + 3 (c4 = 8 w + l % 8), so the sums over the
   // row blocks stay inside the wave.
@@ -1386,18 +1488,17 @@ void decode_mfma_kernel(const DecodeArgs a) {
   float ksq[NVL];
   int kbq[NVL];
   float khs[2];                       // key half steps of channels lane and lane + 64
-  // The channel tables (used only after the value phase): with eight waves every wave loads
-  // them after the join.  In the front they would queue behind the cache stream, and the
-  // wait before the join would then cover them.
-  int vbc = 0, voc = 0, v_budget = 0, v_maxb = 0;
+  // The channel tables, used only after the last value phase and loaded at its start.  In the
+  // front they would queue behind the cache stream, and the wait before the join would then
+  // cover them.  Values that steer uniform code come from a plane-building wave through LDS
+  // (a scalar load would hold up every LDS wait until it returns).
+  int vbc = 0, voc = 0;
   float vsc = 0.f, vhs = 0.f;
   // Fused append: waves 0 and 1 encode the key and the value token, lane l channels l and
   // l + 64 (their widths, first bits and scales).
   int e_b[2] = {0, 0}, e_off[2] = {0, 0};
   float e_s[2] = {0.f, 0.f};
-  bool e_mr = false;
   auto load_tables = [&]() {
-    v_budget = hv->budget;
     if (APPEND && wave < 2) {
       const HeadParams* eh = wave == 0 ? hk : hv;
 #pragma unroll
@@ -1406,24 +1507,21 @@ void decode_mfma_kernel(const DecodeArgs a) {
         e_off[i] = eh->bit_off[lane + 64 * i];
         e_s[i] = eh->s[lane + 64 * i];
       }
-      // (read here, not in the merge: a load there waits a full round trip)
-      e_mr = eh->quantizer == AATC_QUANT_MIDRISE;
     }
     vbc = hv->bits[cq];
     voc = hv->bit_off[cq];
     vsc = hv->s[cq];
     vhs = hv->half_step[cq];
-    v_maxb = hv->max_bits;
   };
+  int hdr = 0;                        // wave 0, lanes 0..5: the fields of hdr_s
   v4f tr[RJ];
   uint2 desc[NPI];
-  const bool q_bf = a.q_dtype == AATC_BF16;
   uint32_t qraw[NRC];
   bool qhi[NRC];
-  // Fused append: dot products d = split + n_splits k, k = wave + NWC i, of the 2 x 128
-  // (key channels, then value channels); the first two of each plane-building wave are
-  // fetched up front (the token's two elements of this lane and the matching two of
-  // column d % kD of Tq), further ones (fewer than 32 splits) when they are computed.
+  // Fused append: dot products d = split + ns k, k = wave + NWC i, of the 2 x 128 (key
+  // channels, then value channels); the first two of each plane-building wave are fetched
+  // up front (the token's two elements of this lane and the matching two of column d % kD of
+  // Tq), further ones (fewer than 32 runs) are formed by the transfer waves, one per lane.
   const int x_eb = a.x_dtype == AATC_BF16 ? 2 : 4;
   constexpr int KF = 2;                               // coefficients fetched up front
   int adk[KF];
@@ -1442,27 +1540,35 @@ void decode_mfma_kernel(const DecodeArgs a) {
       tr[jj] = reinterpret_cast<const v4f*>(hk->T)[(RJ * jq + jj) * (kD / 4) + c4];
     khs[0] = hk->half_step[lane];
     khs[1] = hk->half_step[lane + 64];
+    if (wave == 0 && lane < 6) {
+      const int32_t* f = lane == 0 ? &hv->budget : lane == 1 ? &hv->max_bits
+                       : lane == 2 ? &hv->quantizer : lane == 3 ? &hk->quantizer
+                       : lane == 4 ? &hk->record_bytes : &hv->record_bytes;
+      hdr = *f;
+    }
     // Plane items (head, record dword D, bit d of each byte): the 4 record bits 32 D +
     // 8 j + d, j = 0..3, of one head.
 #pragma unroll
     for (int r = 0; r < NPI; ++r) {
-      const int dd = (r * NTC + tid) % (8 * RWK);                // < 128: in the table
+      const int dd = (r * NTC + tid) % (8 * RWK);                // < 8 RWK: in the table
       desc[r] = reinterpret_cast<const uint2*>(hk->bit_desc)[dd];
     }
     // Queries, element r NTC + tid, read as the aligned dword that holds the element
     // (either type, no branch; the dword never leaves the element's page).
-    const int64_t qb = ((int64_t)seq * a.n_q_heads + kvh * G) * kD;
+    const int64_t qb = ((int64_t)row * all_heads + NH * hgi) * kD;
 #pragma unroll
     for (int r = 0; r < NRC; ++r) {
       const int64_t i = qb + min(r * NTC + tid, G * kD - 1);
-      const uintptr_t ad = reinterpret_cast<uintptr_t>(a.q) + (q_bf ? 2 * i : 4 * i);
+      const uintptr_t ad = reinterpret_cast<uintptr_t>(q) + (q_bf ? 2 * i : 4 * i);
       qraw[r] = *reinterpret_cast<gdword>(ad & ~(uintptr_t)3);
       qhi[r] = (ad & 2) != 0;
     }
+  };
+  auto front_coefficients = [&]() {
     if constexpr (APPEND) {
 #pragma unroll
       for (int f = 0; f < KF; ++f) {
-        const int d = __builtin_amdgcn_readfirstlane(split + a.n_splits * (wave + NWC * f));
+        const int d = split + ns * (wave + NWC * f);
         adk[f] = d;
         const bool on = d < 2 * kD;
         const HeadParams* eh = d >= kD ? hv : hk;
@@ -1480,17 +1586,24 @@ void decode_mfma_kernel(const DecodeArgs a) {
     }
   };
 
-  Partial* parts = a.partials + row * a.n_splits * G;
-  float* out_rows = a.out + ((int64_t)seq * a.n_q_heads + kvh * G) * kD;
+  // The loads that do not need the length go out before its round trip.
+  if (cw) front_loads();
+  __builtin_amdgcn_sched_barrier(0);
   const int len = (int)min<int64_t>(max(len_raw, 0), a.cap);
-  // With a fused append the splits stop short of the new token at len - 1; the merging
+  // With a fused append the chunks stop short of the new token at len - 1; the merging
   // workgroup encodes it and adds it to the merge.
-  const int nt = max(0, min(S, (APPEND ? len - 1 : len) - t0));
-
-  // (1) This split's packed cache (loads past the capacity read 0).  The layout check
-  //     below gates the compute, not these loads.
-  const int n_load = min(S, (nt + kTile - 1) / kTile * kTile);
-  const int nk16 = n_load * RK / 16, nv16 = n_load * RV / 16, na16 = n_load / 8;
+  const int len_c = max(0, APPEND ? len - 1 : len);
+  const int nchunk = (len_c + S - 1) / S;
+  if (even) {
+    // runs of the row (the other workgroups exit)
+    per = 1;
+    ns = max(1, nchunk);
+    if (nchunk > n_splits) {
+      per = (nchunk + n_splits - 1) / n_splits;
+      ns = (nchunk + per - 1) / per;
+    }
+  }
+  // (1) The run's packed cache (loads past the capacity read 0).
   const __amdgpu_buffer_rsrc_t krs = make_rsrc(a.k_codes + row * a.cap * RK, (uint32_t)(a.cap * RK));
   const __amdgpu_buffer_rsrc_t vrs = make_rsrc(a.v_codes + row * a.cap * RV, (uint32_t)(a.cap * RV));
   const __amdgpu_buffer_rsrc_t akrs = make_rsrc(a.k_alpha + row * a.cap, (uint32_t)(a.cap * 2));
@@ -1499,65 +1612,67 @@ void decode_mfma_kernel(const DecodeArgs a) {
   uint8_t* vbuf = smem + a.off_v;
   uint16_t* akb = reinterpret_cast<uint16_t*>(smem + a.off_ak);
   uint16_t* avb = reinterpret_cast<uint16_t*>(smem + a.off_av);
-  // Loads a thread does not need get an offset past the descriptor (they return 0).
-  constexpr uint32_t kNone = 0x80000000u;
-  v4i rk[DMA ? 1 : NLD], rv[DMA ? 1 : NLD], rak, rav;
-  int nv_mine = 0;                                    // value-tile transfers of this wave
-  // 1 KiB transfers straight into LDS (lane l's 16 bytes at 16 l): key records, the token
-  // scales, then the value tiles, dealt to the issuing waves round robin.  Only whole
-  // 1 KiB blocks of the regions are written (their sizes are 1 KiB multiples).
-  auto issue_cache = [&]() {
-    constexpr int NWD = NW - NWC;
-    const int wd = __builtin_amdgcn_readfirstlane(wave - NWC);
-    const int nki = (n_load * RK + 1023) >> 10, nai = (2 * n_load + 1023) >> 10;
-    const int nvi = (n_load * RV + 1023) >> 10;
-    for (int j = wd; j < nki; j += NWD)
+  // 1 KiB transfers straight into LDS (lane l's 16 bytes at 16 l): the key records and the
+  // token scales of chunk c, or its value tiles, dealt to waves w0, w0 + 1, .. (nw of them)
+  // round robin; each returns this wave's count.  Only whole 1 KiB blocks of the regions are
+  // written (their sizes are 1 KiB multiples).  No branch on the chunk's contents: an empty
+  // chunk computes on masked tokens.
+  auto chunk_load = [&](int c) {                      // tokens of chunk c, whole tiles
+    return min(S, (max(0, len_c - c * S) + kTile - 1) / kTile * kTile);
+  };
+  auto issue_keys = [&](int c, int wd, int nw) {
+    const int t0 = c * S, nl = chunk_load(c);
+    const int nki = (nl * RK + 1023) >> 10, nai = (2 * nl + 1023) >> 10;
+    int cnt = 0;
+    for (int j = wd; j < nki; j += nw) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           krs, (__attribute__((address_space(3))) void*)(kbuf + 1024 * j), 16,
           t0 * RK + 1024 * j + 16 * lane, 0, 0, 0);
-    for (int j = wd; j < nai; j += NWD) {
+      ++cnt;
+    }
+    for (int j = wd; j < nai; j += nw) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           akrs, (__attribute__((address_space(3))) void*)((uint8_t*)akb + 1024 * j), 16,
           2 * t0 + 1024 * j + 16 * lane, 0, 0, 0);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           avrs, (__attribute__((address_space(3))) void*)((uint8_t*)avb + 1024 * j), 16,
           2 * t0 + 1024 * j + 16 * lane, 0, 0, 0);
+      cnt += 2;
     }
-    for (int j = wd; j < nvi; j += NWD) {
+    return cnt;
+  };
+  auto issue_values = [&](int c, int wd, int nw) {
+    const int t0 = c * S, nvi = (chunk_load(c) * RV + 1023) >> 10;
+    int cnt = 0;
+    for (int j = wd; j < nvi; j += nw) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           vrs, (__attribute__((address_space(3))) void*)(vbuf + 1024 * j), 16,
           t0 * RV + 1024 * j + 16 * lane, 0, 0, 0);
-      ++nv_mine;
+      ++cnt;
     }
+    return cnt;
   };
-  // No branch on the split's contents: an empty split computes on masked tokens and
-  // stores (m, l, o~) = (-inf, 0, 0); records that do not match the parameters store a
-  // NaN maximum (the value budget is clamped to the record so LDS accesses stay in range).
-  const bool layout_ok = (hk->record_bytes == RK) & (hv->record_bytes == RV);
-  const __amdgpu_buffer_rsrc_t prs =
-      make_rsrc(parts, (uint32_t)(a.n_splits * G * sizeof(Partial)));
+  // Records that do not match the parameters store a NaN maximum (the value budget is
+  // clamped to the record so LDS accesses stay in range).
+  Partial* parts = a.partials + (row * all_heads + NH * hgi) * a.max_splits;
+  float* out_rows = a.out + (row * all_heads + NH * hgi) * kD;
+  const __amdgpu_buffer_rsrc_t prs = make_rsrc(parts, (uint32_t)(ns * G * sizeof(Partial)));
 
   // (2) Query planes, by the plane-building waves; they synchronize among themselves
-  //     (the other waves are busy issuing the cache) through an LDS arrival count, or
-  //     through workgroup barriers when every wave builds.
+  //     (the other waves are busy issuing the cache) through an LDS arrival count.
   unsigned csync_target = 0u;
   auto plane_sync = [&]() {
-    if constexpr (DMA) {
-      csync_target += NWC;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      if (lane == 0) __hip_atomic_fetch_add(&csync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      while (__hip_atomic_load(&csync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < csync_target)
-        __builtin_amdgcn_s_sleep(1);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    } else {
-      __syncthreads();
-    }
+    csync_target += NWC;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane == 0) __hip_atomic_fetch_add(&csync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (__hip_atomic_load(&csync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < csync_target)
+      __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   };
-  // Scratch of the planes: over the value operands (written only after the planes) with
-  // eight waves, over the cache region with four (the cache lands after the planes).
-  float* scr = reinterpret_cast<float*>(smem + (DMA ? a.off_pb : 0));   // [NJQ][NH][kD]
-  float* qs = scr + NJQ * NH * kD;                                     // [NH][kD]
-  float* qcl = scr;                                  // [NH][kD]
+  // The channel weights (kept for the fused append's score); the queries as scratch over
+  // the value operands (written only after the planes).
+  float* qcl = reinterpret_cast<float*>(smem + a.off_qc);              // [NH][kD]
+  float* qs = reinterpret_cast<float*>(smem + a.off_pb);               // [NH][kD]
   uint8_t* ql = smem + a.off_ql;                     // [4][NH][2 NP][64]
   float rcf[KF] = {0.f, 0.f};                        // fused append: this wave's coefficients
   float reh[KF] = {0.f, 0.f};                        // and the token's error bounds
@@ -1703,104 +1818,151 @@ void decode_mfma_kernel(const DecodeArgs a) {
       append_coefficients<KF>(ax, atq, a.x_dtype, a_inv_s, rcf, reh);  // (past 2 kD: unused)
   };
 
-  // (3) Front.  Eight waves: the plane-building and the issuing waves take separate arms
-  //     up to the barrier where the key records and scales have landed; the value tiles
-  //     keep landing through the key phase.  The barriers are plain s_barrier after
-  //     explicit waits: __syncthreads() would make the issuing waves wait for all of their
-  //     transfers.  The explicit vmcnt(0) waits cost nothing (no load of the wave is in
-  //     flight there) but tell the compiler so: with the two arms merged, it would
-  //     otherwise take the other arm's loads as pending and wait on them later with counts
-  //     that also cover the cache transfers.
-  if constexpr (DMA) {
-    if (cw) {
-      front_loads();
-      if (tid < NH) qmx[tid] = 0u;
-      if (tid == 0) csync = 0u;
-      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-      plain_barrier();                               // the small loads are queued first
-      build_planes();
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    } else {
-      plain_barrier();
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);
-      issue_cache();
-      wait_vmcnt(nv_mine);                           // key records and scales landed
+  // Fused append with fewer than 32 runs: the coefficients that the plane-building waves do
+  // not cover, one per lane of the transfer waves (index i = KF + lane): exact integer sums
+  // over the lane's column of Tq, with the tokens' integers in LDS.  (One coefficient per wave
+  // at a time took 40 us for a row of one run: a round trip and a wave reduction each.)
+  float r_tail = 0.f, eh_tail = 0.f;
+  const int d_tail = split + ns * ((wave & (NWC - 1)) + NWC * (KF + lane));
+  auto tail_coefficients = [&]() {
+    int* xi = reinterpret_cast<int*>(smem + a.off_es);   // [2][kD] (the merge's scratch later)
+    int shift[2];
+    float eh[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const uint8_t* xr = static_cast<const uint8_t*>(t ? a.x_v : a.x_k) + row * kD * x_eb;
+      const float xa = load_elem(xr, a.x_dtype, lane), xb = load_elem(xr, a.x_dtype, lane + 64);
+      shift[t] = token_shift(wave_max_dpp(fmaxf(fabsf(xa), fabsf(xb))));
+      const float va = ldexpf(xa, shift[t]), vb = ldexpf(xb, shift[t]);
+      const float ra = rintf(va), rb = rintf(vb);
+      eh[t] = ldexpf(wave_sum_dpp(fabsf(va - ra) + fabsf(vb - rb)) * (1.f + 0x1p-16f), -shift[t]);
+      xi[t * kD + lane] = (int)ra;                   // (every transfer wave writes the same values)
+      xi[t * kD + lane + 64] = (int)rb;
     }
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    plain_barrier();
-    load_tables();
-  } else {
-    front_loads();
-    load_tables();
+    const bool tv = (d_tail & kD) != 0;              // value channel (past 2 kD: unused)
+    const HeadParams* eh_p = tv ? hv : hk;
+    const int c = d_tail & (kD - 1);
+    const int4* tc = reinterpret_cast<const int4*>(eh_p->Tqt + c * kD);
+    const int4* xq = reinterpret_cast<const int4*>(xi + (tv ? kD : 0));
+    const float isv = eh_p->inv_s[c];
+    long long H = 0;
+#pragma unroll
+    for (int jb = 0; jb < kD / 4; jb += 16) {
+      int4 t4[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) t4[q] = tc[jb + q];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int4 x4 = xq[jb + q];
+        H += (long long)x4.x * t4[q].x;
+        H += (long long)x4.y * t4[q].y;
+        H += (long long)x4.z * t4[q].z;
+        H += (long long)x4.w * t4[q].w;
+      }
+    }
+    r_tail = integer_result((double)H, tv ? shift[1] : shift[0]) * isv;
+    eh_tail = tv ? eh[1] : eh[0];
+  };
+
+  // (3) Front.  The plane-building and the issuing waves take separate arms up to the
+  //     barrier where the key records and scales have landed; the value tiles keep landing
+  //     through the key phase.  The barriers are plain s_barrier after explicit waits:
+  //     __syncthreads() would make the issuing waves wait for all of their transfers.  The
+  //     explicit vmcnt(0) waits cost nothing (no load of the wave is in flight there) but
+  //     tell the compiler so: with the two arms merged, it would otherwise take the other
+  //     arm's loads as pending and wait on them later with counts that also cover the cache
+  //     transfers.
+  const int c0 = split * per, c1 = min(c0 + per, nchunk);   // (an empty row runs one empty chunk)
+  if (split >= ns) return;                           // (whole workgroup, before any barrier)
+  if (cw) {
+    front_coefficients();
     if (tid < NH) qmx[tid] = 0u;
     if (tid == 0) csync = 0u;
-    // Each wave issues its key records and token scales ahead of its value tiles.
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int idx = tid + i * NTHR;
-      rk[i] = buf_load16<0>(krs, idx < nk16 ? (uint32_t)(t0 * RK + 16 * idx) : kNone);
-    }
-    {
-      const uint32_t aoff = (tid < na16) ? (uint32_t)(2 * t0 + 16 * tid) : kNone;
-      rak = buf_load16<0>(akrs, aoff);
-      rav = buf_load16<0>(avrs, aoff);
-    }
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int idx = tid + i * NTHR;
-      rv[i] = buf_load16<0>(vrs, idx < nv16 ? (uint32_t)(t0 * RV + 16 * idx) : kNone);
-    }
-    // Keep the compiler from moving work that waits on the early loads above the cache loads.
-    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    plain_barrier();                                 // the small loads are queued first
     build_planes();
-    __syncthreads();                                 // the planes' scratch is consumed
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int idx = tid + i * NTHR;
-      if (idx < nk16) reinterpret_cast<v4i*>(kbuf)[idx] = rk[i];
-    }
-    if (tid < na16) {
-      reinterpret_cast<v4i*>(akb)[tid] = rak;
-      reinterpret_cast<v4i*>(avb)[tid] = rav;
-    }
-    __syncthreads();
+    if (wave == 0 && lane < 6) hdr_s[lane] = hdr;
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  } else {
+    plain_barrier();
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    issue_keys(c0, wave - NWC, NW - NWC);
+    const int nv_mine = issue_values(c0, wave - NWC, NW - NWC);
+    if (APPEND && ns * NWC * KF < 2 * kD) tail_coefficients();
+    wait_vmcnt(nv_mine);                             // key records and scales landed
   }
-  v4i bq[NT][2 * NP];
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  plain_barrier();
+  const int v_budget = __builtin_amdgcn_readfirstlane(hdr_s[0]);
   float sfx[NT], chk[NT];
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
-    const int h = 4 * rt + hc;
-#pragma unroll
-    for (int s = 0; s < 2 * NP; ++s)
-      bq[rt][s] = *reinterpret_cast<const v4i*>(ql + ((L * NH + h) * 2 * NP + s) * 64 + 16 * g);
     sfx[rt] = ldexpf(1.f, -fexp_s[4 * rt + g]);   // (the head of this lane's scores)
     chk[rt] = chs[4 * rt + g];
   }
-  // Q_c of every head for channels lane and lane + 64, for the fused append's key token
-  // (eight waves: the planes' scratch is intact until the softmax writes the value
-  // operands).
-  float qk[2][NH] = {};
-  if constexpr (APPEND) {
-    if (wave == 0) {
+  // The value phase's constants.  Value-bit tiles of 16 bits are dealt to the waves round
+  // robin; the chunk's 64-token blocks go in two halves: waves 0-3 take the first half of
+  // every tile, waves 4-7 the second (each reads only its half's P operands), and the two
+  // groups walk the tiles in opposite orders, so that the two waves of a SIMD (s and s + 4)
+  // have the same number of tiles between them on every SIMD.
+  const int BV = min(v_budget, 8 * RV);
+  const int NVT = (BV + 15) >> 4;
+  const uint32_t m0 = 0x01010101u << (2 * g), m1 = m0 << 1;
+  constexpr int NCW = NCH / 2;                        // blocks of a wave's tile pass
+  constexpr int NWT = NW / 2;                         // waves over the tiles of one half
+  const int hf = wave >> 2;                           // this wave's half of the blocks
+  const int wj = hf ? 3 - (wave & 3) : (wave & 3);    // its first tile
+  v4i* pb = reinterpret_cast<v4i*>(smem + a.off_pb);  // [NCH][NT][64] value operands
+  const v4i* pbh = pb + hf * NCW * NT * 64;
+  // LDS address of this lane's value-bit dword pair in each block of the half for tile
+  // vt = wj; tile wj + NWT it is 128 NWT it bytes further (an immediate offset: no address
+  // arithmetic in the loop).
+  uint32_t vaddr[NCW];
+  {
+    const uint32_t vb = (uint32_t)reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) uint8_t*)vbuf) + 8 * n + 128 * wj;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int h = 0; h < NH; ++h) qk[i][h] = qcl[h * kD + lane + 64 * i];
+    for (int ch = 0; ch < NCW; ++ch) {
+      vaddr[ch] = vb + (hf * NCW + ch) * kTile * RV;
+      asm volatile("" : "+v"(vaddr[ch]));          // computed once, not per tile
     }
   }
+  // Records of at most 64 bytes (NP <= 4) have up to 32 tiles, wider ones up to 64.
+  constexpr int kMaxIt = (NP <= 4 ? 32 : 64) / NWT;
+  // Running state of the run: the maximum per head, and per lane the sums of P and P alpha^V
+  // (of its tokens) and the value sums of its bits (value bit 16 vt + n of head 4 rt + g), all
+  // relative to that maximum.
+  float mrun[NT], lrun[NT], parun[NT], oacc[kMaxIt][NT];
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    mrun[rt] = -INFINITY;
+    lrun[rt] = parun[rt] = 0.f;
+#pragma unroll
+    for (int it = 0; it < kMaxIt; ++it) oacc[it][rt] = 0.f;
+  }
+  const uint32_t sel_a = (L & 2) ? 0x03020706u : 0x05040100u;
+  const uint32_t sel_b = (L & 1) ? 0x03070105u : 0x06020400u;
+  const int wb = wave * TW;
 
+  for (int c = c0;; ++c) {
+  const int nt = max(0, min(S, len_c - c * S));
+  const bool more = c + 1 < c1;
   // (4) Key scores of this wave's tokens.  The query planes are the A operand (row 4 h + L:
   //     head h, limb L) and the record bits the B operand (column: token), so lane 16 h + n
   //     ends with the four limb sums of head h for token n of the tile and recombines them
   //     itself.
-  const int wb = wave * TW;
   float zr[NTILE][NT];
   float avt[NTILE];
   float lav[NTILE];                      // log2 alpha^V (-inf for 0 and past the tokens)
-  // Every tile's record dwords and token scales first (one LDS round trip), then the
-  // products; lane group g holds record dwords g NP .. g NP + NP - 1, and dwords past the
-  // record (they belong to the next token) meet zero query weights.
+  // The query planes, every tile's record dwords and the token scales first (one LDS round
+  // trip), then the products; lane group g holds record dwords g NP .. g NP + NP - 1, and
+  // dwords past the record (they belong to the next token) meet zero query weights.
+  v4i bq[NT][2 * NP];
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+    for (int s = 0; s < 2 * NP; ++s)
+      bq[rt][s] = *reinterpret_cast<const v4i*>(ql + ((L * NH + 4 * rt + hc) * 2 * NP + s) * 64 + 16 * g);
   uint32_t wda[NTILE][NP];
   uint16_t aka[NTILE], ava[NTILE];
 #pragma unroll
@@ -1864,8 +2026,8 @@ void decode_mfma_kernel(const DecodeArgs a) {
     }
   }
 
-  // (5) Softmax: one maximum per head over the workgroup, and one fixed-point exponent
-  //     per head for P alpha^V from its largest value, max_i 2^(z_i - m) alpha^V_i =
+  // (5) Softmax: one maximum per head over the run so far, and one fixed-point exponent per
+  //     head for the chunk's P alpha^V from its largest value, max_i 2^(z_i - m) alpha^V_i =
   //     2^(max_i (z_i + log2 alpha^V_i) - m) (both maxima in one reduction).
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
@@ -1882,26 +2044,32 @@ void decode_mfma_kernel(const DecodeArgs a) {
       wpa[wave][4 * rt + g] = m2;
     }
   }
-  __syncthreads();
-  float mh[NT];
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  plain_barrier();                       // maxima in; every key record and scale of the chunk read
+  int nk_mine = 0;
+  if (more) nk_mine = issue_keys(c + 1, wave, NW);
+  float mh[NT], sa[NT];
   int fvh[NT];
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
-    mh[rt] = wmax[0][4 * rt + g];
-    float m2 = wpa[0][4 * rt + g];
+    float m = wmax[0][4 * rt + g], m2 = wpa[0][4 * rt + g];
 #pragma unroll
     for (int w = 1; w < NW; ++w) {
-      mh[rt] = fmaxf(mh[rt], wmax[w][4 * rt + g]);
+      m = fmaxf(m, wmax[w][4 * rt + g]);
       m2 = fmaxf(m2, wpa[w][4 * rt + g]);
     }
+    mh[rt] = fmaxf(mrun[rt], m);
+    // The rescale of the run's sums (nothing summed yet: they are 0).
+    sa[rt] = mrun[rt] == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun[rt] - mh[rt]);
+    mrun[rt] = mh[rt];
     // P alpha^V <= 2^(m2 - m) < 2^e; one bit of margin for the hardware exp2 and log2,
-    // so P alpha^V 2^fv < 2^30.
+    // so P alpha^V 2^fv < 2^30.  (A chunk far below the run's maximum: e is held at -90, so
+    // that 2^fv stays in range; what that rounds away is below 2^-119 of the sum.)
     int e = 0;
     frexpf(__builtin_amdgcn_exp2f(m2 - mh[rt]), &e);
-    fvh[rt] = m2 > -INFINITY ? 29 - e : 0;
-    if (n == 0 && wave == 0) fv_s[4 * rt + g] = fvh[rt];
+    fvh[rt] = m2 > -INFINITY ? 29 - max(e, -90) : 0;
   }
-  // Token 16 q + 4 e + L of a chunk sits at bit d = 2 e + q % 2 of its value byte; this
+  // Token 16 q + 4 e + L of a block sits at bit d = 2 e + q % 2 of its value byte; this
   // lane's tokens have e = hc.
   float sc_even[NT], sc_odd[NT];
 #pragma unroll
@@ -1909,9 +2077,6 @@ void decode_mfma_kernel(const DecodeArgs a) {
     sc_even[rt] = ldexpf(1.f, fvh[rt] - 2 * hc);
     sc_odd[rt] = (hc == 3 ? -1.f : 1.f) * ldexpf(1.f, fvh[rt] - 2 * hc - 1);
   }
-  const uint32_t sel_a = (L & 2) ? 0x03020706u : 0x05040100u;
-  const uint32_t sel_b = (L & 1) ? 0x03070105u : 0x06020400u;
-  v4i* pb = reinterpret_cast<v4i*>(smem + a.off_pb);  // [NCH][NT][64] value operands
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
     float lsum = 0.f, pasum = 0.f;
@@ -1937,57 +2102,21 @@ void decode_mfma_kernel(const DecodeArgs a) {
       pb[((wave * CPW + ch) * NT + rt) * 64 + 16 * hc + 4 * g + L] =
           (v4i){(int)y[0], (int)y[1], (int)y[2], (int)y[3]};
     }
-    lsum = row16_sum(lsum);
-    pasum = row16_sum(pasum);
-    if (n == 0) {
-      wsum[wave][4 * rt + g] = lsum;
-      wpav[wave][4 * rt + g] = pasum;
-    }
+    lrun[rt] = fmaf(lrun[rt], sa[rt], lsum);
+    parun[rt] = fmaf(parun[rt], sa[rt], pasum);
   }
-  // The value tiles: the issuing waves wait for the rest of their transfers, or every
-  // wave stores its registers (their region held nothing since the query transform).
-  if constexpr (DMA) {
-    // (Every wave: no load of the plane-building waves is in flight here, and the explicit
-    // wait keeps the compiler from carrying the issuing waves' loads past this point.)
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  } else {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int idx = tid + i * NTHR;
-      if (idx < nv16) reinterpret_cast<v4i*>(vbuf)[idx] = rv[i];
-    }
-  }
-  __syncthreads();
+  // The value tiles have landed (the next chunk's key transfers, issued after them, may
+  // still be in flight).
+  wait_vmcnt_small(nk_mine);
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  plain_barrier();
 
-  // (6) Value bits x P limbs; value-bit tiles of 16 bits are dealt to the waves round
-  //     robin.  O'(v) goes to LDS (over the consumed key records).  With eight waves the
-  //     chunks go in two halves: waves 0-3 take the first half of every tile, waves 4-7
-  //     the second (each reads only its half's P operands, and O' has one copy per half),
-  //     and the two groups walk the tiles in opposite orders, so that the two waves of a
-  //     SIMD (s and s + 4) have the same number of tiles between them on every SIMD.
-  const int BV = min(v_budget, 8 * RV);
-  const int NVT = (BV + 15) >> 4;
-  const uint32_t m0 = 0x01010101u << (2 * g), m1 = m0 << 1;
-  constexpr bool kHalves = NW == 8 && NCH % 2 == 0;
-  constexpr int NCW = kHalves ? NCH / 2 : NCH;        // chunks of a wave's tile pass
-  constexpr int NWT = kHalves ? NW / 2 : NW;          // waves over the tiles of one half
-  const int hf = kHalves ? (wave >> 2) : 0;           // this wave's chunk half
-  const int wj = kHalves ? (hf ? 3 - (wave & 3) : (wave & 3)) : wave;   // its first tile
-  float* ob = reinterpret_cast<float*>(smem + a.off_ob);   // [halves][NH][ob_stride]
-  // T_V for the merge: with eight waves every split loads its matrix-core operands during
-  // the value loop (32 VGPRs, one k-step per tile, so that the loads never back up the
-  // memory queue), and the split that merges has them at hand.  Otherwise each split
-  // touches a slice of T_V, so that the merging one finds it in its XCD's L2 (the splits of
-  // a (sequence, KV head) run on one XCD: block order above).
-  constexpr bool kTvHeld = TvMfma<NTHR>::NPASS == 1;
-  TvMfma<NTHR> tv;
-  uint32_t tv_touch = 0u;
-  if constexpr (!kTvHeld)
-    tv_touch = reinterpret_cast<gdword>(reinterpret_cast<uintptr_t>(hv->Tm))[
-        (split * NTHR + tid) * 16 % (kD * kD)];
-  // A operands (this half's chunks) stay in registers when they fit (16 x 4 VGPRs).
+  // (6) Value bits x P limbs, into the run's sums.
+  if (!more) {
+    load_tables();
+  }
+  // A operands (this half's blocks) stay in registers when they fit (16 x 4 VGPRs).
   constexpr bool kPbRegs = NCW * NT <= 16;
-  const v4i* pbh = pb + hf * NCW * NT * 64;
   v4i pbr[kPbRegs ? NCW * NT : 1];
   if constexpr (kPbRegs) {
     // All reads first (one LDS round trip), then the pins that keep them in registers
@@ -1997,27 +2126,13 @@ void decode_mfma_kernel(const DecodeArgs a) {
 #pragma unroll
     for (int i = 0; i < NCW * NT; ++i) asm volatile("" : "+v"(pbr[i]));
   }
-  // LDS address of this lane's value-bit dword pair in each chunk of the half for tile
-  // vt = wj; tile wj + NWT it is 128 NWT it bytes further (an immediate offset: no address
-  // arithmetic in the loop).
-  uint32_t vaddr[NCW];
-  {
-    const uint32_t vb = (uint32_t)reinterpret_cast<uintptr_t>(
-        (__attribute__((address_space(3))) uint8_t*)vbuf) + 8 * n + 128 * wj;
+  float osc[NT];
 #pragma unroll
-    for (int ch = 0; ch < NCW; ++ch) {
-      vaddr[ch] = vb + (hf * NCW + ch) * kTile * RV;
-      asm volatile("" : "+v"(vaddr[ch]));          // computed once, not per tile
-    }
-  }
-  float* obh = ob + hf * NH * a.ob_stride;
-  constexpr int kMaxIt = (64 * 8 / 16 + NWT - 1) / NWT;   // records of at most 64 bytes
+  for (int rt = 0; rt < NT; ++rt) osc[rt] = ldexpf(1.f, -fvh[rt]);
 #pragma unroll
   for (int it = 0; it < kMaxIt; ++it) {
     const int vt = wj + NWT * it;
     if (vt >= NVT) break;                           // (uniform)
-    if constexpr (kTvHeld)
-      if (it < 4) tv.load_step(hv, it);
     // One accumulator per column tile: a dependent product takes its predecessor's result
     // straight from the matrix unit.
     v4i acc[NT];
@@ -2031,7 +2146,7 @@ void decode_mfma_kernel(const DecodeArgs a) {
       wws[ch] = *(const __attribute__((address_space(3))) v2u*)(uintptr_t)(
           vaddr[ch] + 128 * NWT * it);
     // (The scheduler would otherwise pair each read with its products: one LDS round
-    // trip per chunk.)
+    // trip per block.)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ch = 0; ch < NCW; ++ch) {
@@ -2051,49 +2166,65 @@ void decode_mfma_kernel(const DecodeArgs a) {
       float f = fmaf((float)d[3], 256.f, (float)d[2]);
       f = fmaf(f, 256.f, (float)d[1]);
       f = fmaf(f, 256.f, (float)d[0]);
-      obh[(4 * rt + g) * a.ob_stride + 16 * vt + n] = f;
+      oacc[it][rt] = fmaf(oacc[it][rt], sa[rt], f * osc[rt]);
     }
   }
-  if constexpr (kTvHeld) {
-    // (k-steps the loop did not reach: fewer than four tiles for this wave)
-    const int nit = NVT > wj ? (NVT - wj + NWT - 1) / NWT : 0;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      if (kk >= nit) tv.load_step(hv, kk);
+  if (!more) break;
+  // The next chunk's key records have landed and every wave is done with the value tiles
+  // and operands: the value region takes the next chunk's tiles.
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  plain_barrier();
+  issue_values(c + 1, wave, NW);
   }
 
-  __syncthreads();
+  // T_V's matrix-core operands (32 VGPRs): every run loads them, and the one that merges has
+  // them at hand.
+  TvMfma<NTHR> tv;
+  tv.load(hv);
+  // O'(v) of both halves to LDS (over the consumed key records), the sums per wave.
+  float* ob = reinterpret_cast<float*>(smem + a.off_ob);   // [halves][NH][ob_stride]
+  float* obh = ob + hf * NH * a.ob_stride;
+#pragma unroll
+  for (int it = 0; it < kMaxIt; ++it) {
+    const int vt = wj + NWT * it;
+    if (vt >= NVT) break;                           // (uniform)
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) obh[(4 * rt + g) * a.ob_stride + 16 * vt + n] = oacc[it][rt];
+  }
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    const float lsum = row16_sum(lrun[rt]), pasum = row16_sum(parun[rt]);
+    if (n == 0) {
+      wsum[wave][4 * rt + g] = lsum;
+      wpav[wave][4 * rt + g] = pasum;
+      if (wave == 0) mfin[4 * rt + g] = mrun[rt];
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  plain_barrier();
 
-  asm volatile("" ::"v"(tv_touch));      // keeps the touch load
   if constexpr (APPEND) {
     // Fused append: the coefficients into the workspace (device-coherent, before this
-    // workgroup's arrival), and further ones when the row has fewer than 32 splits.
+    // workgroup's arrival).  Coefficient d at d; the wave or lane with the token's first
+    // channel (d = 0 keys, 128 values) also stores the token's error bound at 2 kD + d / kD.
+    const __amdgpu_buffer_rsrc_t rrs = make_rsrc(a.append_r + row * kAppStride, kAppStride * 4);
     if (cw) {
-      // Coefficient d at d; the wave with the token's first channel (d = 0 keys, 128
-      // values) also stores the token's error bound at 2 kD + d / kD.
-      const __amdgpu_buffer_rsrc_t rrs = make_rsrc(a.append_r + row * kAppStride, kAppStride * 4);
 #pragma unroll
       for (int f = 0; f < KF; ++f) {
         if (adk[f] < 2 * kD && lane == 0) buf_store4_coherent(rcf[f], rrs, (uint32_t)(4 * adk[f]));
         if (adk[f] < 2 * kD && (adk[f] & (kD - 1)) == 0 && lane == 0)
           buf_store4_coherent(reh[f], rrs, (uint32_t)(4 * (2 * kD + adk[f] / kD)));
       }
-      for (int d = split + a.n_splits * (wave + NWC * KF); d < 2 * kD; d += a.n_splits * NWC) {
-        const HeadParams* eh = d >= kD ? hv : hk;
-        const int c = d & (kD - 1);
-        const uint8_t* xb = static_cast<const uint8_t*>(d >= kD ? a.x_v : a.x_k) + row * kD * x_eb;
-        const uint32_t xw[1][2] = {{*reinterpret_cast<const uint32_t*>(xb + ((lane * x_eb) & ~3)),
-                                    *reinterpret_cast<const uint32_t*>(xb + (((lane + 64) * x_eb) & ~3))}};
-        const int tw[1][2] = {{eh->Tqt[c * kD + lane], eh->Tqt[c * kD + lane + 64]}};
-        const float isv[1] = {eh->inv_s[c]};
-        float rc[1], ec[1];
-        append_coefficients<1>(xw, tw, a.x_dtype, isv, rc, ec);
-        if (lane == 0) buf_store4_coherent(rc[0], rrs, (uint32_t)(4 * d));
-        if (c == 0 && lane == 0) buf_store4_coherent(ec[0], rrs, (uint32_t)(4 * (2 * kD + d / kD)));
-      }
+    } else if (ns * NWC * KF < 2 * kD && d_tail < 2 * kD) {
+      buf_store4_coherent(r_tail, rrs, (uint32_t)(4 * d_tail));
+      if ((d_tail & (kD - 1)) == 0)
+        buf_store4_coherent(eh_tail, rrs, (uint32_t)(4 * (2 * kD + d_tail / kD)));
     }
   }
-  // (7) Partial: o~_c = s_c 2^(1-b_c-fv) (sum_{k < b-1} 2^k O'(c,k) - 2^(b-1) O'(c,b-1)),
+  const int v_maxb = hdr_s[1];
+  const bool layout_ok = (hdr_s[4] == RK) & (hdr_s[5] == RV);
+  // (7) Partial: o~_c = s_c 2^(1-b_c) (sum_{k < b-1} 2^k O'(c,k) - 2^(b-1) O'(c,b-1)),
   //     one (head, channel) per thread; midrise adds s_c 2^(-b_c) sum_i P_i alpha^V_i
   //     (the half step of every level).
 #pragma unroll
@@ -2104,7 +2235,7 @@ void decode_mfma_kernel(const DecodeArgs a) {
       float acc = 0.f;
       auto bit_term = [&](int k) {
         const int v = min(voc + k, 8 * RV - 1);
-        const float t = ldexpf(kHalves ? oh[v] + oh[NH * a.ob_stride + v] : oh[v], k);
+        const float t = ldexpf(oh[v] + oh[NH * a.ob_stride + v], k);
         acc += (k < vbc) ? ((k == vbc - 1) ? -t : t) : 0.f;
       };
       // (the first eight bits unrolled with their reads issued together; wider codes take
@@ -2115,22 +2246,20 @@ void decode_mfma_kernel(const DecodeArgs a) {
       float pa = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) pa += wpav[w][h];
-      const float o = vbc ? fmaf(vsc * vhs, pa, ldexpf(vsc * acc, 1 - vbc - fv_s[h])) : 0.f;
+      const float o = vbc ? fmaf(vsc * vhs, pa, ldexpf(vsc * acc, 1 - vbc)) : 0.f;
       buf_store4_coherent(o, prs, (uint32_t)((split * G + h) * sizeof(Partial) + 16 + 4 * cq));
     }
   }
   if (tid < G) {
-    float m = wmax[0][tid], l = wsum[0][tid];
+    float l = wsum[0][tid];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      m = fmaxf(m, wmax[w][tid]);
-      l += wsum[w][tid];
-    }
-    buf_store16_coherent((v4f){layout_ok ? m : NAN, l, 0.f, 0.f}, prs,
+    for (int w = 1; w < NW; ++w) l += wsum[w][tid];
+    buf_store16_coherent((v4f){layout_ok ? mfin[tid] : NAN, l, 0.f, 0.f}, prs,
                          (uint32_t)((split * G + tid) * sizeof(Partial)));
   }
   // The merge's scratch: from the start of the front region (its cache and O' are consumed).
   float* merge_scratch = reinterpret_cast<float*>(smem);
+  unsigned* counter = a.counters + row * kCtrStride + 16 * hgi;
   if constexpr (APPEND) {
     AppendHook<NTHR, NH> hook;
     hook.coeff = a.append_r + row * kAppStride;
@@ -2150,26 +2279,22 @@ void decode_mfma_kernel(const DecodeArgs a) {
     hook.rk = RK;
     hook.rv = RV;
     hook.on = len > 0;
-    hook.e_mr = e_mr;
+    hook.e_mr = hdr_s[wave == 0 ? 3 : 2] == AATC_QUANT_MIDRISE;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       hook.e_b[i] = e_b[i];
       hook.e_off[i] = e_off[i];
       hook.e_s[i] = e_s[i];
-#pragma unroll
-      for (int h = 0; h < NH; ++h) hook.qk[i][h] = qk[i][h];
     }
+    hook.qc = qcl;
     hook.sc = reinterpret_cast<AppendScratch*>(smem + a.off_es);
-    merge_if_last_wide<NTHR, NH, kTvHeld>(a.params_v, kvh, row, G, a.n_splits, a.partials,
-                                          a.counters, out_rows, merge_scratch, tv, hook);
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, hook);
   } else if (a.seg) {
-    SegHook sh{a.seg + row * G};
-    merge_if_last_wide<NTHR, NH, kTvHeld>(a.params_v, kvh, row, G, a.n_splits, a.partials,
-                                          a.counters, out_rows, merge_scratch, tv, sh);
+    SegHook sh{a.seg + row * all_heads + NH * hgi};
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, sh);
   } else {
     NoHook none;
-    merge_if_last_wide<NTHR, NH, kTvHeld>(a.params_v, kvh, row, G, a.n_splits, a.partials,
-                                          a.counters, out_rows, merge_scratch, tv, none);
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, none);
   }
 }
 
@@ -2206,41 +2331,57 @@ class LdsLimit {
   std::atomic<size_t> set_[kDevices] = {};
 };
 
-template <int NT, int NTILE, int NP, int NW, bool APPEND>
-static aatc_status launch_mfma(DecodeArgs a, int batch, hipStream_t st) {
-  constexpr int NH = 4 * NT, NTHR = 64 * NW, S = NW * 16 * NTILE;
-  a.n_splits = (int)((a.cap + S - 1) / S);
-  const int64_t rows = (int64_t)batch * a.n_kv_heads;
-  if (rows * a.n_splits > (1 << 30)) return AATC_E_UNSUPPORTED;
-  a.n_blocks = (int)(rows * a.n_splits);
-  // LDS: key records | value tiles | alpha^K | alpha^V   (front, also the query-transform
-  // and merge scratch) | query limb planes | value operands | [O' if it does not fit
-  // over the key records].
-  // Eight waves: the cache streams into LDS while the query planes are built, so their
-  // scratch shares the value-operand region (written only after the planes) instead of
-  // the cache region.  The transfers write whole 1 KiB blocks of the cache regions.
-  constexpr bool DMA = NW == 8;
-  constexpr int NJQ = (DMA ? NTHR / 2 : NTHR) / 32;
-  const size_t scr_bytes = (size_t)(NJQ + 1) * NH * kD * sizeof(float);
-  if (DMA && (((size_t)S * a.rk) % 1024 || ((size_t)S * a.rv) % 1024 || (2 * S) % 1024))
+constexpr int kComputeUnits = 256;
+
+template <int NT, int NTILE, int NP, bool APPEND>
+static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
+  constexpr int NH = 4 * NT, NTHR = 512, S = 128 * NTILE;
+  const int64_t chunks = (a.cap + S - 1) / S;
+  const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
+  if (rows * chunks > (1 << 30)) return AATC_E_UNSUPPORTED;
+  // One workgroup per compute unit: a row's chunks in runs of equal length when every chunk
+  // can have a workgroup, or the batch is one sequence (its rows are equally long); otherwise
+  // runs dealt by the sequences' lengths, at least two workgroups per row.
+  int64_t grid;
+  bool even = a.batch == 1 || rows * chunks <= kComputeUnits;
+  int n_splits = 0;                                   // workgroups per row (even)
+  if (even) {
+    n_splits = (int)std::min(chunks, std::max<int64_t>(1, kComputeUnits / rows));
+    a.max_splits = n_splits;
+    grid = rows * n_splits;
+  } else {
+    a.max_splits = (int)chunks;
+    grid = std::min(rows * chunks, std::max<int64_t>(kComputeUnits, 2 * rows));
+    // (rows x 1 chunk: one run each, which the closed form of assign_runs needs no slack for)
+    if (grid <= rows) {
+      even = true;
+      n_splits = a.max_splits = 1;
+      grid = rows;
+    }
+  }
+  // LDS: key records | value tiles | alpha^K | alpha^V   (front, also the merge scratch) |
+  // query limb planes | channel weights | value operands | [O' if it does not fit over the
+  // key records].  The cache streams into LDS while the query planes are built, so the
+  // planes' scratch shares the value-operand region (written only after the planes).  The transfers write
+  // whole 1 KiB blocks of the cache regions.
+  const size_t qc_bytes = (size_t)NH * kD * sizeof(float);
+  if (((size_t)S * a.rk) % 1024 || ((size_t)S * a.rv) % 1024 || (2 * S) % 1024)
     return AATC_E_UNSUPPORTED;
   a.off_v = S * a.rk;
   a.off_ak = a.off_v + S * a.rv;
   a.off_av = a.off_ak + 2 * S;
   size_t front = (size_t)a.off_av + 2 * S;
-  if (!DMA) front = std::max(front, scr_bytes);
   front = std::max(front, wide_merge_lds_bytes<NTHR, NH>());
   front = round256(front);
   a.off_ql = (int)front;
-  a.off_pb = a.off_ql + 4 * NH * 2 * NP * 64;
-  size_t pb_bytes = (size_t)(S / 64) * NT * 64 * 16;
-  if (DMA) pb_bytes = std::max(pb_bytes, scr_bytes);
-  size_t off = (size_t)a.off_pb + pb_bytes;
+  a.off_qc = a.off_ql + 4 * NH * 2 * NP * 64;
+  a.off_pb = a.off_qc + (int)qc_bytes;
+  size_t off = (size_t)a.off_pb + std::max((size_t)(S / 64) * NT * 64 * 16, qc_bytes);
   a.ob_stride = 8 * a.rv;
-  // O' per (head, value bit); eight waves keep one copy per chunk half.
-  const size_t ob_bytes = (size_t)(NW == 8 && S % 128 == 0 ? 2 : 1) * NH * a.ob_stride * 4;
+  // O' per (half, head, value bit).
+  const size_t ob_bytes = (size_t)2 * NH * a.ob_stride * 4;
   const size_t es_bytes = APPEND ? (sizeof(AppendScratch) + 15) / 16 * 16 : 0;
-  constexpr size_t kLdsMax = 160 * 1024 - 4 * 1024;
+  constexpr size_t kLdsMax = 160 * 1024 - 2 * 1024;   // (static LDS: under 2 KiB)
   if (ob_bytes <= (size_t)S * a.rk) {
     a.off_ob = 0;
   } else {
@@ -2252,38 +2393,38 @@ static aatc_status launch_mfma(DecodeArgs a, int batch, hipStream_t st) {
   const size_t lds = off;
   if (lds > kLdsMax) return AATC_E_UNSUPPORTED;
   static LdsLimit limit;
-  if (!limit.ensure((const void*)decode_mfma_kernel<NT, NTILE, NP, NW, APPEND>, lds))
+  if (!limit.ensure((const void*)decode_mfma_kernel<NT, NTILE, NP, APPEND>, lds))
     return AATC_E_DEVICE;
-  const unsigned grid = (unsigned)a.n_blocks;
-  hipLaunchKernelGGL((decode_mfma_kernel<NT, NTILE, NP, NW, APPEND>), dim3(grid), dim3(NTHR), lds,
-                     st, a);
+  const uint32_t shape = (uint32_t)a.G | (uint32_t)a.hg << 8 | (even ? 0x10000u : 0u) |
+                         (a.q_dtype == AATC_BF16 ? 0x20000u : 0u);
+  hipLaunchKernelGGL((decode_mfma_kernel<NT, NTILE, NP, APPEND>), dim3((unsigned)grid), dim3(NTHR),
+                     lds, st, a.seq_len, a.params_k, a.params_v, a.q, n_splits, a.n_kv_heads,
+                     a.batch, shape, a);
   return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
 }
 
-template <int NT, int NTILE, int NW, bool APPEND>
-static aatc_status launch_mfma_np(const DecodeArgs& a, int batch, hipStream_t st) {
+// NP: record dwords per lane group of the key operands (16 NP bytes of record).
+template <int NT, int NTILE, bool APPEND>
+static aatc_status launch_mfma_np(const DecodeArgs& a, hipStream_t st) {
   switch ((a.rk / 4 + 3) / 4) {
-    case 1: return launch_mfma<NT, NTILE, 1, NW, APPEND>(a, batch, st);
-    case 2: return launch_mfma<NT, NTILE, 2, NW, APPEND>(a, batch, st);
-    case 3: return launch_mfma<NT, NTILE, 3, NW, APPEND>(a, batch, st);
-    default: return launch_mfma<NT, NTILE, 4, NW, APPEND>(a, batch, st);
+    case 1: return launch_mfma<NT, NTILE, 1, APPEND>(a, st);
+    case 2: return launch_mfma<NT, NTILE, 2, APPEND>(a, st);
+    case 3: return launch_mfma<NT, NTILE, 3, APPEND>(a, st);
+    default: return launch_mfma<NT, NTILE, 4, APPEND>(a, st);
   }
 }
 
-// Split size: 1024 tokens on eight waves while that still gives every compute unit a
-// workgroup (and always with a fused append), else 512 on four; records over 96 bytes in
-// all halve both (LDS).
-template <int NT>
-static aatc_status launch_mfma_nt(const DecodeArgs& a, int batch, hipStream_t st) {
-  const bool big = a.rk + a.rv > 96;
-  if (a.x_k) return big ? launch_mfma_np<NT, 4, 8, true>(a, batch, st)
-                        : launch_mfma_np<NT, 8, 8, true>(a, batch, st);
-  const int64_t rows = (int64_t)batch * a.n_kv_heads;
-  const int64_t wide = rows * ((a.cap + (big ? 511 : 1023)) / (big ? 512 : 1024));
-  if (wide >= 256) return big ? launch_mfma_np<NT, 4, 8, false>(a, batch, st)
-                              : launch_mfma_np<NT, 8, 8, false>(a, batch, st);
-  return big ? launch_mfma_np<NT, 4, 4, false>(a, batch, st)
-             : launch_mfma_np<NT, 8, 4, false>(a, batch, st);
+// Chunk size: 1024 tokens while that still gives every compute unit a workgroup, else 512;
+// records over 96 bytes in all take 512 (LDS).
+template <int NT, bool APPEND>
+static aatc_status launch_mfma_nt(const DecodeArgs& a, hipStream_t st) {
+  if (a.rk > 64 || a.rv > 64)
+    return a.rk <= 96 && a.rv <= 96 ? launch_mfma<NT, 4, 6, APPEND>(a, st)
+                                    : launch_mfma<1, 4, 8, APPEND>(a, st);
+  const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
+  if (a.rk + a.rv > 96 || rows * ((a.cap + 1023) / 1024) < kComputeUnits)
+    return launch_mfma_np<NT, 4, APPEND>(a, st);
+  return launch_mfma_np<NT, 8, APPEND>(a, st);
 }
 
 aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
@@ -2317,7 +2458,24 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     seg = sp;
   }
-  if (G <= kMaxNH && rk <= 64 && rv <= 64) {
+  // The matrix-core kernel takes records of up to 128 bytes, eight query heads of a KV head
+  // per workgroup (four for records over 96 bytes, by LDS) and the rest as further workgroups.
+  // Its fused append covers one workgroup row per KV head; other shapes run the per-token
+  // encode first.
+  const bool mfma = rk <= 128 && rv <= 128;
+  const int heads = rk > 96 || rv > 96 ? 4 : kMaxNH;
+  const bool fused = mfma && G <= heads;
+  if (x_k && !fused) {
+    aatc_status e = launch_encode_last(params_k, n_kv_heads, batch, x_k, x_dtype,
+                                       AATC_LAYOUT_RECORDS, const_cast<void*>(k_codes),
+                                       const_cast<uint16_t*>(k_alpha), cap, rk, seq_len, stream);
+    if (e == AATC_OK)
+      e = launch_encode_last(params_v, n_kv_heads, batch, x_v, x_dtype, AATC_LAYOUT_TILES,
+                             const_cast<void*>(v_codes), const_cast<uint16_t*>(v_alpha), cap, rv,
+                             seq_len, stream);
+    if (e != AATC_OK) return e;
+  }
+  if (mfma) {
     DecodeArgs a{};
     a.params_k = params_k;
     a.params_v = params_v;
@@ -2336,24 +2494,19 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
     a.append_r = reinterpret_cast<float*>(ws + wl.append_r);
     a.seg = seg;
     a.cap = cap;
+    a.batch = batch;
     a.n_q_heads = n_q_heads;
     a.n_kv_heads = n_kv_heads;
     a.G = G;
+    a.hg = G <= 4 ? 1 : (G + heads - 1) / heads;
     a.q_dtype = (int)q_dtype;
     a.rk = rk;
     a.rv = rv;
     a.scale_log2e = softmax_scale * kLog2e;
-    return G <= 4 ? launch_mfma_nt<1>(a, batch, st) : launch_mfma_nt<2>(a, batch, st);
-  }
-  if (x_k) {                // generic path: append with the per-token encode kernel first
-    aatc_status e = launch_encode_last(params_k, n_kv_heads, batch, x_k, x_dtype,
-                                       AATC_LAYOUT_RECORDS, const_cast<void*>(k_codes),
-                                       const_cast<uint16_t*>(k_alpha), cap, rk, seq_len, stream);
-    if (e == AATC_OK)
-      e = launch_encode_last(params_v, n_kv_heads, batch, x_v, x_dtype, AATC_LAYOUT_TILES,
-                             const_cast<void*>(v_codes), const_cast<uint16_t*>(v_alpha), cap, rv,
-                             seq_len, stream);
-    if (e != AATC_OK) return e;
+    const bool narrow = G <= 4 || heads == 4;          // four head slots per workgroup
+    if (x_k && fused)
+      return narrow ? launch_mfma_nt<1, true>(a, st) : launch_mfma_nt<2, true>(a, st);
+    return narrow ? launch_mfma_nt<1, false>(a, st) : launch_mfma_nt<2, false>(a, st);
   }
   const int n_splits = (int)((cap + kSplit - 1) / kSplit);
   size_t lds = std::max((size_t)G * (kSplit + 8 * std::max(rk, rv)) * sizeof(float),
