@@ -459,13 +459,16 @@ struct NoHook {
   __device__ void publish() {}
   __device__ void fold(int, int, float&, float&, v4f&) const {}
   __device__ void fold1(int, int, float&, float&, float&) const {}
+  __device__ float add1(int, int, float o) const { return o; }
+  __device__ v4f add4(int, int, v4f o) const { return o; }
   __device__ void finish() {}
 };
 
 // Called by every workgroup after it stored its partial with device-coherent stores.
 // The last of a (sequence, KV head) to arrive merges the split partials.  The hook's
 // loads go out ahead of the partials', its during_loads() (encode(), then the barrier of
-// publish()) runs while they are in flight, fold() adds one more (score, value) term per output slot, finish() runs at the end.
+// publish()) runs while they are in flight, fold() adds one more (score, value) term per output
+// slot, add1() one more term after the inverse transform, finish() runs at the end.
 template <int NTHR, bool TV, bool ONE_PASS = false, class Hook = NoHook>
 __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int64_t row, int G,
                                               int n_splits, const Partial* partials,
@@ -572,7 +575,9 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
   }
   // (b) o = T_V o~ (transformed-domain partials), or o~ itself.
   if constexpr (TV) {
-    tv.apply(osum, ored, G, [&](int h, int j, float o) { out_rows[(int64_t)h * kD + j] = o; });
+    tv.apply(osum, ored, G, [&](int h, int j, float o) {
+      out_rows[(int64_t)h * kD + j] = hook.add1(h, j, o);
+    });
   } else {
     for (int i = tid; i < G * kD; i += NTHR) out_rows[i] = osum[i];
   }
@@ -753,7 +758,7 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
   __syncthreads();
   // o = T_V o~ (the partials are in the transformed domain).
   tv.apply(ob_hi, ob_lo, G, [&](int hh, int j0, v4f o) {
-    *reinterpret_cast<v4f*>(out_rows + (int64_t)hh * kD + j0) = o;
+    *reinterpret_cast<v4f*>(out_rows + (int64_t)hh * kD + j0) = hook.add4(hh, j0, o);
   });
   hook.finish();
   if (tid == 0) *counter = 0u;
@@ -763,143 +768,186 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
 // Full-precision segment (the first tokens and the recent window kept at input precision,
 // Sec. 6 and App. E): exact softmax attention of each query head over the segment's tokens
 // in the original domain, one workgroup per (sequence, KV head), written as one more split
-// partial in the transformed domain (o~ = T_V^T sum_t p_t v_t, with the log2-domain maximum
-// and sum of its weights), which the merge of the compressed-cache splits folds in.
+// partial (log2-domain maximum and sum of its weights, sum_t p_t v_t in the original domain),
+// which the merge of the compressed-cache splits folds in: its weight in the softmax before
+// the inverse transform, its value sum after it.
+//
+// A few tens of KB per workgroup: the time is latency.  Sixteen waves, four tokens per wave at
+// once (16 lanes x 8 elements a row, 16-byte loads), every key load of a wave in flight
+// together; the value sums with a wave per (head, share of the tokens).  Batch 8, 8 KV heads,
+// 132 tokens: 125 us before (a thread per token with scalar loads, and T_V^T applied here).
 // ---------------------------------------------------------------------------------------
-constexpr int kSegThreads = 256;
+constexpr int kSegThreads = 1024;
+constexpr int kSegWaves = kSegThreads / 64;
 constexpr int kSegMax = 256;           // tokens of one segment
+constexpr int kSegIt = kSegMax / (4 * kSegWaves);   // key rows per lane group
+
+// Elements 8 e .. 8 e + 7 of a row as fp32 (vec: rows 16-byte aligned).
+__device__ inline void load_row8(const void* base, int dtype, int64_t row, int e, bool vec,
+                                 float (&v)[8]) {
+  if (vec && dtype == AATC_BF16) {
+    const uint4 u = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + row * kD + 8 * e);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(w[i] << 16);
+      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  } else if (vec) {
+    const v4f* p = reinterpret_cast<const v4f*>(static_cast<const float*>(base) + row * kD + 8 * e);
+    const v4f a = p[0], b = p[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = a[i];
+      v[4 + i] = b[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = load_elem(base, dtype, row * kD + 8 * e + i);
+  }
+}
 
 __global__ __launch_bounds__(kSegThreads) void segment_partial_kernel(
-    const void* __restrict__ params_v, int n_q_heads, int n_kv_heads,
-    const void* __restrict__ q, int q_dtype, const void* __restrict__ seg_k,
-    const void* __restrict__ seg_v, int seg_dtype, const int32_t* __restrict__ seg_len,
-    int seg_cap, float scale_log2e, Partial* __restrict__ seg_out) {
-  __shared__ float qs[kMaxGroup][kD];
+    int n_q_heads, int n_kv_heads, const void* __restrict__ q, int q_dtype,
+    const void* __restrict__ seg_k, const void* __restrict__ seg_v, int seg_dtype,
+    const int32_t* __restrict__ seg_len, int seg_cap, float scale_log2e,
+    Partial* __restrict__ seg_out) {
+  __shared__ __align__(16) float qs[kMaxGroup][kD];
   __shared__ float z[kMaxGroup][kSegMax];
-  __shared__ float orw[kMaxGroup][kD];
-  __shared__ float red[kSegThreads / 64][kMaxGroup];
-  __shared__ float mh[kMaxGroup], lh[kMaxGroup];
+  __shared__ __align__(16) float ored[kSegWaves][kD];
   const int row = blockIdx.x, kvh = row % n_kv_heads, seq = row / n_kv_heads;
   const int G = n_q_heads / n_kv_heads;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, e = lane & 15, tr = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = min(max(seg_len[seq], 0), seg_cap);
-  const int64_t tok0 = (int64_t)row * seg_cap;        // [batch][n_kv_heads][seg_cap][d]
+  Partial* out = seg_out + (int64_t)row * G;
+  if (n == 0) {                                        // (uniform, before any barrier)
+    for (int i = tid; i < G * kD; i += kSegThreads) out[i / kD].o[i % kD] = 0.f;
+    if (tid < G) {
+      out[tid].m = -INFINITY;
+      out[tid].l = 0.f;
+    }
+    return;
+  }
+  const int64_t tok0 = (int64_t)row * seg_cap;         // [batch][n_kv_heads][seg_cap][d]
+  const bool vec = ((reinterpret_cast<uintptr_t>(seg_k) | reinterpret_cast<uintptr_t>(seg_v)) & 15u) == 0u;
+  // Key rows 64 i + 4 wave + tr (past the end clamped to the last row: their logits are
+  // dropped), then the queries.
+  float kr[kSegIt][8];
+#pragma unroll
+  for (int i = 0; i < kSegIt; ++i)
+    if (64 * i < n)                                    // (uniform)
+      load_row8(seg_k, seg_dtype, tok0 + min(64 * i + 4 * wave + tr, n - 1), e, vec, kr[i]);
   for (int i = tid; i < G * kD; i += kSegThreads)
     qs[i / kD][i % kD] =
         load_q(q, q_dtype, ((int64_t)seq * n_q_heads + kvh * G) * kD + i) * scale_log2e;
   __syncthreads();
-  // Logits: thread t takes token t for every head.
-  for (int t = tid; t < n; t += kSegThreads) {
-    float acc[kMaxGroup];
+#pragma unroll 1
+  for (int h = 0; h < G; ++h) {
+    const v4f q0 = *reinterpret_cast<const v4f*>(&qs[h][8 * e]), q1 = *reinterpret_cast<const v4f*>(&qs[h][8 * e + 4]);
 #pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h) acc[h] = 0.f;
-    for (int j = 0; j < kD; ++j) {
-      const float kv = load_elem(seg_k, seg_dtype, (tok0 + t) * kD + j);
+    for (int i = 0; i < kSegIt; ++i) {
+      if (64 * i >= n) break;                          // (uniform)
+      float a = 0.f;
 #pragma unroll
-      for (int h = 0; h < kMaxGroup; ++h)
-        if (h < G) acc[h] = fmaf(qs[h][j], kv, acc[h]);
+      for (int k = 0; k < 4; ++k) a = fmaf(q0[k], kr[i][k], fmaf(q1[k], kr[i][4 + k], a));
+      a = row16_sum(a);
+      if (e == 0) z[h][64 * i + 4 * wave + tr] = a;
     }
+  }
+  __syncthreads();
+  // Maximum, weights 2^(z - m) and their sum: wave h takes head h.
+  if (wave < G) {
+    float zl[kSegMax / 64], m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int h = 0; h < kMaxGroup; ++h)
-      if (h < G) z[h][t] = acc[h];
-  }
-  __syncthreads();
-  // Maximum and sum per head (the log2-domain weights 2^(z - m)).
-  for (int h = 0; h < G; ++h) {
-    float m = -INFINITY;
-    for (int t = tid; t < n; t += kSegThreads) m = fmaxf(m, z[h][t]);
+    for (int i = 0; i < kSegMax / 64; ++i) {
+      zl[i] = lane + 64 * i < n ? z[wave][lane + 64 * i] : -INFINITY;
+      m = fmaxf(m, zl[i]);
+    }
     m = wave_max_dpp(m);
-    if (lane == 0) red[wave][h] = m;
-  }
-  __syncthreads();
-  if (tid < G) {
-    float m = red[0][tid];
-    for (int w = 1; w < kSegThreads / 64; ++w) m = fmaxf(m, red[w][tid]);
-    mh[tid] = m;
-  }
-  __syncthreads();
-  for (int h = 0; h < G; ++h) {
-    float l = 0.f;
-    for (int t = tid; t < n; t += kSegThreads) {
-      const float p = exp2f(z[h][t] - mh[h]);
-      z[h][t] = p;
+#pragma unroll
+    for (int i = 0; i < kSegMax / 64; ++i) {
+      const float p = lane + 64 * i < n ? exp2f(zl[i] - m) : 0.f;
+      z[wave][lane + 64 * i] = p;
       l += p;
     }
     l = wave_sum_dpp(l);
-    if (lane == 0) red[wave][h] = l;
+    if (lane == 0) {
+      out[wave].m = m;
+      out[wave].l = l;
+    }
   }
   __syncthreads();
-  if (tid < G) {
-    float l = 0.f;
-    for (int w = 0; w < kSegThreads / 64; ++w) l += red[w][tid];
-    lh[tid] = l;
-  }
-  // Value sums in the original domain: thread (half, j) over its half of the heads.
-  {
-    const int j = tid % kD, h0 = (tid / kD) * (kMaxGroup / 2);
-    float acc[kMaxGroup / 2];
+  // Value sums: wave (share, head) of Gp = G rounded up to a power of two heads; a lane group
+  // takes every fourth token of the share, four rows in flight.
+  const int lg = G > 1 ? 32 - __builtin_clz((unsigned)(G - 1)) : 0;
+  const int h = wave & ((1 << lg) - 1), step = 4 * (kSegWaves >> lg);
+  float acc[8] = {};
+  if (h < G) {
+    for (int t0 = 4 * (wave >> lg) + tr; t0 < n + tr; t0 += 4 * step) {   // (uniform trip count)
+      float vr[4][8], p[4];
 #pragma unroll
-    for (int i = 0; i < kMaxGroup / 2; ++i) acc[i] = 0.f;
-    for (int t = 0; t < n; ++t) {
-      const float vv = load_elem(seg_v, seg_dtype, (tok0 + t) * kD + j);
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * step;
+        load_row8(seg_v, seg_dtype, tok0 + min(t, n - 1), e, vec, vr[u]);
+        p[u] = t < n ? z[h][min(t, n - 1)] : 0.f;
+      }
 #pragma unroll
-      for (int i = 0; i < kMaxGroup / 2; ++i)
-        if (h0 + i < G) acc[i] = fmaf(z[h0 + i][t], vv, acc[i]);
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] = t0 + u * step < n ? fmaf(p[u], vr[u][k], acc[k]) : acc[k];
     }
 #pragma unroll
-    for (int i = 0; i < kMaxGroup / 2; ++i)
-      if (h0 + i < G) orw[h0 + i][j] = acc[i];
+    for (int k = 0; k < 8; ++k) acc[k] = xor32_sum(xor16_sum(acc[k]));
+    if (tr == 0) {
+      *reinterpret_cast<v4f*>(&ored[wave][8 * e]) = (v4f){acc[0], acc[1], acc[2], acc[3]};
+      *reinterpret_cast<v4f*>(&ored[wave][8 * e + 4]) = (v4f){acc[4], acc[5], acc[6], acc[7]};
+    }
   }
   __syncthreads();
-  // Into the transformed domain of the merge: o~_c = sum_j T_V[j][c] o_j.
-  const HeadParams* hv = head_params(params_v, kvh);
-  Partial* out = seg_out + (int64_t)row * G;
-  {
-    const int c = tid % kD, h0 = (tid / kD) * (kMaxGroup / 2);
-    float acc[kMaxGroup / 2];
-#pragma unroll
-    for (int i = 0; i < kMaxGroup / 2; ++i) acc[i] = 0.f;
-    for (int j = 0; j < kD; ++j) {
-      const float t = hv->T[j * kD + c];
-#pragma unroll
-      for (int i = 0; i < kMaxGroup / 2; ++i)
-        if (h0 + i < G) acc[i] = fmaf(t, orw[h0 + i][j], acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxGroup / 2; ++i)
-      if (h0 + i < G) out[h0 + i].o[c] = acc[i];
-  }
-  if (tid < G) {
-    out[tid].m = n > 0 ? mh[tid] : -INFINITY;
-    out[tid].l = n > 0 ? lh[tid] : 0.f;
+  for (int i = tid; i < G * kD; i += kSegThreads) {
+    const int hh = i / kD, j = i % kD;
+    float o = 0.f;
+    for (int w = hh; w < kSegWaves; w += 1 << lg) o += ored[w][j];
+    out[hh].o[j] = o;
   }
 }
 
-// The merging workgroup folds the segment's partial of its (sequence, KV head) into every
-// output element (written by segment_partial_kernel, which ran before this launch).
+// The merging workgroup folds the segment's partial of its (sequence, KV head) (written by
+// segment_partial_kernel, which ran before this launch): its weight enters the softmax of
+// every output element, its value sum is added after the inverse transform.
 struct SegHook {
-  const Partial* seg;                  // this row's G partials
+  const Partial* seg;                  // this row's partials
+  float* w;                            // LDS: the segment's final weight per head
   __device__ void prefetch() {}
   __device__ void during_loads() {}
   __device__ void encode() {}
   __device__ void publish() {}
-  __device__ void fold1(int h, int c, float& M, float& Ls, float& acc) const {
+  template <class V>
+  __device__ void weigh(int h, bool first, float& M, float& Ls, V& acc) const {
     const float ms = seg[h].m;
-    if (ms == -INFINITY) return;
-    const float mn = fmaxf(M, ms);
-    const float sa = exp2f(M - mn), sb = exp2f(ms - mn);
-    acc = acc * sa + seg[h].o[c] * sb;
-    Ls = Ls * sa + seg[h].l * sb;
-    M = mn;
+    float f = 0.f;
+    if (ms != -INFINITY) {
+      const float mn = fmaxf(M, ms);
+      const float sa = exp2f(M - mn), sb = exp2f(ms - mn);
+      acc = acc * sa;
+      Ls = Ls * sa + seg[h].l * sb;
+      M = mn;
+      f = sb / Ls;
+    }
+    if (first) w[h] = f;
+  }
+  __device__ void fold1(int h, int c, float& M, float& Ls, float& acc) const {
+    weigh(h, c == 0, M, Ls, acc);
   }
   __device__ void fold(int h, int c4, float& M, float& Ls, v4f& acc) const {
-    const float ms = seg[h].m;
-    if (ms == -INFINITY) return;
-    const float mn = fmaxf(M, ms);
-    const float sa = exp2f(M - mn), sb = exp2f(ms - mn);
-    acc = acc * sa + reinterpret_cast<const v4f*>(seg[h].o)[c4] * sb;
-    Ls = Ls * sa + seg[h].l * sb;
-    M = mn;
+    weigh(h, c4 == 0, M, Ls, acc);
+  }
+  __device__ float add1(int h, int j, float o) const {
+    return w[h] != 0.f ? fmaf(w[h], seg[h].o[j], o) : o;
+  }
+  __device__ v4f add4(int h, int j0, v4f o) const {
+    return w[h] != 0.f ? o + w[h] * *reinterpret_cast<const v4f*>(seg[h].o + j0) : o;
   }
   __device__ void finish() {}
 };
@@ -1090,6 +1138,8 @@ struct AppendHook {
     M = mn;
   }
 
+  __device__ float add1(int, int, float o) const { return o; }
+  __device__ v4f add4(int, int, v4f o) const { return o; }
   __device__ void fold1(int h, int c, float& M, float& Ls, float& acc) const {
     if (!on) return;
     const float ms = znew(h);
@@ -1290,7 +1340,8 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(
   }
   float* out_rows = out + ((int64_t)seq * n_q_heads + kvh * G) * kD;
   if (seg) {
-    SegHook sh{seg + kv_row * G};
+    __shared__ float seg_w[kMaxGroup];
+    SegHook sh{seg + kv_row * G, seg_w};
     merge_if_last<kThreads, true>(params_v, kvh, kv_row, G, n_splits, partials, counters,
                                   out_rows, dyn, sh);
   } else {
@@ -2290,7 +2341,7 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
     hook.sc = reinterpret_cast<AppendScratch*>(smem + a.off_es);
     merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, hook);
   } else if (a.seg) {
-    SegHook sh{a.seg + row * all_heads + NH * hgi};
+    SegHook sh{a.seg + row * all_heads + NH * hgi, mfin};
     merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, sh);
   } else {
     NoHook none;
@@ -2452,8 +2503,7 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
     if (seg_cap > kSegMax || x_k) return AATC_E_UNSUPPORTED;
     Partial* sp = reinterpret_cast<Partial*>(ws + wl.seg);
     hipLaunchKernelGGL(segment_partial_kernel, dim3((unsigned)(batch * n_kv_heads)),
-                       dim3(kSegThreads), 0, st, params_v, n_q_heads, n_kv_heads, q,
-                       (int)q_dtype, seg_k, seg_v, (int)seg_dtype, seg_len, seg_cap,
+                       dim3(kSegThreads), 0, st, n_q_heads, n_kv_heads, q, (int)q_dtype, seg_k, seg_v, (int)seg_dtype, seg_len, seg_cap,
                        softmax_scale * kLog2e, sp);
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     seg = sp;
