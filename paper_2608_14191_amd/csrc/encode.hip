@@ -135,10 +135,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 //     and codes are certified against that bound: alpha if the fp16 rounding of the largest
 //     |r| cannot change within it, each code if its fp32 quantizer input lies farther than
 //     the bound (plus the fp32 roundings of both evaluations) from a rounding boundary.
+// fp32 tokens are hardly ever exact in 22 bits: the bound then failed 73-89 % of key tokens
+// (spectrum i^-1.5 with outlier coordinates, 2.75-4 bits), all redone by the fix-up.  They
+// take a fourth limb, max |x_j| 2^S in [2^29, 2^30): twelve products, and a bound 2^8 smaller
+// that fails under 0.3 % (3001 tokens x 8 heads, K and V at 4 bits: 5040 us before).  Their H
+// can pass 2^53: it is formed in fp64 within 2^7, which the bound includes.
 // Tokens that fail, and tokens whose k is out of range, get the scale mark kRedo;
 // encode_fixup_kernel, launched next on the stream, encodes them exactly.
 //
-// A workgroup of twelve waves shares the limb tables of one KV head's transform (48 KiB of
+// A workgroup of twelve waves (eight for fp32) shares the limb tables of one KV head's transform (48 KiB of
 // LDS, built once).  After that each wave works alone, with no workgroup barrier, on
 // 32-token units (half a 64-token tile): two groups of 16 tokens against all 128 channels,
 // codes OR-ed into the wave's own LDS record rows, then the unit's records, or its half of
@@ -153,8 +158,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // channel tile ct and k half kc sit at ((2 ct + kc) 64 + l) 16, so every operand read is one
 // contiguous 1 KiB per wave (no bank conflicts).
 constexpr int kTbBytes = 8 * 2 * 64 * 16;        // one limb of the 128 x 128 transform
-constexpr int kMW = 12;                           // waves per matrix-core workgroup
-constexpr int kMThreads = 64 * kMW;
+// Waves per matrix-core workgroup: three per SIMD, or two for fp32 (the fourth limb and the
+// wider elements in flight need more than 168 registers).
+template <bool BF16> constexpr int kMW = BF16 ? 12 : 8;
 constexpr int kUnit = 32;                         // tokens per wave work unit
 constexpr int kNarrowWords = kD * 8 / 32;         // largest record of codes up to 8 bits
 constexpr int kStage = kNarrowWords + 1;          // LDS record row stride (one word of padding)
@@ -298,7 +304,7 @@ struct XScale {
 // y = X + kXBias for elements 4 q .. 4 q + 3 of k half kc, X = x 2^S rounded to an integer
 // (x 2^S + kXBias rounded to fp32, then toward zero: any rounding would do, since E below is
 // taken against these very integers).  Elements with x 2^S an integer give exactly that
-// integer.  -22 <= S <= 78.
+// integer.  -22 <= S <= 78.  (bf16 tokens.)
 template <bool BF16>
 __device__ inline void chunk_y(const Chunk<BF16>& c, int kc, int q, const XScale& sc,
                                uint32_t (&y)[4]) {
@@ -306,16 +312,15 @@ __device__ inline void chunk_y(const Chunk<BF16>& c, int kc, int q, const XScale
   for (int e = 0; e < 4; ++e) y[e] = (uint32_t)(int)fmaf(c.elem(kc, 4 * q + e), sc.f, (float)kXBias);
 }
 
-// The int8 limbs of X as B operands (byte e of word q: element 4 q + e): X0 = byte 0 of y
-// - 128, X1 = byte 1 of y - 128, X2 = byte 2 of y (signed), for y = X + kXBias.
-template <bool BF16>
-__device__ inline void chunk_limbs(const Chunk<BF16>& c, const XScale& sc, ev4i (&A)[3][2]) {
+// The int8 limbs of X as B operands (byte e of word q: element 4 q + e).  bf16: X0 = byte 0 of
+// y - 128, X1 = byte 1 of y - 128, X2 = byte 2 of y (signed), for y = X + kXBias.
+__device__ inline void chunk_limbs(const Chunk<true>& c, const XScale& sc, ev4i (&A)[3][2]) {
 #pragma unroll
   for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t y[4];
-      chunk_y<BF16>(c, kc, q, sc, y);
+      chunk_y<true>(c, kc, q, sc, y);
       // v_perm_b32(a, b, sel): byte k of the result is byte sel_k of {a: 4..7, b: 0..3}
       const uint32_t p01 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);
       const uint32_t p23 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
@@ -327,22 +332,49 @@ __device__ inline void chunk_limbs(const Chunk<BF16>& c, const XScale& sc, ev4i 
 }
 
 // This lane's part of E = sum_j |x_j 2^S - X_j| for the X_j of chunk_limbs (each term
-// exact: x_j 2^S - X_j has at most 8 (bf16) or 24 (fp32) significant bits; a product
-// below the fp32 range rounds by under 2^-150, which the caller's slack covers).
-template <bool BF16>
-__device__ inline float chunk_err(const Chunk<BF16>& c, const XScale& sc) {
+// exact: x_j 2^S - X_j has at most 8 significant bits; a product below the fp32 range rounds
+// by under 2^-150, which the caller's slack covers).
+__device__ inline float chunk_err(const Chunk<true>& c, const XScale& sc) {
   float E = 0.f;
 #pragma unroll
   for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t y[4];
-      chunk_y<BF16>(c, kc, q, sc, y);
+      chunk_y<true>(c, kc, q, sc, y);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         E += fabsf(fmaf(c.elem(kc, 4 * q + e), sc.f, (float)(kXBias - (int)y[e])));
     }
   return E;
+}
+
+// fp32: four limbs of X = x 2^S rounded to the nearest integer, |X| <= 2^30: bytes 0, 1, 2 of
+// y - 128 and byte 3 of y (signed), for y = X + 0x808080; and this lane's part of E (each
+// term exact: X has at most 24 significant bits).
+__device__ inline void chunk_limbs(const Chunk<false>& c, const XScale& sc, ev4i (&A)[4][2],
+                                   float& E) {
+  E = 0.f;
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = c.elem(kc, 4 * q + e), r = rintf(x * sc.f);
+        E += fabsf(fmaf(x, sc.f, -r));
+        y[e] = (uint32_t)(int)r + 0x808080u;
+      }
+      const uint32_t l01 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);
+      const uint32_t l23 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
+      const uint32_t h01 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);
+      const uint32_t h23 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+      A[0][kc][q] = (int)(__builtin_amdgcn_perm(l23, l01, 0x05040100u) ^ 0x80808080u);
+      A[1][kc][q] = (int)(__builtin_amdgcn_perm(l23, l01, 0x07060302u) ^ 0x80808080u);
+      A[2][kc][q] = (int)(__builtin_amdgcn_perm(h23, h01, 0x05040100u) ^ 0x80808080u);
+      A[3][kc][q] = (int)__builtin_amdgcn_perm(h23, h01, 0x07060302u);
+    }
 }
 
 // A value the compiler cannot see through (keeps work that depends on it inside its branch).
@@ -370,12 +402,13 @@ __device__ inline void limb_bytes4(const int (&v)[4], uint32_t (&out)[3]) {
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
+__global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int64_t n_tok,
     int64_t x_stride, int layout, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha,
     int64_t cap, int64_t pos) {
   __shared__ __align__(16) int8_t tb[3][kTbBytes];         // [limb][ct][kc][lane][16]
-  __shared__ uint32_t stage[kMW][kUnit][kStage];           // each wave's record rows
+  constexpr int kMThreads = 64 * kMW<BF16>;
+  __shared__ uint32_t stage[kMW<BF16>][kUnit][kStage];     // each wave's record rows
   // Channel tables, read by the lanes that hold channels 16 ct + 4 kg + i.
   __shared__ __align__(16) float tab_is[kD];               // 1 / s_c
   __shared__ __align__(16) float tab_p2[kD];               // 2^(b_c - 1) (1 for b_c = 0)
@@ -386,6 +419,8 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
   __shared__ uint32_t tab_msb[kD / 4];                     // sum of 1 << (sh + b - 1)
   __shared__ uint16_t tab_o[kD];                           // first record bits
 
+  constexpr int XL = BF16 ? 3 : 4;                  // limbs of X
+  constexpr int NS = XL + 2;                        // limb-product sums
   const int head = blockIdx.y;
   const HeadParams* hp = head_params(params, head);
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
@@ -451,11 +486,11 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
     tab_bias[tid] = bias;
     tab_msb[tid] = msb;
   }
-  for (int i = tid; i < kMW * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
+  for (int i = tid; i < kMW<BF16> * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
   __syncthreads();                                 // (the last workgroup barrier)
 
-  const int64_t ustep = (int64_t)gridDim.x * kMW;
-  int64_t u = (int64_t)blockIdx.x * kMW + wave;
+  const int64_t ustep = (int64_t)gridDim.x * kMW<BF16>;
+  int64_t u = (int64_t)blockIdx.x * kMW<BF16> + wave;
   if (u >= n_units) return;
   uint32_t (*rows)[kStage] = stage[wave];
   // Where this lane's eight fields go in a record row: byte offset of the first word (bits
@@ -494,17 +529,25 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
       const bool valid = tu >= lo && tu < hi;
       // (1) The token's fixed-point shift and exactness flag.
       bool maybe = false;
-      const int S = token_shift(chunk_stats<BF16>(cur, maybe));
+      const float xmax = chunk_stats<BF16>(cur, maybe);
+      const int S = token_shift(xmax) + 8 * (XL - 3);
       const int k = S + kTFrac;
       const bool k_ok = k >= 0 && k <= 100;
       const XScale sc(min(max(S, -kTFrac), 100 - kTFrac));
       const bool cert = __builtin_amdgcn_ballot_w64(maybe) != 0ull;
       // (2) The limbs of X as B operands, and in waves with a flagged token the fixed-point
       //     error sum E of each token (over its four lanes).
-      ev4i A[3][2];
-      chunk_limbs<BF16>(cur, sc, A);
+      ev4i A[XL][2];
       float Et = 0.f;
-      if (cert) Et = opaque(enc_cross_row_sum(chunk_err<BF16>(cur, sc)));
+      if constexpr (BF16) {
+        chunk_limbs(cur, sc, A);
+        if (cert) Et = opaque(enc_cross_row_sum(chunk_err(cur, sc)));
+      } else {
+        float E;
+        chunk_limbs(cur, sc, A, E);
+        // (2^-14: the roundings of H in fp64, in units of 2^22)
+        Et = xmax > 0.f ? enc_cross_row_sum(E) + 0x1p-14f : 0.f;
+      }
       // (3) Channel tile by channel tile: the five limb-product sums (18 products), H exactly,
       //     then u_c = fl32(fl32(H) / s_c) for channels 16 ct + 4 kg + i of this token.  The
       //     operands of the next k half are read while the products of this one run, and
@@ -519,32 +562,43 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
 #pragma unroll
         for (int l = 0; l < 3; ++l) bq[l] = *reinterpret_cast<const ev4i*>(&tb[l][o]);
       };
-      auto products = [&](const ev4i (&bq)[3], int kc, ev4i (&sa)[5]) {
-        sa[4] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[2], A[2][kc], sa[4], 0, 0, 0);
-        sa[3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[2], A[1][kc], sa[3], 0, 0, 0);
-        sa[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[2], A[0][kc], sa[2], 0, 0, 0);
-        sa[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[1], A[0][kc], sa[1], 0, 0, 0);
-        sa[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[0], A[0][kc], sa[0], 0, 0, 0);
-        sa[3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[1], A[2][kc], sa[3], 0, 0, 0);
-        sa[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[1], A[1][kc], sa[2], 0, 0, 0);
-        sa[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[0], A[1][kc], sa[1], 0, 0, 0);
-        sa[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[0], A[2][kc], sa[2], 0, 0, 0);
+      auto products = [&](const ev4i (&bq)[3], int kc, ev4i (&sa)[NS]) {
+        // (a product's sum is never the previous product's)
+        auto mac = [&](int t, int xa) {
+          sa[xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[t], A[xa][kc], sa[xa + t], 0, 0, 0);
+        };
+#pragma unroll
+        for (int xa = XL - 1; xa >= 0; --xa) mac(2, xa);
+        mac(1, 0);
+        mac(0, 0);
+#pragma unroll
+        for (int xa = XL - 1; xa >= 1; --xa) mac(1, xa);
+#pragma unroll
+        for (int xa = 1; xa < XL; ++xa) mac(0, xa);
       };
-      auto to_u = [&](const ev4i (&sa)[5], int ct) {
+      auto to_u = [&](const ev4i (&sa)[NS], int ct) {
         const float4 is4 = *reinterpret_cast<const float4*>(&tab_is[16 * ct + 4 * kg]);
         const float isv[4] = {is4.x, is4.y, is4.z, is4.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          // H = 2^24 (2^8 S4 + S3) + 2^16 S2 + (2^8 S1 + S0): exact in fp64 (< 2^51)
-          const int hi8 = sa[4][i] * 256 + sa[3][i];
-          const int lo8 = sa[1][i] * 256 + sa[0][i];
-          const double H = fma(fma((double)hi8, 256.0, (double)sa[2][i]), 65536.0, (double)lo8);
+          double H;
+          if constexpr (BF16) {
+            // H = 2^24 (2^8 S4 + S3) + 2^16 S2 + (2^8 S1 + S0): exact in fp64 (< 2^51)
+            const int hi8 = sa[4][i] * 256 + sa[3][i];
+            const int lo8 = sa[1][i] * 256 + sa[0][i];
+            H = fma(fma((double)hi8, 256.0, (double)sa[2][i]), 65536.0, (double)lo8);
+          } else {
+            // the sums in pairs (2^8 S_(k+1) + S_k below 2^31)
+            const int h5 = sa[5][i] * 256 + sa[4][i], h3 = sa[3][i] * 256 + sa[2][i];
+            const int h1 = sa[1][i] * 256 + sa[0][i];
+            H = fma(fma((double)h5, 65536.0, (double)h3), 65536.0, (double)h1);
+          }
           uv[ct][i] = (float)H * isv[i];
           am = fmaxf(am, fabsf(uv[ct][i]));          // (u = 0 on dropped channels)
         }
       };
       {
-        ev4i bq[2][3], sa[2][5];
+        ev4i bq[2][3], sa[2][NS];
         load_b(0, bq[0]);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
@@ -553,7 +607,7 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
           __builtin_amdgcn_sched_barrier(0);            // (the reads stay ahead of the products)
           if (kc == 0) {
 #pragma unroll
-            for (int kk = 0; kk < 5; ++kk) sa[ct & 1][kk] = (ev4i){0, 0, 0, 0};
+            for (int kk = 0; kk < NS; ++kk) sa[ct & 1][kk] = (ev4i){0, 0, 0, 0};
           }
           products(bq[q & 1], kc, sa[ct & 1]);
           if (kc == 1 && ct > 0) to_u(sa[(ct - 1) & 1], ct - 1);
@@ -630,7 +684,7 @@ __global__ __launch_bounds__(kMThreads) void encode_mfma_kernel(
               // xq + 1/2; the distance to the nearest boundary from the fraction
               const float mg = fmaf(kf, ea, fmaf(0x1p-21f, fabsf(xq), 0x1p-22f));
               const float d = fabsf(__builtin_amdgcn_fractf(xq) - 0.5f);
-              bad |= MR ? (d >= 0.5f - mg) : (d <= mg);
+              bad |= MR ? (kf > 0.f && d >= 0.5f - mg) : (d <= mg);   // (dropped: kf = 0)
             }
           }
           field[ct] = f ^ tab_msb[c0 >> 2];
@@ -812,7 +866,7 @@ __global__ __launch_bounds__(64) void encode_token_kernel(
 // transform into LDS would move as many bytes as the reads it saves).
 constexpr int kFixThreads = 256;
 constexpr int kFixWaves = kFixThreads / 64;
-constexpr int kFixTokens = 2048;
+template <int kFixTokens>
 __global__ __launch_bounds__(kFixThreads) void encode_fixup_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int dtype, int64_t n_tok,
     int64_t x_stride, int layout, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha,
@@ -829,14 +883,14 @@ __global__ __launch_bounds__(kFixThreads) void encode_fixup_kernel(
     // (all marks of a thread read before any is tested, past the end clamped to the last
     // token: one round trip)
     const uint16_t* am = alpha + (int64_t)head * cap + pos;
-    uint16_t mv[kFixTokens / kFixThreads];
+    constexpr int M = (kFixTokens + kFixThreads - 1) / kFixThreads;
+    uint16_t mv[M];
 #pragma unroll
-    for (int m = 0; m < kFixTokens / kFixThreads; ++m)
-      mv[m] = am[min<int64_t>(base + tid + kFixThreads * m, n_tok - 1)];
+    for (int m = 0; m < M; ++m) mv[m] = am[min<int64_t>(base + tid + kFixThreads * m, n_tok - 1)];
 #pragma unroll
-    for (int m = 0; m < kFixTokens / kFixThreads; ++m) {
+    for (int m = 0; m < M; ++m) {
       const int i = tid + kFixThreads * m;
-      if (mv[m] == kRedo && base + i < n_tok) list[atomicAdd(&n_list, 1)] = (uint16_t)i;
+      if (mv[m] == kRedo && i < kFixTokens && base + i < n_tok) list[atomicAdd(&n_list, 1)] = (uint16_t)i;
     }
   }
   __syncthreads();
@@ -875,24 +929,28 @@ aatc_status launch_encode(const void* params, int n_heads, const void* x, aatc_d
   const bool aligned = (reinterpret_cast<uintptr_t>(x) % 16 == 0) &&
                        ((size_t)x_tok_stride * esize) % 16 == 0;
   if (aligned) {
-    // About one workgroup of twelve waves per compute unit over all KV heads.
-    const int64_t per_head = std::min<int64_t>(std::max(1, 256 / n_heads),
-                                               (2 * n_tiles + kMW - 1) / kMW);
-    dim3 grid((unsigned)per_head, (unsigned)n_heads);
-    if (x_dtype == AATC_BF16)
-      hipLaunchKernelGGL(encode_mfma_kernel<true>, grid, dim3(kMThreads), 0,
+    // About one workgroup per compute unit over all KV heads.
+    auto bulk = [&](auto kernel, int waves) {
+      const int64_t per_head = std::min<int64_t>(std::max(1, 256 / n_heads),
+                                                 (2 * n_tiles + waves - 1) / waves);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)per_head, (unsigned)n_heads), dim3(64 * waves), 0,
                          (hipStream_t)stream, params, x, n_tok, x_tok_stride, (int)layout,
                          static_cast<uint8_t*>(codes), alpha, cap, pos);
-    else
-      hipLaunchKernelGGL(encode_mfma_kernel<false>, grid, dim3(kMThreads), 0,
-                         (hipStream_t)stream, params, x, n_tok, x_tok_stride, (int)layout,
-                         static_cast<uint8_t*>(codes), alpha, cap, pos);
+    };
+    if (x_dtype == AATC_BF16) bulk(encode_mfma_kernel<true>, kMW<true>);
+    else bulk(encode_mfma_kernel<false>, kMW<false>);
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     // The tokens whose certificate failed, exactly (stream order: after the kernel above).
-    const dim3 fgrid((unsigned)((n_tok + kFixTokens - 1) / kFixTokens), (unsigned)n_heads);
-    hipLaunchKernelGGL(encode_fixup_kernel, fgrid, dim3(kFixThreads), 0, (hipStream_t)stream, params, x,
-                       (int)x_dtype, n_tok, x_tok_stride, (int)layout,
-                       static_cast<uint8_t*>(codes), alpha, cap, pos);
+    // 2048 tokens per workgroup when that gives every compute unit one (a scan of mostly
+    // unmarked tokens), else 64, so that a short call's marked tokens spread over the chip.
+    auto fixup = [&](auto kernel, int tokens) {
+      const dim3 fgrid((unsigned)((n_tok + tokens - 1) / tokens), (unsigned)n_heads);
+      hipLaunchKernelGGL(kernel, fgrid, dim3(kFixThreads), 0, (hipStream_t)stream, params, x,
+                         (int)x_dtype, n_tok, x_tok_stride, (int)layout,
+                         static_cast<uint8_t*>(codes), alpha, cap, pos);
+    };
+    if ((n_tok / 2048) * n_heads >= 256) fixup(encode_fixup_kernel<2048>, 2048);
+    else fixup(encode_fixup_kernel<64>, 64);
     return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
   }
   dim3 grid((unsigned)n_tiles, (unsigned)n_heads);
