@@ -391,63 +391,85 @@ struct TvBlock {
   }
 };
 
-// o = T_V o~ on the matrix cores in bf16 pairs: with T = Th + Tl and o~ = oh + ol (each
-// term bf16, the second the first's remainder), T o~ = Th oh + Th ol + Tl oh up to
-// |Tl ol| + rounding, about 2^-16 relative; the three products accumulate in fp32
-// (v_mfma_f32_16x16x32_bf16).  Wave w computes output rows 16 w' .. + 15 (w' = w + NTHR /
-// 64 p over the passes p) for up to 16 vectors: A = its 16-row block of T (the
-// parameter block's operand-ordered copy), B column n = vector n.
+// o = T_V o~ on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32 sums), T and o~ as sums of bf16
+// terms, each the remainder of those before: pairs (three products, 2^-16 relative), T's from
+// the parameter block's operand-ordered copy; or triples (exact, the six products T_a o_b with
+// a + b <= 2, the rest below 2^-24), T split here, for the shapes that had fp32 sums before
+// (6 bits, 6001 tokens: 5.6e-6 of the output in pairs against 4.6e-6; triples cost 0.8 us, their
+// row-wise loads and the split).  Wave w < 8 computes output rows 16 w .. + 15 for up to 16
+// vectors: A = its 16-row block of T, lane 16 g + n row n at columns 32 kk + 8 g .. + 7, B
+// column n = vector n.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// bf16 of x (round to nearest even) and of the remainder x - bf16(x).
-__device__ inline void bf16_pair(float x, __bf16& hi, __bf16& lo) {
-  hi = (__bf16)x;
-  lo = (__bf16)(x - (float)hi);
-}
-
-template <int NTHR>
 struct TvMfma {
-  static constexpr int NPASS = 512 / NTHR;
-  static_assert(NPASS * NTHR == 512, "256 or 512 threads");
-  bf16x8 a[NPASS][4][2];                  // [pass][k-step][Th, Tl]
-  __device__ void load(const HeadParams* hv) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) load_step(hv, kk);
-  }
-  __device__ void load_step(const HeadParams* hv, int kk) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bf16x8* tp = reinterpret_cast<const bf16x8*>(hv->Tm);
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-        a[p][kk][t] = tp[(((wave + (NTHR / 64) * p) * 4 + kk) * 2 + t) * 64 + lane];
-  }
-  // B operands in LDS: ob[t] (t = 0: oh, 1: ol) holds [k-step][lane] 16-byte units, lane
-  // 16 g + n: vector n at elements 32 kk + 8 g .. + 7 (put() writes one element).
-  __device__ static void put(__bf16* ob_hi, __bf16* ob_lo, int n, int c, float x) {
-    const int i = ((c >> 5) * 64 + 16 * ((c >> 3) & 3) + n) * 8 + (c & 7);
-    bf16_pair(x, ob_hi[i], ob_lo[i]);
-  }
-  // Calls sink(n, j0, o[j0 .. j0 + 3] of vector n) for n < G (the caller synchronizes
-  // after the puts).
-  template <class Sink>
-  __device__ void apply(const __bf16* ob_hi, const __bf16* ob_lo, int G, Sink sink) const {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15;
-    const bf16x8* bh = reinterpret_cast<const bf16x8*>(ob_hi);
-    const bf16x8* bl = reinterpret_cast<const bf16x8*>(ob_lo);
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0;
+  bf16x8 a[4][3];                         // [k-step][term]
+  v4f t[4][2];                            // triples: the lane's columns of T until split()
+  __device__ void load(const HeadParams* hv, bool triple) {
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 7;
+    if (triple) {
+      const v4f* tp = reinterpret_cast<const v4f*>(hv->T + (16 * wave + (lane & 15)) * kD + 8 * (lane >> 4));
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8 h8 = bh[kk * 64 + lane], l8 = bl[kk * 64 + lane];
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p][kk][0], h8, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p][kk][0], l8, acc1, 0, 0, 0);
-        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p][kk][1], h8, acc2, 0, 0, 0);
+        t[kk][0] = tp[8 * kk];
+        t[kk][1] = tp[8 * kk + 1];
       }
-      if (n < G) sink(n, 16 * (wave + (NTHR / 64) * p) + 4 * (lane >> 4), acc0 + acc1 + acc2);
+    } else {
+      const bf16x8* tp = reinterpret_cast<const bf16x8*>(hv->Tm);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) a[kk][u] = tp[((wave * 4 + kk) * 2 + u) * 64 + lane];
     }
+  }
+  __device__ void split() {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x = t[kk][e >> 2][e & 3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          a[kk][u][e] = (__bf16)x;
+          x -= (float)a[kk][u][e];
+        }
+      }
+  }
+  static constexpr int kOperand = 4 * 64 * 8;   // elements of one term's B operands in LDS
+  // B operands in LDS: term t at ob + t kOperand holds [k-step][lane] 16-byte units, lane
+  // 16 g + n: vector n at elements 32 kk + 8 g .. + 7 (put() writes one element).
+  __device__ static void put(__bf16* ob, int n, int c, float x, bool triple) {
+    const int i = ((c >> 5) * 64 + 16 * ((c >> 3) & 3) + n) * 8 + (c & 7);
+    const __bf16 b0 = (__bf16)x;
+    x -= (float)b0;
+    const __bf16 b1 = (__bf16)x;
+    ob[i] = b0;
+    ob[kOperand + i] = b1;
+    if (triple) ob[2 * kOperand + i] = (__bf16)(x - (float)b1);
+  }
+  // Calls sink(n, j0, o[j0 .. j0 + 3] of vector n) for n < G (triples: after split(); the
+  // caller synchronizes after the puts); waves 0 .. 7.
+  template <class Sink>
+  __device__ void apply(const __bf16* ob, int G, bool triple, Sink sink) const {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15;
+    const bf16x8* b8 = reinterpret_cast<const bf16x8*>(ob);
+    v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const bf16x8 b0 = b8[kk * 64 + lane], b1 = b8[(4 + kk) * 64 + lane];
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][0], b0, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][0], b1, acc1, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][1], b0, acc2, 0, 0, 0);
+    }
+    if (triple) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const bf16x8 b0 = b8[kk * 64 + lane], b1 = b8[(4 + kk) * 64 + lane], b2 = b8[(8 + kk) * 64 + lane];
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][0], b2, acc1, 0, 0, 0);
+        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][1], b1, acc2, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][2], b0, acc1, 0, 0, 0);
+      }
+    }
+    if (n < G) sink(n, 16 * wave + 4 * (lane >> 4), acc0 + acc1 + acc2);
   }
 };
 
@@ -594,7 +616,7 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
 // (the first barrier also publishes it).  The NG group sums of a unit meet in LDS; then
 // each output element (head h, channel c) takes its one more hook term and goes into the
 // B operands of o = T_V o~.
-// LDS: T_V B operands (8 KiB) | weights [2][NH][SB] | rescales [2][NH] | (M, L, bad) [NH]
+// LDS: T_V B operands (12 KiB) | weights [2][NH][SB] | rescales [2][NH] | (M, L, bad) [NH]
 // | group sums [NG][NU] (16 B each).  Every run has loaded tv during its last value phase, so
 // the merging one starts with T_V in registers.
 template <int NTHR, int NH>
@@ -608,7 +630,7 @@ struct WideMerge {
   static constexpr int NHW = (NH + NTW - 1) / NTW;    // heads per table wave
   static constexpr int NP = (NH * kD + NTHR - 1) / NTHR;   // output elements per thread
   static_assert(NG >= 1 && NG * NU == NTHR && SB <= 64 && NTW >= 1, "thread mapping");
-  static constexpr int kWt = 2 * 4 * 64 * 8 / 2;     // float offsets of the regions
+  static constexpr int kWt = 3 * TvMfma::kOperand / 2;   // float offsets of the regions
   static constexpr int kSa = kWt + 2 * NH * SB;
   static constexpr int kFin = kSa + 2 * NH;
   static constexpr int kRed = (kFin + 4 * NH + 3) / 4 * 4;
@@ -621,7 +643,7 @@ constexpr size_t wide_merge_lds_bytes() { return WideMerge<NTHR, NH>::kFloats * 
 template <int NTHR, int NH, class Hook>
 __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Partial* parts,
                                                    unsigned* counter, float* out_rows, float* lds,
-                                                   const TvMfma<NTHR>& tv, Hook& hook) {
+                                                   TvMfma& tv, bool triple, Hook& hook) {
   using WM = WideMerge<NTHR, NH>;
   constexpr int SU = WM::SU, SB = WM::SB, NU = WM::NU, NTW = WM::NTW, NHW = WM::NHW;
   __shared__ unsigned last_s;
@@ -638,8 +660,7 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
   if (!last_s) return;
   hook.prefetch();
   __builtin_amdgcn_sched_barrier(0);
-  __bf16* ob_hi = reinterpret_cast<__bf16*>(lds);
-  __bf16* ob_lo = ob_hi + 4 * 64 * 8;
+  __bf16* ob = reinterpret_cast<__bf16*>(lds);
   float* wt = lds + WM::kWt;
   float* sat = lds + WM::kSa;
   v4f* fin = reinterpret_cast<v4f*>(lds + WM::kFin);
@@ -723,7 +744,10 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
     acc = a0 + a1;
   };
   issue(0);
-  hook.encode();                          // waves 0 and 1, while the loads are in flight
+  // While the loads are in flight: the hook's encode in waves 0 and 1, the split of T_V in the
+  // rest (theirs after the sums).
+  if (triple && wave >= 2) tv.split();
+  hook.encode();
   for (int s0 = 0, b = 0;; ++b) {
     tables(s0, b);
     __syncthreads();                      // the batch's weights (first: the hook's encode)
@@ -732,6 +756,7 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
     if (s0 >= n_splits) break;
     issue(s0);
   }
+  if (triple && wave < 2) tv.split();
   if (table && lane == 0) {
 #pragma unroll
     for (int i = 0; i < NHW; ++i) {
@@ -752,12 +777,13 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
       const v4f f = fin[hh];
       float M = f[0], Ls = f[1];
       hook.fold1(hh, c, M, Ls, a);
-      TvMfma<NTHR>::put(ob_hi, ob_lo, hh, c, f[2] != 0.f ? NAN : (Ls > 0.f ? a / Ls : 0.f));
+      TvMfma::put(ob, hh, c, f[2] != 0.f ? NAN : (Ls > 0.f ? a / Ls : 0.f),
+                  triple);
     }
   }
   __syncthreads();
   // o = T_V o~ (the partials are in the transformed domain).
-  tv.apply(ob_hi, ob_lo, G, [&](int hh, int j0, v4f o) {
+  tv.apply(ob, G, triple, [&](int hh, int j0, v4f o) {
     *reinterpret_cast<v4f*>(out_rows + (int64_t)hh * kD + j0) = hook.add4(hh, j0, o);
   });
   hook.finish();
@@ -2231,8 +2257,9 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
 
   // T_V's matrix-core operands (32 VGPRs): every run loads them, and the one that merges has
   // them at hand.
-  TvMfma<NTHR> tv;
-  tv.load(hv);
+  TvMfma tv;
+  const bool triple = NP > 4 || (!APPEND && hg > 1);
+  tv.load(hv, triple);
   // O'(v) of both halves to LDS (over the consumed key records), the sums per wave.
   float* ob = reinterpret_cast<float*>(smem + a.off_ob);   // [halves][NH][ob_stride]
   float* obh = ob + hf * NH * a.ob_stride;
@@ -2339,13 +2366,13 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
     }
     hook.qc = qcl;
     hook.sc = reinterpret_cast<AppendScratch*>(smem + a.off_es);
-    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, hook);
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, triple, hook);
   } else if (a.seg) {
     SegHook sh{a.seg + row * all_heads + NH * hgi, mfin};
-    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, sh);
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, triple, sh);
   } else {
     NoHook none;
-    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, none);
+    merge_if_last_wide<NTHR, NH>(G, ns, parts, counter, out_rows, merge_scratch, tv, triple, none);
   }
 }
 
