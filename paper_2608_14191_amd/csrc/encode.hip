@@ -93,7 +93,7 @@ __device__ void exact_tile(const HeadParams* hp, const void* __restrict__ x, int
                        ((t - pos) * x_stride + (int64_t)head * kD) * (dtype == AATC_BF16 ? 2 : 4);
     float xl[2], r[2];
     load_token_pair(xrow, dtype, xl);
-    exact_r_wave<true>(hp, xl, xrow, dtype, r);
+    exact_r_wave(hp, xl, r);
     const __half a16 = wave_quantize_into(hp, r, rec[t - tile_base]);
     if (lane == 0) alpha[(int64_t)head * cap + t] = __half_as_ushort(a16);
   }
@@ -757,9 +757,8 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
 // entries for j + 16 .. j + 31 in flight while those for j .. j + 15 are summed: four round
 // trips to the parameter block in sequence instead of eight, for more registers.  For the
 // kernels that encode a token or a few per wave, where that latency is the time.
-template <bool LEAN = false>
 __device__ inline void exact_r_wave_pipelined(const HeadParams* hp, const float (&xl)[2],
-                                              const void* xrow, int dtype, float (&r)[2]) {
+                                              float (&r)[2]) {
   const int lane = threadIdx.x & 63;
   double s[2] = {0.0, 0.0}, a[2] = {0.0, 0.0};
   const int4* tc[2] = {reinterpret_cast<const int4*>(hp->Tqt + lane * kD),
@@ -795,7 +794,7 @@ __device__ inline void exact_r_wave_pipelined(const HeadParams* hp, const float 
     if (jb + 32 < kD) load(jb + 32, ta);
     sum(jb + 16, tb);
   }
-  exact_r_finish<LEAN>(hp, s, a, token_lsb(xl), xl, xrow, dtype, r);
+  exact_r_finish(hp, s, a, token_lsb(xl), xl, r);
 }
 
 // Codes and scale of one token from r (lane l: channels l and l + 64, one wave) into the
@@ -855,7 +854,7 @@ __global__ __launch_bounds__(64) void encode_token_kernel(
   const HeadParams* hp = head_params(params, head);
   float xl[2], r[2];
   load_token_pair(xrow, dtype, xl);
-  exact_r_wave_pipelined(hp, xl, xrow, dtype, r);
+  exact_r_wave_pipelined(hp, xl, r);
   store_token_wave(hp, r, layout, codes, alpha, cap, t, head, rec);
 }
 
@@ -905,7 +904,7 @@ __global__ __launch_bounds__(kFixThreads) void encode_fixup_kernel(
                        ((t - pos) * x_stride + (int64_t)head * kD) * esize;
     float xl[2], r[2];
     load_token_pair(xrow, dtype, xl);
-    exact_r_wave_pipelined<true>(hp, xl, xrow, dtype, r);
+    exact_r_wave_pipelined(hp, xl, r);
     store_token_wave(hp, r, layout, codes, alpha, cap, t, head, rec[wave]);
   }
 }

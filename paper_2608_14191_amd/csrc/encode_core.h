@@ -78,26 +78,36 @@ __device__ inline float wave_max64(float v) {
   return v;
 }
 
-// The exact fallback for one channel: h_c from the token (element j held by lane j % 64
-// of the wave, in xl[j / 64]) and column c of the integer transform, read 16 entries per
-// round trip.
-__device__ inline float exact_h_channel(const float (&xl)[2], const int32_t* tcol) {
-  // (j is uniform; the register is chosen by j, not per lane: the caller may run this with
-  // some lanes inactive, and readlane reads the chosen register of any lane)
-  return exact_dot_q22_batched(
-      [&](int j) {
-        const int a = __builtin_amdgcn_readlane(__float_as_int(xl[0]), j & 63);
-        const int b = __builtin_amdgcn_readlane(__float_as_int(xl[1]), j & 63);
-        return __int_as_float(j < 64 ? a : b);
-      },
-      reinterpret_cast<const int4*>(tcol), kD);
-}
-
-// The same with the token's elements and the column read one entry at a time from memory:
-// fewer registers (for kernels that call it with much else live), one round trip per entry.
-__device__ inline float exact_h_channel_lean(const void* xrow, int dtype, const int32_t* tcol) {
-  return exact_dot_q22([&](int j) { return load_elem(xrow, dtype, j); },
-                       [&](int j) { return tcol[j]; }, kD);
+// The exact fallback for one channel by a whole wave (every lane active): lane l holds
+// elements l + 64 i of the token, tcol points at the channel's column of the integer
+// transform.  Every lane adds its products to an exact accumulator of its own; the words are
+// summed over the wave (integers: |w| < 2^39 for up to 512 products) and rounded once.  (One
+// lane walking the column took a round trip per entry: 70 us for 128.)
+template <int N>
+__device__ inline float exact_dot_wave(const float (&xl)[N], const int32_t* tcol) {
+  const int lane = threadIdx.x & 63;
+  int32_t t[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = tcol[lane + 64 * i];
+  int64_t w[kAccWords];
+#pragma unroll
+  for (int k = 0; k < kAccWords; ++k) w[k] = 0;
+#pragma unroll 1
+  for (int i = 0; i < N; ++i) {
+    float x = xl[0];
+    int32_t ti = t[0];
+#pragma unroll
+    for (int u = 1; u < N; ++u) {
+      x = i == u ? xl[u] : x;
+      ti = i == u ? t[u] : ti;
+    }
+    acc_add(w, x, ti);
+  }
+#pragma unroll 1
+  for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < kAccWords; ++k) w[k] += (int64_t)__shfl_xor((long long)w[k], o, 64);
+  return acc_round(w);
 }
 
 // The exponent of the lowest set bit over a token's nonzero elements (element j held by lane
@@ -123,12 +133,10 @@ __device__ inline int token_lsb(const float (&xl)[2]) {
 // token_lsb); while a_i stays below 2^(53 + g) each of them is an fp64 number, s_i is exact
 // and one rounding gives h_c (ties included).  Otherwise s_i is within 128 2^-53 (1 + tiny)
 // a_i of its exact value: where that interval, scaled by 2^-22, rounds to one fp32 number
-// it is h_c, elsewhere the exact accumulator of exact_dot.h decides (xl / xrow / dtype: the
-// token, as below).
-template <bool LEAN = false>
+// it is h_c, elsewhere the exact accumulator of exact_dot.h decides (xl: the token, as below).
 __device__ inline void exact_r_finish(const HeadParams* hp, const double (&s)[2],
                                       const double (&a)[2], int g, const float (&xl)[2],
-                                      const void* xrow, int dtype, float (&r)[2]) {
+                                      float (&r)[2]) {
   const int lane = threadIdx.x & 63;
   // (a_i itself is within 128 2^-53 of the exact sum of |products|)
   const double lim = ldexp(1.0 - 0x1p-40, 53 + min(g, 900));
@@ -136,30 +144,28 @@ __device__ inline void exact_r_finish(const HeadParams* hp, const double (&s)[2]
   for (int i = 0; i < 2; ++i) {
     const int c = lane + 64 * i;
     const double sv = ldexp(s[i], -kTFrac), av = ldexp(a[i], -kTFrac);
-    float h;
-    if (a[i] < lim) {
-      h = (float)sv;
-    } else {
+    float h = (float)sv;
+    bool open = false;                              // not decided by the interval
+    if (!(a[i] < lim)) {
       const double b = av * (kD * 0x1p-52);
       const double bb = b * (1.0 + 0x1p-48) + fabs(sv) * 0x1p-51 + 0x1p-1060;
       const float lo = (float)(sv - bb), hi = (float)(sv + bb);
       h = lo;
-      // (a dropped channel's r is 0 whatever h is)
-      if (lo != hi && hp->bits[c] > 0)
-        h = LEAN ? exact_h_channel_lean(xrow, dtype, hp->Tqt + c * kD)
-                 : exact_h_channel(xl, hp->Tqt + c * kD);
+      open = lo != hi && hp->bits[c] > 0;           // (a dropped channel's r is 0 whatever h is)
+    }
+    for (unsigned long long m = __builtin_amdgcn_ballot_w64(open); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const float e = exact_dot_wave<2>(xl, hp->Tqt + (l + 64 * i) * kD);
+      h = lane == l ? e : h;
     }
     r[i] = h * hp->inv_s[c];
   }
 }
 
 // The same for one wave holding the token: xl holds this lane's elements lane and
-// lane + 64 (as fp32), xrow / dtype address the token in memory for the exact fallback;
-// the transform is read from the parameter block, 16 entries per round trip.
-// LEAN selects the exact routine's register-light form.
-template <bool LEAN = false>
-__device__ inline void exact_r_wave(const HeadParams* hp, const float (&xl)[2],
-                                    const void* xrow, int dtype, float (&r)[2]) {
+// lane + 64 (as fp32); the transform is read from the parameter block, 16 entries per round
+// trip.
+__device__ inline void exact_r_wave(const HeadParams* hp, const float (&xl)[2], float (&r)[2]) {
   const int lane = threadIdx.x & 63;
   double s[2] = {0.0, 0.0}, a[2] = {0.0, 0.0};
   const int4* tc[2] = {reinterpret_cast<const int4*>(hp->Tqt + lane * kD),
@@ -186,7 +192,7 @@ __device__ inline void exact_r_wave(const HeadParams* hp, const float (&xl)[2],
       }
     }
   }
-  exact_r_finish<LEAN>(hp, s, a, token_lsb(xl), xl, xrow, dtype, r);
+  exact_r_finish(hp, s, a, token_lsb(xl), xl, r);
 }
 
 // Certificate of a token encoded from the fixed-point transform (one wave, lane l:

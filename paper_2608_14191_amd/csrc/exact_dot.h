@@ -108,29 +108,4 @@ AATC_HD inline float exact_dot_q22(XF xf, TQ tq, int n) {
   return acc_round(w);
 }
 
-#if defined(__HIPCC__)
-// The same sum with Tq read from 16-byte-aligned memory, 16 entries per round trip (the
-// four loads of a group are issued together), n a multiple of 16.
-template <typename XF>
-__device__ inline float exact_dot_q22_batched(XF xf, const int4* tq, int n) {
-  int64_t w[kAccWords];
-#pragma unroll
-  for (int i = 0; i < kAccWords; ++i) w[i] = 0;
-#pragma unroll 1
-  for (int j0 = 0; j0 < n; j0 += 16) {
-    int4 v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = tq[j0 / 4 + q];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc_add(w, xf(j0 + 4 * q), v[q].x);
-      acc_add(w, xf(j0 + 4 * q + 1), v[q].y);
-      acc_add(w, xf(j0 + 4 * q + 2), v[q].z);
-      acc_add(w, xf(j0 + 4 * q + 3), v[q].w);
-    }
-  }
-  return acc_round(w);
-}
-#endif
-
 }  // namespace aatc
