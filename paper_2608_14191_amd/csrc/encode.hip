@@ -10,7 +10,7 @@
 //     about 2^-14 of the token's largest, for bf16 input); other tokens are certified from
 //     a bound on the fixed-point error, and the few it cannot certify are redone exactly;
 //   - encode_exact_kernel (any layout): every token by the exact one-wave routine;
-//   - encode_token_kernel (a few tokens): the same, one wave per (token, KV head).
+//   - encode_token_kernel (a few tokens): the same sums, one workgroup per (token, KV head).
 #include <algorithm>
 
 #include <hip/hip_fp16.h>
@@ -829,32 +829,77 @@ __device__ inline void store_token_wave(const HeadParams* hp, const float (&r)[2
   wave_lds_sync();
 }
 
-// One wave per (token, KV head), for appends of a few tokens.
+// One workgroup per (token, KV head), for appends of a few tokens: thread (share, channel) sums
+// 32 elements' exact products in fp64, every transform entry of its share in flight at once
+// (they need nothing of the token), the four shares meet in LDS (any order of these sums is
+// exact, or within the bound of exact_r_finish), and one wave quantizes and stores.  The time
+// is latency: 16 tokens x 8 heads took 7.6 us with one wave per (token, head), four round trips
+// to the transform in sequence.
 // With `seq_len` set, block x is a sequence instead: it encodes token seq_len[b] - 1 of
 // sequence b (nothing for an empty sequence) into caches `codes_bstride` bytes and
 // `alpha_bstride` scales apart.
-__global__ __launch_bounds__(64) void encode_token_kernel(
+constexpr int kTokShares = 4;
+__global__ __launch_bounds__(kD * kTokShares) void encode_token_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int dtype, int64_t x_stride,
     int layout, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha, int64_t cap,
     int64_t pos, const int32_t* __restrict__ seq_len, int64_t codes_bstride,
     int64_t alpha_bstride) {
+  constexpr int JP = kD / kTokShares;               // elements per share
   __shared__ uint32_t rec[kRecWords];
+  __shared__ __align__(16) float xs[kD];
+  __shared__ double ps[kTokShares][kD], pa[kTokShares][kD];
+  const int tid = threadIdx.x, c = tid & (kD - 1), share = tid / kD;
+  const int head = blockIdx.y;
+  const HeadParams* hp = head_params(params, head);
+  const int4* tc = reinterpret_cast<const int4*>(hp->Tqt + c * kD + JP * share);
+  int4 t4[JP / 4];
+#pragma unroll
+  for (int q = 0; q < JP / 4; ++q) t4[q] = tc[q];
+  // (the tables the last wave will want, into this compute unit's cache meanwhile)
+  if (share == 1) {
+    const uint32_t w = __float_as_uint(hp->inv_s[c]) ^ hp->bits[c] ^ hp->bit_off[c] ^
+                       (uint32_t)hp->record_bytes ^ (uint32_t)hp->quantizer;
+    asm volatile("" ::"v"(w));
+  }
   int64_t t = pos + blockIdx.x;
   if (seq_len) {
     t = min<int64_t>(max(seq_len[blockIdx.x], 0), cap) - 1;
-    if (t < 0) return;
+    if (t < 0) return;                              // (whole workgroup, before any barrier)
     codes += blockIdx.x * codes_bstride;
     alpha += blockIdx.x * alpha_bstride;
   }
-  const int head = blockIdx.y;
-  for (int i = threadIdx.x; i < kRecWords; i += 64) rec[i] = 0u;
-  wave_lds_sync();
   const void* xrow = static_cast<const char*>(x) +
                      ((int64_t)blockIdx.x * x_stride + (int64_t)head * kD) * (dtype == AATC_BF16 ? 2 : 4);
-  const HeadParams* hp = head_params(params, head);
+  if (tid < kD) xs[tid] = load_elem(xrow, dtype, tid);
+  else for (int i = tid - kD; i < kRecWords; i += kD * (kTokShares - 1)) rec[i] = 0u;
+  __syncthreads();
+  double s = 0.0, a = 0.0;
+#pragma unroll
+  for (int q = 0; q < JP / 4; ++q) {
+    const float4 x4 = *reinterpret_cast<const float4*>(&xs[JP * share + 4 * q]);
+    const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
+    const int tv[4] = {t4[q].x, t4[q].y, t4[q].z, t4[q].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double xd = (double)xv[e], td = (double)tv[e];
+      s = fma(xd, td, s);
+      a = fma(fabs(xd), fabs(td), a);
+    }
+  }
+  ps[share][c] = s;
+  pa[share][c] = a;
+  __syncthreads();
+  if (tid >= 64) return;                            // (no barrier follows)
+  double s2[2], a2[2];
   float xl[2], r[2];
-  load_token_pair(xrow, dtype, xl);
-  exact_r_wave_pipelined(hp, xl, r);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int ch = tid + 64 * i;
+    s2[i] = (ps[0][ch] + ps[1][ch]) + (ps[2][ch] + ps[3][ch]);
+    a2[i] = (pa[0][ch] + pa[1][ch]) + (pa[2][ch] + pa[3][ch]);
+    xl[i] = xs[ch];
+  }
+  exact_r_finish(hp, s2, a2, token_lsb(xl), xl, r);
   store_token_wave(hp, r, layout, codes, alpha, cap, t, head, rec);
 }
 
@@ -916,8 +961,8 @@ aatc_status launch_encode(const void* params, int n_heads, const void* x, aatc_d
                           void* codes, uint16_t* alpha, int64_t cap, int64_t pos,
                           void* stream) {
   if (n_tok <= kSmallBatch) {
-    hipLaunchKernelGGL(encode_token_kernel, dim3((unsigned)n_tok, (unsigned)n_heads), dim3(64),
-                       0, (hipStream_t)stream, params, x, (int)x_dtype, x_tok_stride,
+    hipLaunchKernelGGL(encode_token_kernel, dim3((unsigned)n_tok, (unsigned)n_heads),
+                       dim3(kD * kTokShares), 0, (hipStream_t)stream, params, x, (int)x_dtype, x_tok_stride,
                        (int)layout, static_cast<uint8_t*>(codes), alpha, cap, pos, nullptr,
                        (int64_t)0, (int64_t)0);
     return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
@@ -963,8 +1008,8 @@ aatc_status launch_encode_last(const void* params, int n_heads, int batch, const
                                aatc_dtype x_dtype, aatc_layout layout, void* codes,
                                uint16_t* alpha, int64_t cap, int record_bytes,
                                const int32_t* seq_len, void* stream) {
-  hipLaunchKernelGGL(encode_token_kernel, dim3((unsigned)batch, (unsigned)n_heads), dim3(64), 0,
-                     (hipStream_t)stream, params, x, (int)x_dtype, (int64_t)n_heads * kD,
+  hipLaunchKernelGGL(encode_token_kernel, dim3((unsigned)batch, (unsigned)n_heads),
+                     dim3(kD * kTokShares), 0, (hipStream_t)stream, params, x, (int)x_dtype, (int64_t)n_heads * kD,
                      (int)layout, static_cast<uint8_t*>(codes), alpha, cap, (int64_t)0, seq_len,
                      (int64_t)n_heads * cap * record_bytes, (int64_t)n_heads * cap);
   return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
