@@ -4,9 +4,10 @@
 // A group is gkv consecutive KV heads; its token is the concatenation of their vectors
 // (d = 128 gkv elements, KV head kk of the group at [128 kk, 128 kk + 128)).  Encode and
 // decode follow Alg. 1 on those d-element vectors with the group's transform:
-//   - group_encode_kernel: h = T^T x exactly rounded (the exact one-wave routine of the
+//   - group_encode_mfma_kernel: h = T^T x exactly rounded (the integer products of the
 //     per-head path, over d elements), one alpha per (token, group), codes packed into
-//     one token-major record per (token, group);
+//     one token-major record per (token, group); group_encode_exact_kernel redoes the few
+//     tokens it cannot certify;
 //   - group_query_kernel: per query head, the channel weights W_c = q~_c s_c 2^(1-b_c)
 //     scale log2(e) of q~ = T[block]^T q (App. B's effective query; the query of KV head k
 //     lives in block k % gkv of its group);
@@ -20,6 +21,7 @@
 //     (by 32-row chunks).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -60,136 +62,518 @@ __device__ inline int record_code(const uint32_t* row, int off, int b) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Encode: one wave per (token, group); lane l holds elements and channels l + 64 i.
-// h_c = fl32(sum_j x_j T_jc) exactly: fp64 sums of the exact products x_j T_jc, exact while
-// |x|_1 stays below 2^(31 + g) (every product is a multiple of 2^(g - 22), g the lowest set
-// bit of the token's elements, and |T| <= 1); otherwise an interval test, and the exact
-// accumulator where the interval straddles an fp32 rounding boundary.
+// Encode on the matrix cores: the integer product of the per-head bulk encode (token in fixed
+// point X = x 2^S, transform as the integers T 2^22, int8 limbs of both, int32 sums by weight,
+// H = sum_j X_j Tq_jc) over d = 128 gkv elements.  bf16: three limbs of X (max |X| in
+// [2^21, 2^22)), fp32: four ([2^29, 2^30)).  |H| can reach 2^53 (bf16) or 2^61 (fp32): it is
+// formed in fp64 within 2^9, and E = sum_j |x_j 2^S - X_j| bounds |H - H_exact| by E 2^22 (plus
+// those roundings).  A token whose E is 0 (bf16) has its exact H; for the others the scale and
+// every code are certified against the bound, and the few that fail (0.2 % of key tokens at
+// d = 512, bf16) get the scale mark kGRedo, which group_encode_exact_kernel, launched next,
+// redoes exactly.
+//
+// A workgroup of eight waves takes 16 TT tokens against all channels: the X limbs in LDS in
+// operand order (96 KiB at d = 512 and 64 tokens), shared by the waves; a wave owns every
+// eighth tile of 16 channels and reads their transform columns straight from the parameter
+// block into operands (nothing to share, and the limbs take a few byte permutes per 64
+// products), so the transform is read once per 16 TT tokens.  What bounds it: the products
+// (bf16: 9 x 8 per 16 x 16 outputs, 18 us per 8192 tokens and two groups).  Measured, 8192
+// tokens, two groups of 512 channels, K and V: 5890 us before (fp64 VALU products, a wave per
+// two tokens).
 // ---------------------------------------------------------------------------------------
-constexpr int kGTokensPerWave = 2;              // tokens sharing each row of T in a wave
+typedef int gi4 __attribute__((ext_vector_type(4)));
+constexpr uint16_t kGRedo = 0xFFFFu;             // (an fp16 NaN: no token scale has it)
+constexpr int kGEncWaves = 8;
+
+__device__ inline float g_cross_row_max(float v) {      // over lanes l, l ^ 16, l ^ 32, l ^ 48
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float g_cross_row_sum(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sixteen consecutive elements of a token as fp32.
+__device__ inline void g_load16(const void* x, int dtype, int64_t at, bool vec, float (&v)[16]) {
+  if (vec && dtype == AATC_BF16) {
+    const uint4* p = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + at);
+    const uint4 a = p[0], b = p[1];
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[2 * i] = __uint_as_float(w[i] << 16);
+      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  } else if (vec) {
+    const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(x) + at);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 a = p[i];
+      v[4 * i] = a.x, v[4 * i + 1] = a.y, v[4 * i + 2] = a.z, v[4 * i + 3] = a.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = load_elem(x, dtype, at + i);
+  }
+}
+
+// The limbs (balanced int8 digits, lowest first) of four integers |v| <= 2^30 as one dword per
+// limb: byte e of limb a of v_e.
+template <int XL>
+__device__ inline void g_limbs4(const int (&v)[4], uint32_t (&out)[XL]) {
+  uint32_t y[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = (uint32_t)v[e] + (XL == 3 ? 0x8080u : 0x808080u);
+  const uint32_t l01 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);
+  const uint32_t l23 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
+  const uint32_t h01 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);
+  const uint32_t h23 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u) ^ 0x80808080u;
+  out[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u) ^ 0x80808080u;
+  out[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u) ^ (XL == 3 ? 0u : 0x80808080u);
+  if constexpr (XL == 4) out[3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+}
+
+template <int NC, bool BF16, int TT>
+__global__ __launch_bounds__(64 * kGEncWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void group_encode_mfma_kernel(const void* __restrict__ params, const void* __restrict__ x,
+                              int64_t n_tok, int64_t x_stride, int vec,
+                              uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha,
+                              int64_t cap, int64_t pos) {
+  constexpr int D = 64 * NC;
+  constexpr int XL = BF16 ? 3 : 4, NS = XL + 2;     // limbs of X, limb-product sums
+  constexpr int NT = 64 * kGEncWaves;
+  constexpr int TOK = 16 * TT;                      // tokens of the workgroup
+  constexpr int NCT = D / 16 / kGEncWaves;          // channel tiles per wave
+  constexpr int WPT = kGEncWaves / TT;              // waves that stage one token tile
+  constexpr int KPW = (NC + WPT - 1) / WPT;         // 64-element pieces each of them stages
+  constexpr int DT = BF16 ? AATC_BF16 : AATC_F32;
+  extern __shared__ __align__(16) uint8_t smem[];   // X limbs [XL][NC][TT][64 lanes][16], then
+                                                    // the record rows [TOK][R / 4 + 1]
+  __shared__ float sx[TOK][WPT];                    // per token: the pieces' max |x|, then E
+  __shared__ float se[TOK][WPT];
+  __shared__ float sm[3][TOK][kGEncWaves];          // per token and wave: max |u| and its bounds
+  __shared__ unsigned sbad[TOK];
+  __shared__ uint16_t sa[TOK];                      // the scales
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t t0 = (int64_t)blockIdx.x * TOK;
+  const GroupParams* gp = group_params(params, g);
+  if (gp->max_bits > 8) {
+    // Codes wider than 8 bits need not fit a four-channel field: every token to the exact
+    // kernel (uniform over the grid).
+    if (tid < TOK && t0 + tid < n_tok) alpha[(int64_t)g * cap + pos + t0 + tid] = kGRedo;
+    return;
+  }
+  const int rw = gp->record_bytes >> 2, rs = rw + 1;
+  // (1) Stage X: wave (tile tt, piece wk) holds its token's pieces kc = wk + WPT i in registers
+  //     until the token's maximum is known.
+  {
+    const int tt = wave % TT, wk = wave / TT, t = 16 * tt + n;
+    const bool ok = t0 + t < n_tok;
+    const int64_t at = (t0 + (ok ? t : 0)) * x_stride + (int64_t)g * D + 16 * kg;
+    float xv[KPW][16], m = 0.f;
+#pragma unroll
+    for (int i = 0; i < KPW; ++i) {
+      const int kc = wk + WPT * i;
+      if (kc < NC) g_load16(x, DT, at + 64 * kc, vec != 0, xv[i]);      // (uniform)
+    }
+#pragma unroll
+    for (int i = 0; i < KPW; ++i)
+      if (wk + WPT * i < NC) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          xv[i][e] = ok ? xv[i][e] : 0.f;
+          m = fmaxf(m, fabsf(xv[i][e]));
+        }
+      }
+    m = g_cross_row_max(m);
+    if (kg == 0) sx[t][wk] = m;
+    if (tid < TOK) sbad[tid] = 0u;
+    __syncthreads();
+    m = sx[t][0];
+#pragma unroll
+    for (int w = 1; w < WPT; ++w) m = fmaxf(m, sx[t][w]);
+    const int S = token_shift(m) + 8 * (XL - 3);
+    const float sc = ldexpf(1.f, min(max(S, -kTFrac), 100 - kTFrac));
+    float E = 0.f;
+#pragma unroll
+    for (int i = 0; i < KPW; ++i) {
+      const int kc = wk + WPT * i;
+      if (kc >= NC) break;
+      uint32_t lb[XL][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        int v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xe = xv[i][4 * q + e], r = rintf(xe * sc);
+          E += fabsf(fmaf(xe, sc, -r));            // (exact: at most 24 significant bits)
+          v[e] = (int)r;
+        }
+        uint32_t o[XL];
+        g_limbs4<XL>(v, o);
+#pragma unroll
+        for (int a = 0; a < XL; ++a) lb[a][q] = o[a];
+      }
+#pragma unroll
+      for (int a = 0; a < XL; ++a)
+        *reinterpret_cast<uint4*>(smem + (((size_t)(a * NC + kc) * TT + tt) * 64 + lane) * 16) =
+            make_uint4(lb[a][0], lb[a][1], lb[a][2], lb[a][3]);
+    }
+    E = g_cross_row_sum(E);
+    if (kg == 0) se[t][wk] = E;
+  }
+  __syncthreads();
+  // (2) Products, channel tile by channel tile: u_c = fl32(fl32(H) / s_c) (r_c 2^(S + 22)) of
+  //     channels 16 ct + 4 kg + i of tokens 16 tt + n stays in registers.
+  float uv[NCT][TT][4];
+  {
+    const int4* tq = reinterpret_cast<const int4*>(gp->Tqt);
+    int4 raw[2][4];
+    auto fetch = [&](int step, int4 (&r)[4]) {     // columns of tile step / NC, piece step % NC
+      const int ct = wave + kGEncWaves * (step / NC), kc = step % NC;
+      const int4* p = tq + ((size_t)(16 * ct + n) * D + 64 * kc + 16 * kg) / 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r[q] = p[q];
+    };
+    fetch(0, raw[0]);
+#pragma unroll
+    for (int it = 0; it < NCT; ++it) {
+      gi4 acc[TT][NS];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int k = 0; k < NS; ++k) acc[tt][k] = (gi4){0, 0, 0, 0};
+#pragma unroll 2
+      for (int kc = 0; kc < NC; ++kc) {
+        const int step = it * NC + kc;
+        int4 cur[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cur[q] = raw[0][q];
+        if (step + 1 < NCT * NC) fetch(step + 1, raw[0]);
+        gi4 a[3];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int v[4] = {cur[q].x, cur[q].y, cur[q].z, cur[q].w};
+          uint32_t o[3];
+          g_limbs4<3>(v, o);
+#pragma unroll
+          for (int l = 0; l < 3; ++l) a[l][q] = (int)o[l];
+        }
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          gi4 b[XL];
+#pragma unroll
+          for (int l = 0; l < XL; ++l)
+            b[l] = *reinterpret_cast<const gi4*>(smem + (((size_t)(l * NC + kc) * TT + tt) * 64 + lane) * 16);
+          auto mac = [&](int t, int xa) {
+            acc[tt][xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t], b[xa], acc[tt][xa + t], 0, 0, 0);
+          };
+          // (a product's sum is never the previous product's)
+#pragma unroll
+          for (int xa = XL - 1; xa >= 0; --xa) mac(2, xa);
+          mac(1, 0);
+          mac(0, 0);
+#pragma unroll
+          for (int xa = XL - 1; xa >= 1; --xa) mac(1, xa);
+#pragma unroll
+          for (int xa = 1; xa < XL; ++xa) mac(0, xa);
+        }
+      }
+      const int c0 = 16 * (wave + kGEncWaves * it) + 4 * kg;
+      const float4 is4 = *reinterpret_cast<const float4*>(gp->inv_s + c0);
+      const float is[4] = {is4.x, is4.y, is4.z, is4.w};
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // (one sum at a time: two do not fit 32 bits at d = 512)
+          double H = (double)acc[tt][NS - 1][i];
+#pragma unroll
+          for (int k = NS - 2; k >= 0; --k) H = fma(H, 256.0, (double)acc[tt][k][i]);
+          uv[it][tt][i] = (float)H * is[i];
+        }
+    }
+  }
+  // (3) Per token: the largest |u| and, for tokens with an error bound, the range of the exact
+  //     one, over this wave's channels, then over the waves.
+  float eH[TT];                                     // bound of |H - H_exact|, 0 when exact
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    float E = se[16 * tt + n][0];
+#pragma unroll
+    for (int w = 1; w < WPT; ++w) E += se[16 * tt + n][w];
+    // (2^-13 in units of 2^22: the fp64 roundings of H, which pass 2^53 only with E > 0 or
+    // fp32 input; the factor covers E's own rounding and the fp32 products below)
+    eH[tt] = (BF16 && E == 0.f) ? 0.f : (E + 0x1p-13f) * (1.f + 0x1p-14f) * 0x1p22f;
+    float am = 0.f, lo = 0.f, hi = 0.f;
+#pragma unroll
+    for (int it = 0; it < NCT; ++it) {
+      const int c0 = 16 * (wave + kGEncWaves * it) + 4 * kg;
+      const float4 is4 = *reinterpret_cast<const float4*>(gp->inv_s + c0);
+      const float is[4] = {is4.x, is4.y, is4.z, is4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float u = fabsf(uv[it][tt][i]);       // (0 on dropped channels)
+        am = fmaxf(am, u);
+        hi = fmaxf(hi, fmaf(eH[tt], is[i], u));
+        lo = fmaxf(lo, fmaf(-eH[tt], is[i], u));
+      }
+    }
+    am = g_cross_row_max(am);
+    lo = g_cross_row_max(lo);
+    hi = g_cross_row_max(hi);
+    if (kg == 0) {
+      sm[0][16 * tt + n][wave] = am;
+      sm[1][16 * tt + n][wave] = lo;
+      sm[2][16 * tt + n][wave] = hi;
+    }
+  }
+  __syncthreads();                                  // (the X limbs are consumed too)
+  uint32_t* rec = reinterpret_cast<uint32_t*>(smem);
+  for (int i = tid; i < TOK * rs; i += NT) rec[i] = 0u;
+  // (4) Scale and codes; channels 16 ct + 4 kg .. + 3 are one bit field of <= 32 bits.
+  const bool midrise = gp->quantizer == AATC_QUANT_MIDRISE;
+  uint32_t field[NCT][TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    const int t = 16 * tt + n;
+    float mx = sx[t][0], am = 0.f, lo = 0.f, hi = 0.f;
+#pragma unroll
+    for (int w = 1; w < WPT; ++w) mx = fmaxf(mx, sx[t][w]);
+#pragma unroll
+    for (int w = 0; w < kGEncWaves; ++w) {
+      am = fmaxf(am, sm[0][t][w]);
+      lo = fmaxf(lo, sm[1][t][w]);
+      hi = fmaxf(hi, sm[2][t][w]);
+    }
+    // With k = S + 22 in [0, 100] every value here is r 2^k of the canonical sequence, a normal
+    // fp32 number or zero; other tokens are redone.
+    const int k = token_shift(mx) + 8 * (XL - 3) + kTFrac;
+    const float amax_r = ldexpf(am, -k);
+    const __half a16 = token_alpha(amax_r);
+    const float inv_ak = ldexpf(inverse_alpha(a16), -k);
+    bool bad = k < 0 || k > 100;
+    if (eH[tt] > 0.f) {
+      const float lo_r = ldexpf(lo, -k) - 0x1p-21f * amax_r;
+      const float hi_r = ldexpf(hi, -k) + 0x1p-21f * amax_r + 0x1p-140f;
+      bad |= __half_as_ushort(token_alpha(fmaxf(lo_r, 0.f))) != __half_as_ushort(token_alpha(hi_r));
+    }
+    const float ea = eH[tt] * inv_ak;
+    auto codes_of = [&](auto certify, auto mid_rise) {
+      constexpr bool CERT = decltype(certify)::value, MR = decltype(mid_rise)::value;
+#pragma unroll
+      for (int it = 0; it < NCT; ++it) {
+        const int c0 = 16 * (wave + kGEncWaves * it) + 4 * kg;
+        uint32_t b4 = *reinterpret_cast<const uint32_t*>(gp->bits + c0);
+        const float4 is4 = *reinterpret_cast<const float4*>(gp->inv_s + c0);
+        const float is[4] = {is4.x, is4.y, is4.z, is4.w};
+        uint32_t f = 0u, sh = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i, b4 >>= 8) {
+          const uint32_t b = b4 & 255u;
+          const float p2 = __uint_as_float((126u + max(b, 1u)) << 23);       // 2^(b - 1)
+          const float xq = (uv[it][tt][i] * inv_ak) * p2;
+          const float xc = __builtin_amdgcn_fmed3f(xq, -p2, p2 - 1.f);
+          int code;
+          if constexpr (MR) asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(code) : "v"(xc));
+          else asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(code) : "v"(xc));
+          f |= ((uint32_t)code & ((1u << b) - 1u)) << sh;                    // (b = 0: nothing)
+          sh += b;
+          if constexpr (CERT) {
+            // the bound in x units plus both evaluations' fp32 roundings, against the distance
+            // to the nearest decision boundary (dropped channels: u = 0, 1 / s = 0)
+            const float kf = p2 * is[i] * (1.f + 0x1p-20f);
+            const float mg = fmaf(kf, ea, fmaf(0x1p-21f, fabsf(xq), 0x1p-22f));
+            const float d = fabsf(__builtin_amdgcn_fractf(xq) - 0.5f);
+            bad |= eH[tt] > 0.f && (MR ? (kf > 0.f && d >= 0.5f - mg) : (d <= mg));
+          }
+        }
+        field[it][tt] = f;
+      }
+    };
+    const bool cert = __builtin_amdgcn_ballot_w64(eH[tt] > 0.f) != 0ull;
+    if (midrise) {
+      if (cert) codes_of(std::true_type{}, std::true_type{});
+      else codes_of(std::false_type{}, std::true_type{});
+    } else {
+      if (cert) codes_of(std::true_type{}, std::false_type{});
+      else codes_of(std::false_type{}, std::false_type{});
+    }
+    if (bad) atomicOr(&sbad[t], 1u);
+    if (wave == 0 && kg == 0) sa[t] = __half_as_ushort(a16);
+  }
+  __syncthreads();                                  // (rows cleared)
+#pragma unroll
+  for (int it = 0; it < NCT; ++it) {
+    const int off = gp->bit_off[16 * (wave + kGEncWaves * it) + 4 * kg];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      uint32_t* w0 = rec + (16 * tt + n) * rs + (off >> 5);
+      const uint64_t v = (uint64_t)field[it][tt] << (off & 31);
+      if ((uint32_t)v) atomicOr(w0, (uint32_t)v);
+      if ((uint32_t)(v >> 32)) atomicOr(w0 + 1, (uint32_t)(v >> 32));
+    }
+  }
+  __syncthreads();
+  const int nt = (int)min<int64_t>(TOK, n_tok - t0);
+  uint32_t* out = reinterpret_cast<uint32_t*>(codes) + ((int64_t)g * cap + pos + t0) * rw;
+  const uint32_t mk = rw > 1 ? (uint32_t)((0x100000000ull + (uint32_t)rw - 1u) / (uint32_t)rw) : 0u;
+  for (int i = tid; i < nt * rw; i += NT) {
+    const int t = rw > 1 ? (int)__umulhi((uint32_t)i, mk) : i;
+    if (!sbad[t]) out[i] = rec[t * rs + (i - t * rw)];
+  }
+  if (tid < nt)
+    alpha[(int64_t)g * cap + pos + t0 + tid] = sbad[tid] ? kGRedo : sa[tid];
+}
+
+// The tokens left with the mark kGRedo, exactly: h_c = fl32(sum_j x_j T_jc) from fp64 sums of
+// the exact products x_j T_jc, exact while |x|_1 stays below 2^(31 + g) (every product, hence
+// every partial sum, is a multiple of 2^(g - 22), g the lowest set bit of the token's elements,
+// and |T| <= 1); otherwise an interval test, and the exact accumulator where the interval
+// straddles an fp32 rounding boundary.  A workgroup scans kGFixTokens marks and takes its
+// marked tokens one at a time: thread (part, channel) sums a share of the elements (rows of T
+// coalesced over the channels, sixteen in flight), the shares meet in LDS.  (A wave per token
+// walked 512 rows in sequence, over 100 us.)
+constexpr int kGFixThreads = 1024;
+constexpr int kGFixTokens = 64;
 template <int NC>
-__global__ __launch_bounds__(kGThreads) void group_encode_kernel(
+__global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int dtype, int64_t n_tok,
     int64_t x_stride, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha, int64_t cap,
     int64_t pos) {
   constexpr int D = 64 * NC;
-  constexpr int TPW = kGTokensPerWave;
+  constexpr int NP = kGFixThreads / D;              // element shares
+  constexpr int JP = (D + NP - 1) / NP;             // elements per share
   constexpr int kRow = D * kMaxBits / 32 + 1;
-  __shared__ uint32_t rec[kGThreads / 64][kRow];
-  const int g = blockIdx.y, lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t t0 = ((int64_t)blockIdx.x * (kGThreads / 64) + wave) * TPW;
-  if (t0 >= n_tok) return;                          // (whole wave; no barrier follows)
-  const int nv = (int)min((int64_t)TPW, n_tok - t0);   // this wave's tokens
+  static_assert(JP % 16 == 0 || D % NP == 0, "whole shares");
+  __shared__ uint16_t list[kGFixTokens];
+  __shared__ int n_list, glsb_s;
+  __shared__ float xs[D];
+  __shared__ double part[NP][D];
+  __shared__ float red[kGFixThreads / 64], redl[kGFixThreads / 64];
+  __shared__ uint32_t row[kRow];
+  __shared__ float hx[D];
+  __shared__ uint16_t open_c[D];
+  __shared__ int n_open;
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const GroupParams* gp = group_params(params, g);
+  const int64_t base = (int64_t)blockIdx.x * kGFixTokens;
+  if (tid == 0) n_list = 0;
+  __syncthreads();
+  if (tid < kGFixTokens && base + tid < n_tok &&
+      alpha[(int64_t)g * cap + pos + base + tid] == kGRedo)
+    list[atomicAdd(&n_list, 1)] = (uint16_t)tid;
+  __syncthreads();
+  const int cnt = n_list;
   const int rw = gp->record_bytes >> 2;
-  uint32_t* row = rec[wave];
   const size_t esize = dtype == AATC_BF16 ? 2 : 4;
-  const void* xrow[TPW];
-  float xl[TPW][NC];
-#pragma unroll
-  for (int u = 0; u < TPW; ++u) {
-    xrow[u] = static_cast<const char*>(x) + ((t0 + min(u, nv - 1)) * x_stride + (int64_t)g * D) * esize;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) xl[u][i] = u < nv ? load_elem(xrow[u], dtype, lane + 64 * i) : 0.f;
-  }
-  double s[TPW][NC];
-#pragma unroll
-  for (int u = 0; u < TPW; ++u)
-#pragma unroll
-    for (int k = 0; k < NC; ++k) s[u][k] = 0.0;
-  // Row j of T (fp32, exact multiples of 2^-22): lane l reads channels l + 64 k, one
-  // coalesced row per element, used for the wave's TPW tokens; products are exact in fp64.
-  const float* trow = gp->T + lane;
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-#pragma unroll 2
-    for (int jj = 0; jj < 64; ++jj) {
-      const float* tr = trow + (size_t)(64 * i + jj) * D;
-      double tv[NC];
-#pragma unroll
-      for (int k = 0; k < NC; ++k) tv[k] = (double)tr[64 * k];
-#pragma unroll
-      for (int u = 0; u < TPW; ++u) {
-        const double xd =
-            (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(xl[u][i]), jj));
-#pragma unroll
-        for (int k = 0; k < NC; ++k) s[u][k] = fma(xd, tv[k], s[u][k]);
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < TPW; ++u) {
-    if (u >= nv) break;                             // (uniform)
-    const int64_t t = t0 + u;
-    // Lowest set bit over the token's nonzero elements (4096 for a zero token), and |x|_1,
-    // which bounds sum_j |x_j T_jc| for every channel (|T| <= 1).
+  for (int li = 0; li < cnt; ++li) {
+    const int64_t t = base + list[li];
+    const void* xrow = static_cast<const char*>(x) + (t * x_stride + (int64_t)g * D) * esize;
+    // The token, its lowest set bit (4096 for a zero token) and |x|_1.
     int glsb = 4096;
     float l1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const uint32_t bv = __float_as_uint(xl[u][i]) & 0x7fffffffu;
-      l1 += fabsf(xl[u][i]);
+    if (tid < D) {
+      const float xe = load_elem(xrow, dtype, tid);
+      xs[tid] = xe;
+      l1 = fabsf(xe);
+      const uint32_t bv = __float_as_uint(xe) & 0x7fffffffu;
       if (bv != 0u) {
         const int ef = (int)(bv >> 23), m = (int)(bv & 0x7fffffu);
-        glsb = min(glsb, ef ? ef - 150 + __builtin_ctz((uint32_t)m | 0x800000u)
-                            : -149 + __builtin_ctz((uint32_t)m));
+        glsb = ef ? ef - 150 + __builtin_ctz((uint32_t)m | 0x800000u) : -149 + __builtin_ctz((uint32_t)m);
       }
     }
+    if (tid == 0) {
+      glsb_s = 4096;
+      n_open = 0;
+    }
+    for (int i = tid; i < kRow; i += kGFixThreads) row[i] = 0u;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) glsb = min(glsb, __shfl_xor(glsb, o, 64));
     l1 = g_wave_sum(l1);
-    // Every product, hence every partial sum, is a multiple of 2^(g - 22); below
-    // 2^(53 + g - 22) in magnitude they are all fp64 numbers and s is exact.  The float sum
-    // l1 is within 2^-14 relative of |x|_1.
-    const double l1d = (double)l1 * (1.0 + 0x1p-14);
-    const bool exact = l1d < ldexp(1.0, 31 + min(glsb, 900));
-    float r[NC];
-    float m = 0.f;
+    if (lane == 0) redl[wave] = l1;
+    __syncthreads();
+    if (lane == 0) atomicMin(&glsb_s, glsb);
+    const int c = tid % D, pt = tid / D;
+    if (pt < NP) {
+      double s0 = 0.0, s1 = 0.0;
+      const float* tr = gp->T + c;
+#pragma unroll 1
+      for (int j0 = pt * JP; j0 < (pt + 1) * JP; j0 += 16) {
+        float tv[16];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int c = lane + 64 * k;
-      const double sv = s[u][k];
-      float h;
-      if (exact) {
-        h = (float)sv;
-      } else {
+        for (int k = 0; k < 16; ++k) tv[k] = tr[(size_t)(j0 + k) * D];
+#pragma unroll
+        for (int k = 0; k < 16; k += 2) {
+          s0 = fma((double)xs[j0 + k], (double)tv[k], s0);
+          s1 = fma((double)xs[j0 + k + 1], (double)tv[k + 1], s1);
+        }
+      }
+      part[pt][c] = s0 + s1;
+    }
+    __syncthreads();
+    float h = 0.f;
+    int b = 0;
+    bool open = false;                              // not decided by the interval
+    if (tid < D) {
+      double sv = part[0][tid];
+#pragma unroll
+      for (int p = 1; p < NP; ++p) sv += part[p][tid];
+      l1 = redl[0];
+      for (int w = 1; w < kGFixThreads / 64; ++w) l1 += redl[w];
+      // The float sum l1 is within 2^-14 relative of |x|_1.
+      const double l1d = (double)l1 * (1.0 + 0x1p-14);
+      b = gp->bits[tid];
+      h = (float)sv;
+      if (!(l1d < ldexp(1.0, 31 + min(glsb_s, 900)))) {
         // fp64 sum of D exact products: |error| <= D 2^-53 sum |p| <= D 2^-53 |x|_1
         const double bb = l1d * (D * 0x1p-52) + fabs(sv) * 0x1p-51 + 0x1p-1060;
         const float lo = (float)(sv - bb), hi = (float)(sv + bb);
         h = lo;
-        if (lo != hi && gp->bits[c] > 0) {
-          // (the exact accumulator holds any sum of up to 512 such products: each is below
-          // 2^46 units of its lsb, so 512 of them stay below 2^137, inside its 320 bits)
-          const int32_t* tc = gp->Tqt + (size_t)c * D;
-          const void* xr = xrow[u];
-          h = exact_dot_q22([&](int j) { return load_elem(xr, dtype, j); },
-                            [&](int j) { return tc[j]; }, D);
-        }
+        open = lo != hi && b > 0;
       }
-      r[k] = h * gp->inv_s[c];
-      m = fmaxf(m, gp->bits[c] > 0 ? fabsf(r[k]) : 0.f);
     }
-    const __half a16 = token_alpha(g_wave_max(m));
-    const float inv = inverse_alpha(a16);
-    const bool midrise = gp->quantizer == AATC_QUANT_MIDRISE;
-    for (int i = lane; i < rw + 1; i += 64) row[i] = 0u;
-    group_wave_sync();                               // the cleared row before the ORs
+    if (open) open_c[atomicAdd(&n_open, 1)] = (uint16_t)tid;
+    __syncthreads();
+    // The open channels by the exact accumulator, one per wave at a time (it holds any sum of
+    // up to 512 such products: each is below 2^46 units of its lsb, so 512 of them stay below
+    // 2^137, inside its 320 bits).
+    for (int k = wave; k < n_open; k += kGFixThreads / 64) {
+      const int oc = open_c[k];
+      float xl[NC];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int c = lane + 64 * k;
-      const int b = gp->bits[c], off = gp->bit_off[c];
-      if (b > 0) {
-        const uint32_t q = quantize_code(r[k], inv, b, midrise);
-        atomicOr(&row[off >> 5], q << (off & 31));
-        if ((off & 31) + b > 32) atomicOr(&row[(off >> 5) + 1], q >> (32 - (off & 31)));
-      }
+      for (int i = 0; i < NC; ++i) xl[i] = xs[lane + 64 * i];
+      const float e = exact_dot_wave<NC>(xl, gp->Tqt + (size_t)oc * D);
+      if (lane == 0) hx[oc] = e;
     }
-    group_wave_sync();                               // every OR before the read-out
+    __syncthreads();
+    if (open) h = hx[tid];
+    const float r = tid < D ? h * gp->inv_s[tid] : 0.f;
+    const float m = g_wave_max(b > 0 ? fabsf(r) : 0.f);
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+    float am = red[0];
+    for (int w = 1; w < kGFixThreads / 64; ++w) am = fmaxf(am, red[w]);
+    const __half a16 = token_alpha(am);
+    if (b > 0) {
+      const uint32_t q = quantize_code(r, inverse_alpha(a16), b, gp->quantizer == AATC_QUANT_MIDRISE);
+      const int off = gp->bit_off[tid];
+      atomicOr(&row[off >> 5], q << (off & 31));
+      if ((off & 31) + b > 32) atomicOr(&row[(off >> 5) + 1], q >> (32 - (off & 31)));
+    }
+    __syncthreads();
     uint32_t* out = reinterpret_cast<uint32_t*>(codes + ((int64_t)g * cap + pos + t) * gp->record_bytes);
-    for (int i = lane; i < rw; i += 64) out[i] = row[i];
-    if (lane == 0) alpha[(int64_t)g * cap + pos + t] = __half_as_ushort(a16);
-    group_wave_sync();                               // the read-out before the next clear
+    for (int i = tid; i < rw; i += kGFixThreads) out[i] = row[i];
+    if (tid == 0) alpha[(int64_t)g * cap + pos + t] = __half_as_ushort(a16);
+    __syncthreads();                                // (the row and sums before the next token)
   }
 }
 
@@ -1273,6 +1657,51 @@ aatc_status launch_decode_nc(GroupDecodeArgs a, int batch, int rwk, int rwv, hip
   return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
 }
 
+template <int NC, bool BF16, int TT>
+aatc_status launch_group_encode_tt(const void* params, int n_groups, const void* x, int64_t n_tok,
+                                   int64_t x_tok_stride, int vec, uint8_t* codes, uint16_t* alpha,
+                                   int64_t cap, int64_t pos, hipStream_t st) {
+  constexpr int D = 64 * NC;
+  // X limbs, or the record rows (codes of at most 8 bits: R <= D bytes).
+  constexpr size_t lds = std::max((size_t)(BF16 ? 3 : 4) * D * 16 * TT, (size_t)16 * TT * (D / 4 + 1) * 4);
+  static GroupLds limit;
+  if (!limit.ensure((const void*)group_encode_mfma_kernel<NC, BF16, TT>, lds)) return AATC_E_DEVICE;
+  const int64_t blocks = (n_tok + 16 * TT - 1) / (16 * TT);
+  if (blocks > 0x7fffffff) return AATC_E_UNSUPPORTED;
+  hipLaunchKernelGGL((group_encode_mfma_kernel<NC, BF16, TT>),
+                     dim3((unsigned)blocks, (unsigned)n_groups), dim3(64 * kGEncWaves), lds, st,
+                     params, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos);
+  return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
+}
+
+template <int NC>
+aatc_status launch_group_encode_nc(const void* params, int n_groups, const void* x,
+                                   aatc_dtype x_dtype, int64_t n_tok, int64_t x_tok_stride,
+                                   uint8_t* codes, uint16_t* alpha, int64_t cap, int64_t pos,
+                                   hipStream_t st) {
+  const int vec = (reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+                   (size_t)x_tok_stride * (x_dtype == AATC_BF16 ? 2 : 4) % 16 == 0) ? 1 : 0;
+  // Tokens per workgroup: as many as leave the chip a workgroup per compute unit (each reads
+  // the whole transform), fp32 at most 32 (registers).
+  auto fills = [&](int tt) { return (n_tok / (16 * tt)) * n_groups >= 192; };
+  aatc_status s;
+  if (x_dtype == AATC_BF16) {
+    if (fills(4)) s = launch_group_encode_tt<NC, true, 4>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
+    else if (fills(2)) s = launch_group_encode_tt<NC, true, 2>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
+    else s = launch_group_encode_tt<NC, true, 1>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
+  } else {
+    if (fills(2)) s = launch_group_encode_tt<NC, false, 2>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
+    else s = launch_group_encode_tt<NC, false, 1>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
+  }
+  if (s != AATC_OK) return s;
+  // The tokens whose certificate failed (stream order: after the kernel above).
+  hipLaunchKernelGGL((group_encode_exact_kernel<NC>),
+                     dim3((unsigned)((n_tok + kGFixTokens - 1) / kGFixTokens), (unsigned)n_groups),
+                     dim3(kGFixThreads), 0, st, params, x, (int)x_dtype, n_tok, x_tok_stride, codes,
+                     alpha, cap, pos);
+  return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
+}
+
 }  // namespace
 
 aatc_status launch_group_encode(const void* params, int n_groups, int gkv, const void* x,
@@ -1281,23 +1710,14 @@ aatc_status launch_group_encode(const void* params, int n_groups, int gkv, const
                                 void* stream) {
   if (n_tok == 0) return AATC_OK;
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t per_block = (int64_t)(kGThreads / 64) * kGTokensPerWave;
-  const int64_t blocks = (n_tok + per_block - 1) / per_block;
-  if (blocks > 0x7fffffff) return AATC_E_UNSUPPORTED;
-  const dim3 grid((unsigned)blocks, (unsigned)n_groups);
   auto* c8 = static_cast<uint8_t*>(codes);
-#define AATC_GENC(NC)                                                                     \
-  hipLaunchKernelGGL(group_encode_kernel<NC>, grid, dim3(kGThreads), 0, st, params, x,   \
-                     (int)x_dtype, n_tok, x_tok_stride, c8, alpha, cap, pos)
   switch (gkv) {
-    case 1: AATC_GENC(2); break;
-    case 2: AATC_GENC(4); break;
-    case 3: AATC_GENC(6); break;
-    case 4: AATC_GENC(8); break;
-    default: return AATC_E_UNSUPPORTED;
+    case 1: return launch_group_encode_nc<2>(params, n_groups, x, x_dtype, n_tok, x_tok_stride, c8, alpha, cap, pos, st);
+    case 2: return launch_group_encode_nc<4>(params, n_groups, x, x_dtype, n_tok, x_tok_stride, c8, alpha, cap, pos, st);
+    case 3: return launch_group_encode_nc<6>(params, n_groups, x, x_dtype, n_tok, x_tok_stride, c8, alpha, cap, pos, st);
+    case 4: return launch_group_encode_nc<8>(params, n_groups, x, x_dtype, n_tok, x_tok_stride, c8, alpha, cap, pos, st);
   }
-#undef AATC_GENC
-  return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
+  return AATC_E_UNSUPPORTED;
 }
 
 size_t group_decode_workspace_bytes(int batch, int n_q_heads, int n_kv_heads, int gkv,
