@@ -15,7 +15,7 @@
 //     query head of the group, the split's softmax and the transformed-domain value sums,
 //     on the matrix cores (fp16 operands) with the records staged in LDS; the VALU kernels
 //     group_split_wide_kernel and group_split_kernel (64-token chunks, an online softmax)
-//     take more query heads per group, wider codes, or records too long for LDS;
+//     take wider codes, or records too long for LDS;
 //   - group_merge_sum_kernel, group_merge_apply_kernel: per (sequence, query head) the merge
 //     of the split partials (by 64-channel chunks) and the inverse transform o = T[block] o~
 //     (by 32-row chunks).
@@ -605,6 +605,18 @@ struct GroupDecodeArgs {
   float* otl;                    // merged o~ per (sequence, query head)
 };
 
+// The fp16 operands and exponents of a head tile (16 query heads) of one (sequence, group).
+// The second tile (more than 16 heads) lies in the merged outputs' region, which is written
+// only after the split: 64 d bytes and 16 exponents of the 4 d heads >= 68 d bytes there.
+__device__ inline uint16_t* wop_tile(const GroupDecodeArgs& a, size_t gset, int d, int tile) {
+  return tile == 0 ? a.wop + gset * (d / 32) * (2 * 64 * 8)
+                   : reinterpret_cast<uint16_t*>(a.otl + gset * a.heads * d);
+}
+__device__ inline int32_t* wexp_tile(const GroupDecodeArgs& a, size_t gset, int d, int tile) {
+  return tile == 0 ? a.wexp + gset * 16
+                   : reinterpret_cast<int32_t*>(a.otl + gset * a.heads * d + 16 * d);
+}
+
 // One workgroup per (sequence, query head): W_c for the head's group channels.  Wave w of
 // sixteen sums the query against rows 8 w .. 8 w + 7 of the head's block of T (lane l:
 // channels l + 64 m, coalesced rows; every load of the wave in flight at once), and the
@@ -671,10 +683,10 @@ __global__ __launch_bounds__(kGQThreads) void group_query_kernel(GroupDecodeArgs
     for (int w = 0; w < NW; ++w) cs += red[w];
     a.cst[rowi] = cs;
   }
-  if (a.wops && hl < 16) {
+  if (a.wops) {
     // The matrix-core split's operands: W 2^e (largest |W| in [2^14, 2^15)) as fp16
-    // Wh + Wl, channel c of this head (slot hl) at block c / 32, lane 16 ((c % 32) / 8) + hl,
-    // element c % 8.
+    // Wh + Wl, channel c of this head (slot hl % 16 of head tile hl / 16) at block c / 32, lane
+    // 16 ((c % 32) / 8) + hl % 16, element c % 8.
     float m = redm[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) m = fmaxf(m, redm[w]);
@@ -682,15 +694,16 @@ __global__ __launch_bounds__(kGQThreads) void group_query_kernel(GroupDecodeArgs
     if (m > 0.f) (void)frexpf(m, &e);
     e = m > 0.f ? 15 - e : 0;
     const size_t gset = (size_t)b * a.n_groups + g;
-    if (tid == 0) a.wexp[gset * 16 + hl] = e;
+    uint16_t* wop = wop_tile(a, gset, D, hl >> 4);
+    if (tid == 0) wexp_tile(a, gset, D, hl >> 4)[hl & 15] = e;
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
       const int c = tid + kGQThreads * i;
       if (c < D) {
         const float w = ldexpf(wvs[i], e);
         const _Float16 wh = (_Float16)w, wl = (_Float16)(w - (float)wh);
-        const int l = 16 * ((c & 31) >> 3) + hl;
-        uint16_t* o = a.wop + (gset * (D / 32) + (c >> 5)) * (2 * 64 * 8);
+        const int l = 16 * ((c & 31) >> 3) + (hl & 15);
+        uint16_t* o = wop + (c >> 5) * (2 * 64 * 8);
         o[l * 8 + (c & 7)] = __builtin_bit_cast(uint16_t, wh);
         o[(64 + l) * 8 + (c & 7)] = __builtin_bit_cast(uint16_t, wl);
       }
@@ -1124,8 +1137,10 @@ __device__ inline void stage_records_any(uint32_t* rb, int rs, const uint32_t* s
   }
 }
 
-// The same split on the matrix cores (up to 16 query heads per group, codes of at most 12
-// bits, which fp16 holds exactly): eight waves, the records of all 256 tokens in LDS.
+// The same split on the matrix cores (up to 32 query heads per group in NHT tiles of 16, codes
+// of at most 12 bits, which fp16 holds exactly): eight waves, the records of all 256 tokens in
+// LDS.  The extraction of the codes bounds both product phases, so a second head tile costs
+// little (28 heads, batch 4 ragged to 8000 tokens: 136 us on the VALU before).
 //   - Scores: v_mfma_f32_16x16x32_f16 with A = the query weights (16 heads x 32 channels)
 //     and B = the codes of 16 tokens (32 channels x 16 tokens).  Each head's weights come
 //     scaled by a power of two (largest |W| in [2^14, 2^15)) and split into fp16 parts
@@ -1136,38 +1151,42 @@ __device__ inline void stage_records_any(uint32_t* rb, int rs, const uint32_t* s
 //     channels over those 32 tokens.  The midrise half step is 1/2 sum_t P, added once.
 // Operand layouts (lane 16 kg + n): A row n, k = 8 kg .. 8 kg + 7; B column n, the same k;
 // the 16 x 16 result row 4 kg + i, column n in element i.
-// DUAL: key and value records in LDS together, every load of the split issued at the start
-// (P then reuses the key rows); otherwise the value records replace the key records after
-// the scores.  A workgroup whose codes are wider takes the VALU body above (uniform).
+// DUAL: key and value records in LDS together; otherwise the value records replace the key
+// records after the scores, held in registers until then where their loads are vectors (every
+// load of the split is issued at the start either way).  P reuses the weight operands'
+// region.  A workgroup whose codes are wider takes the VALU body above (uniform).
 typedef _Float16 gh8 __attribute__((ext_vector_type(8)));
 typedef float gf4 __attribute__((ext_vector_type(4)));
 constexpr int kGPRow = kGSplit + 8;              // halves per head row of P (rows 4 banks
                                                  // apart: conflict-free operand reads)
-constexpr size_t kGPBytes = (size_t)2 * 16 * kGPRow * 2;
-constexpr size_t kGMfmaLdsCap = 144 * 1024;       // dynamic LDS of the matrix-core split
+constexpr size_t kGMfmaLdsCap = 150 * 1024;       // dynamic LDS of the matrix-core split
 
-template <int NC>
+// The weight operands, later P (both parts, 16 NHT head rows).
+template <int NC, int NHT>
+inline constexpr size_t kGWopBytes = std::max((size_t)NHT * (64 * NC / 32) * 2 * 64 * 16,
+                                              (size_t)2 * 16 * NHT * kGPRow * 2);
+template <int NC, int NHT>
 inline constexpr size_t group_mfma_lds(int rw_max, bool dual) {
   const size_t rows = (size_t)kGSplit * (rw_max + 1) * 4;
-  return (size_t)(64 * NC / 32) * 2 * 64 * 16 +               // weight operands
-         (size_t)2 * 64 * NC * 4 +                              // key and value descriptors
-         (dual ? std::max(rows, kGPBytes) + rows : rows + kGPBytes);
+  return kGWopBytes<NC, NHT> + (size_t)2 * 64 * NC * 4 +        // key and value descriptors
+         (dual ? 2 * rows : rows);
 }
 
-template <int NC, bool DUAL>
+template <int NC, int NHT, bool DUAL>
 __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDecodeArgs a) {
   constexpr int D = 64 * NC;
   constexpr int NT = kGWideThreads;
   constexpr int NKB = D / 32;                       // channel blocks of the score products
   constexpr int NCB = D / 16;                       // channel blocks of the value products
-  constexpr int W4 = NKB * 128 / NT;                // 16-byte operand loads per thread
+  constexpr int NQ = 16 * NHT;                      // head slots
+  constexpr int W4 = NKB * 128 / NT;                // 16-byte operand loads per thread and tile
   static_assert(kGSplit == 256, "eight waves of 32 tokens");
   static_assert(NKB * 128 % NT == 0, "whole operand loads");
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ float ak[kGSplit], av[kGSplit];
-  __shared__ float wred[8][16], wred2[8][16];
-  __shared__ float mh[16], lh[16], ph_sum[16], cst[16];
-  __shared__ int wexp[16];
+  __shared__ float wred[8][NQ], wred2[8][NQ];
+  __shared__ float mh[NQ], lh[NQ], ph_sum[NQ], cst[NQ];
+  __shared__ int wexp[NQ];
   __shared__ int pexp;
   const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
@@ -1178,7 +1197,7 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   const GroupParams* pk = group_params(a.params_k, g);
   const GroupParams* pv = group_params(a.params_v, g);
   if (pk->max_bits > 12 || pv->max_bits > 12) {
-    group_split_wide_body<NC, 16>(a);
+    group_split_wide_body<NC, NQ>(a);
     return;
   }
   const int nt = min(len, s0 + kGSplit) - s0;
@@ -1190,15 +1209,12 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   }
   const int rs = max(rwk, rwv) + 1;                 // LDS row stride (one padding dword)
   const size_t rows_b = (size_t)kGSplit * rs * 4;
-  gh8* wop = reinterpret_cast<gh8*>(smem);                                  // [NKB][2][64]
-  uint32_t* kdesc = reinterpret_cast<uint32_t*>(wop + NKB * 2 * 64);        // [D]: off | b << 16
+  gh8* wop = reinterpret_cast<gh8*>(smem);                                  // [NHT][NKB][2][64]
+  _Float16* pl = reinterpret_cast<_Float16*>(smem);                         // [2][NQ][kGPRow]
+  uint32_t* kdesc = reinterpret_cast<uint32_t*>(smem + kGWopBytes<NC, NHT>);   // [D]: off | b << 16
   uint32_t* vdesc = kdesc + D;
   uint32_t* rbk = vdesc + D;                                                // [kGSplit][rs]
-  uint32_t* rbv = DUAL ? reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(rbk) +
-                                                     std::max(rows_b, kGPBytes))
-                       : rbk;
-  _Float16* pl = DUAL ? reinterpret_cast<_Float16*>(rbk)                    // [2][16][kGPRow]
-                      : reinterpret_cast<_Float16*>(reinterpret_cast<uint8_t*>(rbk) + rows_b);
+  uint32_t* rbv = DUAL ? rbk + rows_b / 4 : rbk;
   const size_t gset = (size_t)b * a.n_groups + g;
   const size_t row0 = gset * a.heads;
   const size_t tok0 = gset * (size_t)a.cap + s0;
@@ -1207,28 +1223,40 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   // (1) Every load first: the weight operands, the records (the first pass of each, 16-byte
   //     loads where the records are aligned), the scales, descriptors and constants; then
   //     the stores.
+  const int totk = nt * rwk, totv = nt * rwv;
+  const bool vec = ((reinterpret_cast<uintptr_t>(kw) | reinterpret_cast<uintptr_t>(vw)) & 15u) == 0u &&
+                   totk >= 4 && totv >= 4 && totk <= 4 * NT * kGStage4 && totv <= 4 * NT * kGStage4;
+  uint4 vv[kGStage4];                               // (vec: the value records until stored)
+  uint32_t tv = 0u;
   auto stage_all = [&]() {
-    const uint4* wsrc = reinterpret_cast<const uint4*>(a.wop) + gset * (NKB * 128);
-    uint4 wv4[W4];
-    const int totk = nt * rwk, totv = nt * rwv;
-    const bool vec = ((reinterpret_cast<uintptr_t>(kw) | reinterpret_cast<uintptr_t>(vw)) & 15u) == 0u &&
-                     totk >= 4 && totv >= 4 && totk <= 4 * NT * kGStage4 && totv <= 4 * NT * kGStage4;
-    if (DUAL && vec) {                              // (uniform; no branch among the loads)
-      uint4 vk[kGStage4], vv[kGStage4];
-      uint32_t tk, tv;
+    uint4 wv4[NHT][W4];
+    auto load_w = [&]() {
 #pragma unroll
-      for (int i = 0; i < W4; ++i) wv4[i] = wsrc[tid + NT * i];
+      for (int ht = 0; ht < NHT; ++ht) {
+        const uint4* wsrc = reinterpret_cast<const uint4*>(wop_tile(a, gset, D, ht));
+#pragma unroll
+        for (int i = 0; i < W4; ++i) wv4[ht][i] = wsrc[tid + NT * i];
+      }
+    };
+    auto store_w = [&]() {
+#pragma unroll
+      for (int ht = 0; ht < NHT; ++ht)
+#pragma unroll
+        for (int i = 0; i < W4; ++i)
+          reinterpret_cast<uint4*>(wop)[ht * NKB * 128 + tid + NT * i] = wv4[ht][i];
+    };
+    if (vec) {                                      // (uniform; no branch among the loads)
+      uint4 vk[kGStage4];
+      uint32_t tk;
+      load_w();
       stage4_load<NT>(kw, totk, tid, vk, tk);
       stage4_load<NT>(vw, totv, tid, vv, tv);
-#pragma unroll
-      for (int i = 0; i < W4; ++i) reinterpret_cast<uint4*>(wop)[tid + NT * i] = wv4[i];
+      store_w();
       stage4_store<NT>(rbk, rs, totk, rwk, tid, vk, tk, true);
-      stage4_store<NT>(rbv, rs, totv, rwv, tid, vv, tv, true);
+      if constexpr (DUAL) stage4_store<NT>(rbv, rs, totv, rwv, tid, vv, tv, true);
     } else {
-#pragma unroll
-      for (int i = 0; i < W4; ++i) wv4[i] = wsrc[tid + NT * i];
-#pragma unroll
-      for (int i = 0; i < W4; ++i) reinterpret_cast<uint4*>(wop)[tid + NT * i] = wv4[i];
+      load_w();
+      store_w();
       stage_records_any<NT>(rbk, rs, kw, nt, rwk);
       if constexpr (DUAL) stage_records_any<NT>(rbv, rs, vw, nt, rwv);
     }
@@ -1247,9 +1275,9 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
     }
     const int ti = min(tid, nt - 1);
     const uint16_t ka16 = a.k_alpha[tok0 + ti], va16 = a.v_alpha[tok0 + ti];
-    const int hi = min(tid & 15, a.heads - 1);
+    const int hi = min(tid & (NQ - 1), a.heads - 1);
     const float cst_v = a.cst[row0 + hi];
-    const int wexp_v = a.wexp[gset * 16 + hi];
+    const int wexp_v = wexp_tile(a, gset, D, hi >> 4)[hi & 15];
     stage_all();
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
@@ -1266,7 +1294,7 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
       ak[tid] = tid < nt ? __half2float(__ushort_as_half(ka16)) : 0.f;
       av[tid] = tid < nt ? __half2float(__ushort_as_half(va16)) : 0.f;
     }
-    if (tid < 16) {
+    if (tid < NQ) {
       cst[tid] = tid < a.heads ? cst_v : 0.f;
       wexp[tid] = tid < a.heads ? wexp_v : 0;
     }
@@ -1277,7 +1305,7 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
     const float m = g_wave_max(av[tid]);
     if (lane == 0) wred2[wave][0] = m;
   }
-  // (2) Scores of tokens 32 wave + 16 tb + n, heads 4 kg + i (slots past the group's heads
+  // (2) Scores of tokens 32 wave + 16 tb + n, heads 16 ht + 4 kg + i (slots past the group's heads
   //     hold other data: their operand rows are zeroed).
   // (the extract is made for every channel and a dropped one, width 0, selected to 0:
   // no branch around the LDS reads)
@@ -1286,15 +1314,19 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
     const int code = record_code(row, (int)(dsc & 0xffffu), bw);
     return (_Float16)(float)(bw ? code : 0);
   };
-  const bool head_ok = n < a.heads;
-  gf4 zs[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  gf4 zs[NHT][2] = {};
   {
     const uint32_t* krow[2] = {rbk + (32 * wave + n) * rs, rbk + (32 * wave + 16 + n) * rs};
     const gh8 zero8 = {};
 #pragma unroll 2
     for (int kb = 0; kb < NKB; ++kb) {
-      const gh8 whi = head_ok ? wop[(2 * kb) * 64 + lane] : zero8;
-      const gh8 wlo = head_ok ? wop[(2 * kb + 1) * 64 + lane] : zero8;
+      gh8 whi[NHT], wlo[NHT];
+#pragma unroll
+      for (int ht = 0; ht < NHT; ++ht) {
+        const bool head_ok = 16 * ht + n < a.heads;
+        whi[ht] = head_ok ? wop[(ht * NKB + kb) * 128 + lane] : zero8;
+        wlo[ht] = head_ok ? wop[(ht * NKB + kb) * 128 + 64 + lane] : zero8;
+      }
       const int c0 = 32 * kb + 8 * kg;
       const uint4 d0 = *reinterpret_cast<const uint4*>(kdesc + c0);
       const uint4 d1 = *reinterpret_cast<const uint4*>(kdesc + c0 + 4);
@@ -1304,28 +1336,31 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
         gh8 cb;
 #pragma unroll
         for (int e = 0; e < 8; ++e) cb[e] = code_of(krow[tb], dk[e]);
-        zs[tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(whi, cb, zs[tb], 0, 0, 0);
-        zs[tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wlo, cb, zs[tb], 0, 0, 0);
+#pragma unroll
+        for (int ht = 0; ht < NHT; ++ht) {
+          zs[ht][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(whi[ht], cb, zs[ht][tb], 0, 0, 0);
+          zs[ht][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wlo[ht], cb, zs[ht][tb], 0, 0, 0);
+        }
       }
     }
   }
-  float z[2][4];
+  float z[NHT][2][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int h = 4 * kg + i;
+  for (int hi = 0; hi < 4 * NHT; ++hi) {
+    const int ht = hi >> 2, i = hi & 3, h = 16 * ht + 4 * kg + i;
     float m = -INFINITY;
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
       const int t = 32 * wave + 16 * tb + n;
-      z[tb][i] = t < nt ? ak[t] * (ldexpf(zs[tb][i], -wexp[h]) + cst[h]) : -INFINITY;
-      m = fmaxf(m, z[tb][i]);
+      z[ht][tb][i] = t < nt ? ak[t] * (ldexpf(zs[ht][tb][i], -wexp[h]) + cst[h]) : -INFINITY;
+      m = fmaxf(m, z[ht][tb][i]);
     }
 #pragma unroll
     for (int o = 8; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if (n == 0) wred[wave][h] = m;
   }
   __syncthreads();                                  // (every key record read, maxima in)
-  if (tid < 16) {
+  if (tid < NQ) {
     float m = wred[0][tid];
 #pragma unroll
     for (int w = 1; w < 8; ++w) m = fmaxf(m, wred[w][tid]);
@@ -1338,7 +1373,8 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
     pexp = m > 0.f ? 14 - e : 0;                    // max alpha^V 2^pexp in [2^13, 2^14)
   }
   if constexpr (!DUAL) {
-    stage_records_any<NT>(rbv, rs, vw, nt, rwv);
+    if (vec) stage4_store<NT>(rbv, rs, totv, rwv, tid, vv, tv, true);
+    else stage_records_any<NT>(rbv, rs, vw, nt, rwv);
     if (tid < kGSplit) rbv[tid * rs + rwv] = 0u;
   }
   __syncthreads();
@@ -1347,20 +1383,20 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   {
     const int pe = pexp;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int h = 4 * kg + i;
+    for (int hi = 0; hi < 4 * NHT; ++hi) {
+      const int ht = hi >> 2, i = hi & 3, h = 16 * ht + 4 * kg + i;
       float ps = 0.f, qs = 0.f;
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         const int t = 32 * wave + 16 * tb + n;
-        const float p = t < nt ? __builtin_amdgcn_exp2f(z[tb][i] - mh[h]) : 0.f;
+        const float p = t < nt ? __builtin_amdgcn_exp2f(z[ht][tb][i] - mh[h]) : 0.f;
         const float pv_ = p * av[t];
         ps += p;
         qs += pv_;
         const float sp = ldexpf(pv_, pe);
         const _Float16 hh = (_Float16)sp;
         pl[h * kGPRow + t] = hh;
-        pl[(16 + h) * kGPRow + t] = (_Float16)(sp - (float)hh);
+        pl[(NQ + h) * kGPRow + t] = (_Float16)(sp - (float)hh);
       }
 #pragma unroll
       for (int o = 8; o >= 1; o >>= 1) {
@@ -1374,7 +1410,7 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
     }
   }
   __syncthreads();
-  if (tid < 16) {
+  if (tid < NQ) {
     float ps = 0.f, qs = 0.f;
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
@@ -1386,31 +1422,34 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   }
   __syncthreads();
   // (4) Values: wave w takes channel blocks w, w + 8, ...; lane 16 kg + n ends with heads
-  //     4 kg + i of channel 16 cb + n.
+  //     16 ht + 4 kg + i of channel 16 cb + n.
   const bool mr_v = pv->quantizer == AATC_QUANT_MIDRISE;
   const int pe = pexp;
   for (int cb = wave; cb < NCB; cb += 8) {
     const int c = 16 * cb + n;
     const uint32_t dsc = vdesc[c];
-    gf4 acc = {0.f, 0.f, 0.f, 0.f};
+    gf4 acc[NHT] = {};
 #pragma unroll 2
     for (int tk = 0; tk < kGSplit / 32; ++tk) {
       const int t0 = 32 * tk + 8 * kg;
-      const gh8 phi = *reinterpret_cast<const gh8*>(pl + n * kGPRow + t0);
-      const gh8 plo = *reinterpret_cast<const gh8*>(pl + (16 + n) * kGPRow + t0);
       gh8 cv;
 #pragma unroll
       for (int e = 0; e < 8; ++e) cv[e] = code_of(rbv + (t0 + e) * rs, dsc);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(phi, cv, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(plo, cv, acc, 0, 0, 0);
+#pragma unroll
+      for (int ht = 0; ht < NHT; ++ht) {
+        const gh8 phi = *reinterpret_cast<const gh8*>(pl + (16 * ht + n) * kGPRow + t0);
+        const gh8 plo = *reinterpret_cast<const gh8*>(pl + (NQ + 16 * ht + n) * kGPRow + t0);
+        acc[ht] = __builtin_amdgcn_mfma_f32_16x16x32_f16(phi, cv, acc[ht], 0, 0, 0);
+        acc[ht] = __builtin_amdgcn_mfma_f32_16x16x32_f16(plo, cv, acc[ht], 0, 0, 0);
+      }
     }
     const int bc = (int)(dsc >> 16);
     const float sc = bc > 0 ? ldexpf(pv->s[c], 1 - bc) : 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int h = 4 * kg + i;
+    for (int hi = 0; hi < 4 * NHT; ++hi) {
+      const int h = 16 * (hi >> 2) + 4 * kg + (hi & 3);
       if (h < a.heads) {
-        const float o = ldexpf(acc[i], -pe) + (mr_v ? 0.5f * ph_sum[h] : 0.f);
+        const float o = ldexpf(acc[hi >> 2][hi & 3], -pe) + (mr_v ? 0.5f * ph_sum[h] : 0.f);
         pbase[(size_t)h * (D + kGPH) + kGPH + c] = o * sc;
       }
     }
@@ -1571,18 +1610,26 @@ struct GroupLds {
 };
 
 // Whether the matrix-core split fits (its LDS, and that of the VALU body it falls back to
-// for codes over 12 bits, with 16 head slots); *lds gets the size, and the result is true
+// for codes over 12 bits, with 16 NHT head slots); *lds gets the size, and the result is true
 // when both record sets fit at once (DUAL).
-template <int NC>
+template <int NC, int NHT>
 bool group_mfma_fit(int rwk, int rwv, size_t* lds) {
-  constexpr int D = 64 * NC;
+  constexpr int D = 64 * NC, NQ = 16 * NHT;
   const int rwm = std::max(rwk, rwv);
-  const size_t w16 = sizeof(float) * (size_t)D * 16 + sizeof(uint32_t) * (size_t)kGSplit * (rwm + 1) +
-                     sizeof(float) * (size_t)kGSplit * 16 + sizeof(uint32_t) * D;
-  const size_t m2 = std::max(w16, group_mfma_lds<NC>(rwm, true));
-  const size_t m1 = std::max(w16, group_mfma_lds<NC>(rwm, false));
+  const size_t wide = sizeof(float) * (size_t)D * NQ + sizeof(uint32_t) * (size_t)kGSplit * (rwm + 1) +
+                      sizeof(float) * (size_t)kGSplit * NQ + sizeof(uint32_t) * D;
+  const size_t m2 = std::max(wide, group_mfma_lds<NC, NHT>(rwm, true));
+  const size_t m1 = std::max(wide, group_mfma_lds<NC, NHT>(rwm, false));
   *lds = m2 <= kGMfmaLdsCap ? m2 : m1 <= kGMfmaLdsCap ? m1 : 0;
   return m2 <= kGMfmaLdsCap;
+}
+
+template <int NC, int NHT, bool DUAL>
+aatc_status launch_split_mfma(const GroupDecodeArgs& a, dim3 grid, size_t lds, hipStream_t st) {
+  static GroupLds limit;
+  if (!limit.ensure((const void*)group_split_mfma_kernel<NC, NHT, DUAL>, lds)) return AATC_E_DEVICE;
+  hipLaunchKernelGGL((group_split_mfma_kernel<NC, NHT, DUAL>), grid, dim3(kGWideThreads), lds, st, a);
+  return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
 }
 
 template <int NC, int NQ>
@@ -1593,25 +1640,11 @@ aatc_status launch_split(const GroupDecodeArgs& a, int batch, int rwk, int rwv,
                           sizeof(uint32_t) * (size_t)kGSplit * (std::max(rwk, rwv) + 1) +
                           sizeof(float) * (size_t)kGSplit * NQ + sizeof(uint32_t) * D;
   const dim3 grid((unsigned)a.n_splits, (unsigned)a.n_groups, (unsigned)batch);
-  if constexpr (NQ <= 16) {
-    if (a.wops) {
-      size_t lds = 0;
-      const bool dual = group_mfma_fit<NC>(rwk, rwv, &lds);
-      if (dual) {
-        static GroupLds limit_m2;
-        if (!limit_m2.ensure((const void*)group_split_mfma_kernel<NC, true>, lds))
-          return AATC_E_DEVICE;
-        hipLaunchKernelGGL((group_split_mfma_kernel<NC, true>), grid, dim3(kGWideThreads), lds,
-                           st, a);
-      } else {
-        static GroupLds limit_m1;
-        if (!limit_m1.ensure((const void*)group_split_mfma_kernel<NC, false>, lds))
-          return AATC_E_DEVICE;
-        hipLaunchKernelGGL((group_split_mfma_kernel<NC, false>), grid, dim3(kGWideThreads), lds,
-                           st, a);
-      }
-      return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
-    }
+  if (a.wops) {
+    constexpr int NHT = NQ <= 16 ? 1 : 2;
+    size_t lds = 0;
+    if (group_mfma_fit<NC, NHT>(rwk, rwv, &lds)) return launch_split_mfma<NC, NHT, true>(a, grid, lds, st);
+    return launch_split_mfma<NC, NHT, false>(a, grid, lds, st);
   }
   if (lds_wide <= 144 * 1024) {
     static GroupLds limit_wide;
@@ -1636,8 +1669,9 @@ aatc_status launch_split(const GroupDecodeArgs& a, int batch, int rwk, int rwv,
 template <int NC>
 aatc_status launch_decode_nc(GroupDecodeArgs a, int batch, int rwk, int rwv, hipStream_t st) {
   size_t lds_m = 0;
-  (void)group_mfma_fit<NC>(rwk, rwv, &lds_m);
-  a.wops = a.heads <= 16 && lds_m > 0 ? 1 : 0;      // the query kernel writes the operands
+  if (a.heads <= 16) (void)group_mfma_fit<NC, 1>(rwk, rwv, &lds_m);
+  else (void)group_mfma_fit<NC, 2>(rwk, rwv, &lds_m);
+  a.wops = lds_m > 0 ? 1 : 0;                       // the query kernel writes the operands
   hipLaunchKernelGGL((group_query_kernel<NC>), dim3((unsigned)a.n_q_heads, (unsigned)batch),
                      dim3(kGQThreads), 0, st, a);
   if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
