@@ -58,9 +58,9 @@ inline const GroupParams* group_params(const void* block, int g) {
 
 // Decode workspace under head groups, per call: the query weights W [batch][n_groups]
 // [heads][d], the midrise constants [batch][n_groups][heads], the split partials
-// [batch][n_groups][n_splits][heads][kGPH + d] (m, l, unused to a 128-byte header, o~[d]:
-// every o~ row starts on a 128-byte line), then for the
-// matrix-core split the weights as fp16 operands [batch][n_groups][d / 32][hi, lo][64 lanes]
+// [batch][n_groups][n_splits][heads][kGPH + d] (m, l, the merge's arrival count, unused to a
+// 128-byte header, o~[d]: every o~ row starts on a 128-byte line), then for the matrix-core
+// split the weights as fp16 operands [batch][n_groups][d / 32][hi, lo][64 lanes]
 // [8] (16 head slots) and their per-head power-of-two exponents [batch][n_groups][16], then
 // the merged transformed-domain outputs o~ [batch][n_groups * heads][d].
 constexpr int kGSplit = 256;                 // tokens per decode split

@@ -16,9 +16,8 @@
 //     on the matrix cores (fp16 operands) with the records staged in LDS; the VALU kernels
 //     group_split_wide_kernel and group_split_kernel (64-token chunks, an online softmax)
 //     take wider codes, or records too long for LDS;
-//   - group_merge_sum_kernel, group_merge_apply_kernel: per (sequence, query head) the merge
-//     of the split partials (by 64-channel chunks) and the inverse transform o = T[block] o~
-//     (by 32-row chunks).
+//   - group_merge_kernel: per (sequence, query head) the merge of the split partials and the
+//     inverse transform o = T[block] o~, by 64-channel chunks.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -617,6 +616,14 @@ __device__ inline int32_t* wexp_tile(const GroupDecodeArgs& a, size_t gset, int 
                    : reinterpret_cast<int32_t*>(a.otl + gset * a.heads * d + 16 * d);
 }
 
+// The split partial row of (split 0, head), and the merge's arrival count in its header.
+__device__ inline float* first_partial_row(const GroupDecodeArgs& a, size_t gset, int hl, int d) {
+  return a.part + (gset * a.n_splits * a.heads + hl) * (size_t)(d + kGPH);
+}
+__device__ inline unsigned* merge_count(const GroupDecodeArgs& a, size_t gset, int hl, int d) {
+  return reinterpret_cast<unsigned*>(first_partial_row(a, gset, hl, d)) + 2;
+}
+
 // One workgroup per (sequence, query head): W_c for the head's group channels.  Wave w of
 // sixteen sums the query against rows 8 w .. 8 w + 7 of the head's block of T (lane l:
 // channels l + 64 m, coalesced rows; every load of the wave in flight at once), and the
@@ -682,6 +689,7 @@ __global__ __launch_bounds__(kGQThreads) void group_query_kernel(GroupDecodeArgs
 #pragma unroll
     for (int w = 0; w < NW; ++w) cs += red[w];
     a.cst[rowi] = cs;
+    *merge_count(a, (size_t)b * a.n_groups + g, hl, D) = 0u;
   }
   if (a.wops) {
     // The matrix-core split's operands: W 2^e (largest |W| in [2^14, 2^15)) as fp16
@@ -1460,41 +1468,58 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
   }
 }
 
-// The merge in two launches, spread over (query head, channel chunk) and (query head,
-// output rows) so that every CU reads a share of the split partials and of T_V.
-// group_merge_sum_kernel: one workgroup per (sequence, query head, 64 channels of o~): the
-// splits' maximum M and weights 2^(m_s - M) (recomputed by every chunk: a few hundred
-// floats), thread (range, channel) sums one quarter of the splits with eight loads in
-// flight, and o~ = sum_s w_s o~_s / sum_s w_s l_s goes to the workspace (NaN if a split
-// reported mismatched records, 0 for an empty sequence).
+// The merge: one workgroup per (sequence, query head, 64 channels of o~), so that every compute
+// unit reads a share of the split partials and of T_V.  Every chunk recomputes the splits'
+// maximum M and weights 2^(m_s - M) (a few hundred floats); thread (range, channel) sums one
+// quarter of the splits with eight loads in flight; o~ = sum_s w_s o~_s / sum_s w_s l_s (NaN if
+// a split reported mismatched records, 0 for an empty sequence).  The chunk's share of the
+// inverse transform, sum over its channels of T_V[128 kk + j][c] o~_c (its part of T_V loaded at
+// the start), goes out with device-coherent stores, and the last chunk of a head to arrive
+// adds the shares in order.  (Coherent accesses and a relaxed count need no cache write-back: a
+// release before each arrival had made this 31 us.  Two launches, sums then transform, took
+// 5.8 + 5.8 us, 6.0 + 9.6 for 112 heads.)
+// A share's 128 outputs lie in the chunk's 64 floats of the head's rows of the o~ and of the
+// weight region (read last by the split kernel, so no line of theirs is cached here); the
+// arrival count in the header of the head's first partial row, cleared by the query kernel.
 constexpr int kGMergeThreads = 256;
 constexpr int kGMergeSplits = 1024;              // splits weighted per pass
 template <int NC>
-__global__ __launch_bounds__(kGMergeThreads) void group_merge_sum_kernel(GroupDecodeArgs a) {
+__global__ __launch_bounds__(kGMergeThreads) void group_merge_kernel(GroupDecodeArgs a) {
   constexpr int D = 64 * NC;
   constexpr int NT = kGMergeThreads;
   constexpr int NSUB = NT / 64;                    // split ranges per channel
   constexpr int NW = NT / 64;
   __shared__ float ot[NSUB][64];
+  __shared__ __align__(16) float oc[64];
   __shared__ float wsp[kGMergeSplits];
   __shared__ float red[NW];
+  __shared__ int last_s;
   const int h = blockIdx.x / NC, ci = blockIdx.x % NC, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int gq = a.n_q_heads / a.n_kv_heads;
-  const int k = h / gq, g = k / a.gkv, hl = h - g * a.heads;
-  float* otw = a.otl + ((size_t)b * a.n_q_heads + h) * D + 64 * ci;
+  const int k = h / gq, g = k / a.gkv, kk = k % a.gkv, hl = h - g * a.heads;
+  // Row j = tid / 2 of the head's block of T_V, half of the chunk's columns.
+  float4 tv[8];
+  {
+    const float4* tr = reinterpret_cast<const float4*>(
+        group_params(a.params_v, g)->T + (size_t)(kk * 128 + (tid >> 1)) * D + 64 * ci + 32 * (tid & 1));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) tv[q] = tr[q];
+  }
+  float* out = a.out + ((int64_t)b * a.n_q_heads + h) * 128;
   const int len = (int)min((int64_t)max(a.seq_len[b], 0), a.cap);
-  if (len == 0) {
-    if (tid < 64) otw[tid] = 0.f;
+  if (len == 0) {                                  // (uniform over the head's workgroups)
+    if (ci == 0 && tid < 128) out[tid] = 0.f;
     return;
   }
   const int ns = (len + kGSplit - 1) / kGSplit;
-  const float* pb = a.part + ((((size_t)b * a.n_groups + g) * a.n_splits) * a.heads + hl) * (D + kGPH);
+  const size_t gset = (size_t)b * a.n_groups + g;
+  float* pb = first_partial_row(a, gset, hl, D);
   const size_t sstride = (size_t)a.heads * (D + kGPH);
   float mx = -INFINITY;
   for (int s = tid; s < ns; s += NT) {
     const float ms = pb[s * sstride];
-    mx = ms != ms ? ms : fmaxf(mx, ms);             // (a NaN mark is kept)
+    mx = (mx != mx || ms != ms) ? NAN : fmaxf(mx, ms);   // (a NaN mark is kept)
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -1505,8 +1530,8 @@ __global__ __launch_bounds__(kGMergeThreads) void group_merge_sum_kernel(GroupDe
   __syncthreads();
   float M = red[0];
   for (int w = 1; w < NW; ++w) M = (M != M || red[w] != red[w]) ? NAN : fmaxf(M, red[w]);
-  if (M != M) {
-    if (tid < 64) otw[tid] = NAN;
+  if (M != M) {                                    // (uniform over the head's workgroups)
+    if (ci == 0 && tid < 128) out[tid] = NAN;
     return;
   }
   const int c = tid & 63, sub = tid >> 6;
@@ -1549,43 +1574,38 @@ __global__ __launch_bounds__(kGMergeThreads) void group_merge_sum_kernel(GroupDe
     float v = 0.f;
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) v += ot[u][tid];
-    otw[tid] = v * (L > 0.f ? 1.f / L : 0.f);
+    oc[tid] = v * (L > 0.f ? 1.f / L : 0.f);
   }
-}
-
-// group_merge_apply_kernel: one workgroup per (sequence, query head, 32 output rows):
-// o_j = sum_c T_V[128 kk + j][c] o~_c, thread (row, part) over D / 8 consecutive channels
-// (every load of its slice in flight at once), the eight parts met by shuffles.
-constexpr int kGApplyRows = 32;
-template <int NC>
-__global__ __launch_bounds__(256) void group_merge_apply_kernel(GroupDecodeArgs a) {
-  constexpr int D = 64 * NC;
-  constexpr int PC = D / 8;                         // channels per part (a multiple of 16)
-  const int h = blockIdx.x / (128 / kGApplyRows), jq = blockIdx.x % (128 / kGApplyRows);
-  const int b = blockIdx.y, tid = threadIdx.x;
-  const int gq = a.n_q_heads / a.n_kv_heads;
-  const int k = h / gq, g = k / a.gkv, kk = k % a.gkv;
-  const int j = kGApplyRows * jq + (tid >> 3), part = tid & 7;
-  const GroupParams* pv = group_params(a.params_v, g);
-  const float4* trow = reinterpret_cast<const float4*>(pv->T + (size_t)(kk * 128 + j) * D + part * PC);
-  const float4* ov = reinterpret_cast<const float4*>(a.otl + ((size_t)b * a.n_q_heads + h) * D + part * PC);
-  float4 tv[PC / 4], o4[PC / 4];
+  __syncthreads();
+  float o = 0.f;
 #pragma unroll
-  for (int q = 0; q < PC / 4; ++q) {
-    tv[q] = trow[q];
-    o4[q] = ov[q];
+  for (int q = 0; q < 8; ++q) {
+    const float4 x = *reinterpret_cast<const float4*>(&oc[32 * (tid & 1) + 4 * q]);
+    o = fmaf(tv[q].x, x.x, o);
+    o = fmaf(tv[q].y, x.y, o);
+    o = fmaf(tv[q].z, x.z, o);
+    o = fmaf(tv[q].w, x.w, o);
   }
-  float v = 0.f;
+  o += __shfl_xor(o, 1, 64);
+  const size_t row = ((size_t)b * a.n_q_heads + h) * D;
+  auto share = [&](int x, int j) { return (j < 64 ? a.otl : a.w) + row + 64 * x + (j & 63); };
+  if ((tid & 1) == 0)
+    __hip_atomic_store(share(ci, tid >> 1), o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_s_waitcnt(0);                    // this thread's store has completed
+  __syncthreads();
+  if (tid == 0)
+    last_s = __hip_atomic_fetch_add(merge_count(a, gset, hl, D), 1u, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(NC - 1);
+  __syncthreads();
+  if (!last_s || tid >= 128) return;
+  float v[NC];
 #pragma unroll
-  for (int q = 0; q < PC / 4; ++q) {
-    v = fmaf(tv[q].x, o4[q].x, v);
-    v = fmaf(tv[q].y, o4[q].y, v);
-    v = fmaf(tv[q].z, o4[q].z, v);
-    v = fmaf(tv[q].w, o4[q].w, v);
-  }
+  for (int x = 0; x < NC; ++x)
+    v[x] = __hip_atomic_load(share(x, tid), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float r = v[0];
 #pragma unroll
-  for (int o = 4; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  if (part == 0) a.out[((int64_t)b * a.n_q_heads + h) * 128 + j] = v;
+  for (int x = 1; x < NC; ++x) r += v[x];
+  out[tid] = r;
 }
 
 // The dynamic LDS limit of one kernel on the current device, raised once per device when a
@@ -1681,13 +1701,8 @@ aatc_status launch_decode_nc(GroupDecodeArgs a, int batch, int rwk, int rwv, hip
   else if (a.heads <= 16) s = launch_split<NC, 16>(a, batch, rwk, rwv, st);
   else s = launch_split<NC, 32>(a, batch, rwk, rwv, st);
   if (s != AATC_OK) return s;
-  hipLaunchKernelGGL((group_merge_sum_kernel<NC>),
-                     dim3((unsigned)(a.n_q_heads * NC), (unsigned)batch), dim3(kGMergeThreads), 0,
-                     st, a);
-  if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
-  hipLaunchKernelGGL((group_merge_apply_kernel<NC>),
-                     dim3((unsigned)(a.n_q_heads * (128 / kGApplyRows)), (unsigned)batch),
-                     dim3(256), 0, st, a);
+  hipLaunchKernelGGL((group_merge_kernel<NC>), dim3((unsigned)(a.n_q_heads * NC), (unsigned)batch),
+                     dim3(kGMergeThreads), 0, st, a);
   return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
 }
 
