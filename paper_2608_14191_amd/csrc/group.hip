@@ -436,17 +436,17 @@ void group_encode_mfma_kernel(const void* __restrict__ params, const void* __res
 // the exact products x_j T_jc, exact while |x|_1 stays below 2^(31 + g) (every product, hence
 // every partial sum, is a multiple of 2^(g - 22), g the lowest set bit of the token's elements,
 // and |T| <= 1); otherwise an interval test, and the exact accumulator where the interval
-// straddles an fp32 rounding boundary.  A workgroup scans kGFixTokens marks and takes its
+// straddles an fp32 rounding boundary.  A workgroup scans `share` marks and takes its
 // marked tokens one at a time: thread (part, channel) sums a share of the elements (rows of T
 // coalesced over the channels, sixteen in flight), the shares meet in LDS.  (A wave per token
 // walked 512 rows in sequence, over 100 us.)
 constexpr int kGFixThreads = 1024;
-constexpr int kGFixTokens = 64;
+constexpr int kGFixTokens = 64;                    // most marks of a workgroup
 template <int NC>
 __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int dtype, int64_t n_tok,
     int64_t x_stride, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha, int64_t cap,
-    int64_t pos) {
+    int64_t pos, int share) {
   constexpr int D = 64 * NC;
   constexpr int NP = kGFixThreads / D;              // element shares
   constexpr int JP = (D + NP - 1) / NP;             // elements per share
@@ -464,10 +464,10 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const GroupParams* gp = group_params(params, g);
-  const int64_t base = (int64_t)blockIdx.x * kGFixTokens;
+  const int64_t base = (int64_t)blockIdx.x * share;
   if (tid == 0) n_list = 0;
   __syncthreads();
-  if (tid < kGFixTokens && base + tid < n_tok &&
+  if (tid < share && base + tid < n_tok &&
       alpha[(int64_t)g * cap + pos + base + tid] == kGRedo)
     list[atomicAdd(&n_list, 1)] = (uint16_t)tid;
   __syncthreads();
@@ -477,11 +477,17 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
   for (int li = 0; li < cnt; ++li) {
     const int64_t t = base + list[li];
     const void* xrow = static_cast<const char*>(x) + (t * x_stride + (int64_t)g * D) * esize;
-    // The token, its lowest set bit (4096 for a zero token) and |x|_1.
+    // The token, its lowest set bit (4096 for a zero token) and |x|_1; the channel's table
+    // entries, so that no load is left after the sums.
     int glsb = 4096;
     float l1 = 0.f;
+    int b = 0, off = 0;
+    float is = 0.f;
     if (tid < D) {
       const float xe = load_elem(xrow, dtype, tid);
+      b = gp->bits[tid];
+      off = gp->bit_off[tid];
+      is = gp->inv_s[tid];
       xs[tid] = xe;
       l1 = fabsf(xe);
       const uint32_t bv = __float_as_uint(xe) & 0x7fffffffu;
@@ -520,7 +526,6 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
     }
     __syncthreads();
     float h = 0.f;
-    int b = 0;
     bool open = false;                              // not decided by the interval
     if (tid < D) {
       double sv = part[0][tid];
@@ -530,7 +535,6 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
       for (int w = 1; w < kGFixThreads / 64; ++w) l1 += redl[w];
       // The float sum l1 is within 2^-14 relative of |x|_1.
       const double l1d = (double)l1 * (1.0 + 0x1p-14);
-      b = gp->bits[tid];
       h = (float)sv;
       if (!(l1d < ldexp(1.0, 31 + min(glsb_s, 900)))) {
         // fp64 sum of D exact products: |error| <= D 2^-53 sum |p| <= D 2^-53 |x|_1
@@ -555,7 +559,7 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
     }
     __syncthreads();
     if (open) h = hx[tid];
-    const float r = tid < D ? h * gp->inv_s[tid] : 0.f;
+    const float r = h * is;
     const float m = g_wave_max(b > 0 ? fabsf(r) : 0.f);
     if (lane == 0) red[wave] = m;
     __syncthreads();
@@ -564,7 +568,6 @@ __global__ __launch_bounds__(kGFixThreads) void group_encode_exact_kernel(
     const __half a16 = token_alpha(am);
     if (b > 0) {
       const uint32_t q = quantize_code(r, inverse_alpha(a16), b, gp->quantizer == AATC_QUANT_MIDRISE);
-      const int off = gp->bit_off[tid];
       atomicOr(&row[off >> 5], q << (off & 31));
       if ((off & 31) + b > 32) atomicOr(&row[(off >> 5) + 1], q >> (32 - (off & 31)));
     }
@@ -1743,11 +1746,15 @@ aatc_status launch_group_encode_nc(const void* params, int n_groups, const void*
     else s = launch_group_encode_tt<NC, false, 1>(params, n_groups, x, n_tok, x_tok_stride, vec, codes, alpha, cap, pos, st);
   }
   if (s != AATC_OK) return s;
-  // The tokens whose certificate failed (stream order: after the kernel above).
+  // The tokens whose certificate failed (stream order: after the kernel above).  Each costs its
+  // workgroup about 20 us at d = 512, so they are spread over four workgroups per compute unit
+  // (8192 tokens, two groups, K and V: 162 us with 16 marks each, 169 with 64, 170 with 4); past
+  // that the scans of unmarked shares would add up.
+  const int share = (n_tok / 16) * n_groups <= 1024 ? 16 : kGFixTokens;
   hipLaunchKernelGGL((group_encode_exact_kernel<NC>),
-                     dim3((unsigned)((n_tok + kGFixTokens - 1) / kGFixTokens), (unsigned)n_groups),
+                     dim3((unsigned)((n_tok + share - 1) / share), (unsigned)n_groups),
                      dim3(kGFixThreads), 0, st, params, x, (int)x_dtype, n_tok, x_tok_stride, codes,
-                     alpha, cap, pos);
+                     alpha, cap, pos, share);
   return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
 }
 
