@@ -302,10 +302,10 @@ aatc_status aatc_decode_attention(const void* dev_params_k, const void* dev_para
  * are projected, quantized and appended), followed by aatc_decode_attention with the
  * same arguments; codes, scales and outputs are identical to that sequence of calls.
  * Sequences with seq_len[b] = 0 append nothing.  With G <= 8 and records of at most
- * 64 bytes it is one launch: every workgroup of a (sequence, KV head) computes a share
- * of the new token's exact transform coefficients into the workspace, and the
- * workgroup that merges the splits quantizes and stores the token and adds its term to
- * the attention.  Other shapes run the per-token encode before the decode launch.
+ * 96 bytes, or G <= 4 and records of at most 128, it is one launch: every workgroup of a
+ * (sequence, KV head) computes a share of the new token's exact transform coefficients
+ * into the workspace, and the workgroup that merges the partials quantizes and stores the
+ * token and adds its term to the attention.  Other shapes run the per-token encode before the decode launch.
  *
  * x_k, x_v   device [batch][n_kv_heads][d] new key / value token of each sequence,
  *            x_dtype F32 or BF16.
@@ -333,8 +333,8 @@ aatc_status aatc_append_decode_attention(const void* dev_params_k, const void* d
  * of each query head over the union of the seq_len[b] tokens of the compressed caches (as
  * in aatc_decode_attention) and the seg_len[b] segment tokens, whose order does not matter:
  *   o = sum_i softmax_i(scale q . k_i) v_i,  k_i, v_i dequantized or as stored.
- * The segment is one more softmax partial: a small kernel computes it (in the original
- * domain, then T_V^T into the transformed domain of the merge) before the decode launch.
+ * The segment is one more softmax partial: a small kernel computes it in the original
+ * domain before the decode launch, whose merge adds it after the inverse transform.
  *
  * seg_k, seg_v  device [batch][n_kv_heads][seg_cap][d] segment keys and values, seg_dtype
  *               F32 or BF16 (2- or 4-byte aligned).

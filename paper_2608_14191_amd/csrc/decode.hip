@@ -2,15 +2,16 @@
 // transformed domain of App. B: q~ = T_K^T q; the inverse transform T_V is applied once
 // to each output).
 //
-// Grid: one workgroup per (sequence, KV head, token split).  Each workgroup scores its
-// split's tokens for the G query heads of its KV head, runs a split-local softmax and
-// accumulates the value codes into a partial (m, l, o~) in the workspace.  The last
-// workgroup of each (sequence, KV head) to finish merges the partials and applies T_V.
+// Each workgroup scores a share of one (sequence, KV head)'s tokens for the query heads of
+// that KV head, runs a softmax over the share and accumulates the value codes into a partial
+// (m, l, o~) in the workspace.  The last workgroup of each (sequence, KV head) to finish
+// merges the partials and applies T_V.
 //
 // Two kernels share that structure:
-//  * decode_mfma_kernel: G <= 8 and records of at most 64 bytes (budgets <= 512 bits);
-//    both contractions run on int8 MFMA over the bits of the packed codes;
-//  * decode_split_kernel: any G <= 16 and budget; plain VALU.
+//  * decode_mfma_kernel: records of at most 128 bytes (budgets <= 1024 bits), any G <= 16;
+//    both contractions run on int8 MFMA over the bits of the packed codes; a workgroup's
+//    share is a run of 512- or 1024-token chunks;
+//  * decode_split_kernel: wider records; plain VALU over 512-token splits.
 //
 // Codes are b-bit two's complement patterns, code = sum_{k < b-1} 2^k bit_k -
 // 2^(b-1) bit_(b-1): every record bit is a virtual channel whose weight is its
@@ -85,10 +86,6 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t by
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
                                            kRsrcWord3);
 }
-template <int AUX>
-__device__ inline v4i buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return (v4i)__builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX);
-}
 __device__ inline v2f buf_load8_coherent(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return (v2f)__builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, kCoherent);
 }
@@ -107,12 +104,6 @@ __device__ inline void buf_store4_coherent(float v, __amdgpu_buffer_rsrc_t r, ui
 __device__ inline void st_dev(float* p, float v) {
   __hip_atomic_store(reinterpret_cast<unsigned*>(p), __float_as_uint(v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
 }
 
 // Wave-wide maximum and sum without LDS round trips: quad butterflies and row rotations
@@ -2498,8 +2489,10 @@ static aatc_status launch_mfma_np(const DecodeArgs& a, hipStream_t st) {
   }
 }
 
-// Chunk size: 1024 tokens while that still gives every compute unit a workgroup, else 512;
-// records over 96 bytes in all take 512 (LDS).
+// Chunk size: 1024 tokens while that still gives every compute unit a workgroup, else 512 (a
+// chunk's products take as long as its tokens are many, and a short context leaves compute
+// units without a chunk: 777 tokens, 8 KV heads take 15.7 us); records over 96 bytes in all
+// take 512 (LDS).
 template <int NT, bool APPEND>
 static aatc_status launch_mfma_nt(const DecodeArgs& a, hipStream_t st) {
   if (a.rk > 64 || a.rv > 64)

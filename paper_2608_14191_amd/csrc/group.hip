@@ -36,11 +36,6 @@ constexpr int kGThreads = 256;
 constexpr int kGQThreads = 1024;                  // query kernel: sixteen waves of 8 rows
 constexpr int kGChunk = 64;                       // tokens staged per chunk (one per lane)
 
-__device__ inline void group_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 __device__ inline float g_wave_max(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
