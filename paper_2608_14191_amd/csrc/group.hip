@@ -229,14 +229,14 @@ void group_encode_mfma_kernel(const void* __restrict__ params, const void* __res
   float uv[NCT][TT][4];
   {
     const int4* tq = reinterpret_cast<const int4*>(gp->Tqt);
-    int4 raw[2][4];
+    int4 raw[4];
     auto fetch = [&](int step, int4 (&r)[4]) {     // columns of tile step / NC, piece step % NC
       const int ct = wave + kGEncWaves * (step / NC), kc = step % NC;
       const int4* p = tq + ((size_t)(16 * ct + n) * D + 64 * kc + 16 * kg) / 4;
 #pragma unroll
       for (int q = 0; q < 4; ++q) r[q] = p[q];
     };
-    fetch(0, raw[0]);
+    fetch(0, raw);
 #pragma unroll
     for (int it = 0; it < NCT; ++it) {
       gi4 acc[TT][NS];
@@ -244,30 +244,34 @@ void group_encode_mfma_kernel(const void* __restrict__ params, const void* __res
       for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
         for (int k = 0; k < NS; ++k) acc[tt][k] = (gi4){0, 0, 0, 0};
-#pragma unroll 2
+#pragma unroll 1
       for (int kc = 0; kc < NC; ++kc) {
         const int step = it * NC + kc;
-        int4 cur[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cur[q] = raw[0][q];
-        if (step + 1 < NCT * NC) fetch(step + 1, raw[0]);
         gi4 a[3];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int v[4] = {cur[q].x, cur[q].y, cur[q].z, cur[q].w};
+          const int v[4] = {raw[q].x, raw[q].y, raw[q].z, raw[q].w};
           uint32_t o[3];
           g_limbs4<3>(v, o);
 #pragma unroll
           for (int l = 0; l < 3; ++l) a[l][q] = (int)o[l];
         }
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          gi4 b[XL];
+        __builtin_amdgcn_sched_barrier(0);          // (the next step's loads go out now)
+        if (step + 1 < NCT * NC) fetch(step + 1, raw);
+        gi4 b[2][XL];
+        auto load_b = [&](int tt, gi4 (&bt)[XL]) {
 #pragma unroll
           for (int l = 0; l < XL; ++l)
-            b[l] = *reinterpret_cast<const gi4*>(smem + (((size_t)(l * NC + kc) * TT + tt) * 64 + lane) * 16);
+            bt[l] = *reinterpret_cast<const gi4*>(smem + (((size_t)(l * NC + kc) * TT + tt) * 64 + lane) * 16);
+        };
+        load_b(0, b[0]);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          if (tt + 1 < TT) load_b(tt + 1, b[(tt + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          const gi4 (&bt)[XL] = b[tt & 1];
           auto mac = [&](int t, int xa) {
-            acc[tt][xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t], b[xa], acc[tt][xa + t], 0, 0, 0);
+            acc[tt][xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t], bt[xa], acc[tt][xa + t], 0, 0, 0);
           };
           // (a product's sum is never the previous product's)
 #pragma unroll
@@ -291,7 +295,12 @@ void group_encode_mfma_kernel(const void* __restrict__ params, const void* __res
           double H = (double)acc[tt][NS - 1][i];
 #pragma unroll
           for (int k = NS - 2; k >= 0; --k) H = fma(H, 256.0, (double)acc[tt][k][i]);
-          uv[it][tt][i] = (float)H * is[i];
+          // (kept here: sunk to its uses, the five sums lived on instead of u, 137 registers
+          // spilled at d = 512, 290 MB of scratch writes per 32768 tokens, 171 us instead of 147
+          // for 8192 tokens, K and V)
+          float u = (float)H * is[i];
+          asm volatile("" : "+v"(u));
+          uv[it][tt][i] = u;
         }
     }
   }
