@@ -158,9 +158,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // channel tile ct and k half kc sit at ((2 ct + kc) 64 + l) 16, so every operand read is one
 // contiguous 1 KiB per wave (no bank conflicts).
 constexpr int kTbBytes = 8 * 2 * 64 * 16;        // one limb of the 128 x 128 transform
-// Waves per matrix-core workgroup: three per SIMD, or two for fp32 (the fourth limb and the
-// wider elements in flight need more than 168 registers).
-template <bool BF16> constexpr int kMW = BF16 ? 12 : 8;
+// Waves per matrix-core workgroup: two per SIMD (two bf16 token groups, or one of fp32 with
+// its fourth limb, take more than the 168 registers that three would leave each).
+constexpr int kMW = 8;
 constexpr int kUnit = 32;                         // tokens per wave work unit
 constexpr int kNarrowWords = kD * 8 / 32;         // largest record of codes up to 8 bits
 constexpr int kStage = kNarrowWords + 1;          // LDS record row stride (one word of padding)
@@ -402,13 +402,13 @@ __device__ inline void limb_bytes4(const int (&v)[4], uint32_t (&out)[3]) {
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
+__global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int64_t n_tok,
     int64_t x_stride, int layout, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha,
     int64_t cap, int64_t pos) {
   __shared__ __align__(16) int8_t tb[3][kTbBytes];         // [limb][ct][kc][lane][16]
-  constexpr int kMThreads = 64 * kMW<BF16>;
-  __shared__ uint32_t stage[kMW<BF16>][kUnit][kStage];     // each wave's record rows
+  constexpr int kMThreads = 64 * kMW;
+  __shared__ uint32_t stage[kMW][kUnit][kStage];     // each wave's record rows
   // Channel tables, read by the lanes that hold channels 16 ct + 4 kg + i.
   __shared__ __align__(16) float tab_is[kD];               // 1 / s_c
   __shared__ __align__(16) float tab_p2[kD];               // 2^(b_c - 1) (1 for b_c = 0)
@@ -486,11 +486,11 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
     tab_bias[tid] = bias;
     tab_msb[tid] = msb;
   }
-  for (int i = tid; i < kMW<BF16> * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
+  for (int i = tid; i < kMW * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
   __syncthreads();                                 // (the last workgroup barrier)
 
-  const int64_t ustep = (int64_t)gridDim.x * kMW<BF16>;
-  int64_t u = (int64_t)blockIdx.x * kMW<BF16> + wave;
+  const int64_t ustep = (int64_t)gridDim.x * kMW;
+  int64_t u = (int64_t)blockIdx.x * kMW + wave;
   if (u >= n_units) return;
   uint32_t (*rows)[kStage] = stage[wave];
   // Where this lane's eight fields go in a record row: byte offset of the first word (bits
@@ -505,13 +505,20 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
   // Token t = 64 first + 32 v + 16 g + n of unit v (32 v + 16 g + n past the first tile);
   // the loads run one group ahead.
   const int64_t t0 = first * kTile + n;
-  Chunk<BF16> nxt;
-  auto fetch = [&](int64_t v, int g) {
-    const int64_t t = t0 + 32 * v + 16 * g;
-    if (v < n_units && t >= pos && t < pos + n_tok)
-      nxt.load(x, (t - pos) * x_stride + (int64_t)head * kD, kg);
-    else
-      nxt.clear();
+  // Token groups that share an operand read.  bf16: both of a unit (half the LDS reads of the
+  // transform's limbs, longer chains of products between them; two waves per SIMD hold 221
+  // registers: 65536 tokens x 8 heads, K and V, 271 -> 249 us, 252 -> 245 on a faster clock).  fp32: one (four limbs).
+  constexpr int TG = BF16 ? 2 : 1;
+  Chunk<BF16> nxt[TG];
+  auto fetch = [&](int64_t v, int g0) {
+#pragma unroll
+    for (int j = 0; j < TG; ++j) {
+      const int64_t t = t0 + 32 * v + 16 * (g0 + j);
+      if (v < n_units && t >= pos && t < pos + n_tok)
+        nxt[j].load(x, (t - pos) * x_stride + (int64_t)head * kD, kg);
+      else
+        nxt[j].clear();
+    }
   };
   fetch(u, 0);
   for (; u < n_units; u += ustep) {
@@ -521,38 +528,43 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
     const int lo = (int)max<int64_t>(pos - ubase, 0);
     const int hi = (int)min<int64_t>(pos + n_tok - ubase, kUnit);
 #pragma unroll 1
-    for (int g = 0; g < 2; ++g) {
-      const Chunk<BF16> cur = nxt;
-      if (g == 0) fetch(u, 1);
-      else fetch(u + ustep, 0);
-      const int tu = 16 * g + n;
-      const bool valid = tu >= lo && tu < hi;
-      // (1) The token's fixed-point shift and exactness flag.
-      bool maybe = false;
-      const float xmax = chunk_stats<BF16>(cur, maybe);
-      const int S = token_shift(xmax) + 8 * (XL - 3);
-      const int k = S + kTFrac;
-      const bool k_ok = k >= 0 && k <= 100;
-      const XScale sc(min(max(S, -kTFrac), 100 - kTFrac));
-      const bool cert = __builtin_amdgcn_ballot_w64(maybe) != 0ull;
-      // (2) The limbs of X as B operands, and in waves with a flagged token the fixed-point
-      //     error sum E of each token (over its four lanes).
-      ev4i A[XL][2];
-      float Et = 0.f;
-      if constexpr (BF16) {
-        chunk_limbs(cur, sc, A);
-        if (cert) Et = opaque(enc_cross_row_sum(chunk_err(cur, sc)));
-      } else {
-        float E;
-        chunk_limbs(cur, sc, A, E);
-        // (2^-14: the roundings of H in fp64, in units of 2^22)
-        Et = xmax > 0.f ? enc_cross_row_sum(E) + 0x1p-14f : 0.f;
+    for (int g0 = 0; g0 < 2; g0 += TG) {
+      // (1) The tokens' fixed-point shifts and exactness flags, and (2) the limbs of X as B
+      // operands, and for a group with a flagged token the fixed-point error sum E of each
+      // token (over its four lanes).
+      ev4i A[TG][XL][2];
+      float Et[TG];
+      int kx[TG];
+      bool certs[TG];
+#pragma unroll
+      for (int j = 0; j < TG; ++j) {
+        const Chunk<BF16>& cur = nxt[j];
+        bool maybe = false;
+        const float xmax = chunk_stats<BF16>(cur, maybe);
+        const int S = token_shift(xmax) + 8 * (XL - 3);
+        kx[j] = S + kTFrac;
+        const XScale sc(min(max(S, -kTFrac), 100 - kTFrac));
+        certs[j] = __builtin_amdgcn_ballot_w64(maybe) != 0ull;
+        Et[j] = 0.f;
+        if constexpr (BF16) {
+          chunk_limbs(cur, sc, A[j]);
+          if (certs[j]) Et[j] = opaque(enc_cross_row_sum(chunk_err(cur, sc)));
+        } else {
+          float E;
+          chunk_limbs(cur, sc, A[j], E);
+          // (2^-14: the roundings of H in fp64, in units of 2^22)
+          Et[j] = xmax > 0.f ? enc_cross_row_sum(E) + 0x1p-14f : 0.f;
+        }
       }
+      if constexpr (TG == 1) fetch(g0 == 0 ? u : u + ustep, g0 == 0 ? 1 : 0);
       // (3) Channel tile by channel tile: the five limb-product sums (18 products), H exactly,
       //     then u_c = fl32(fl32(H) / s_c) for channels 16 ct + 4 kg + i of this token.  The
-      //     operands of the next k half are read while the products of this one run, and
-      //     the sums of tile ct - 1 are turned into u while those of tile ct accumulate.
-      float uv[8][4], am = 0.f;
+      //     operands of the next k half are read while the products of this one run; with
+      //     one group, the sums of tile ct - 1 are turned into u while those of tile ct
+      //     accumulate (with two, the other group's products cover for them).
+      float uv[TG][8][4], ams[TG];
+#pragma unroll
+      for (int j = 0; j < TG; ++j) ams[j] = 0.f;
       // (an opaque zero in the operand addresses: the tables are the same for every group,
       // and loads hoisted out of the loop would hold 192 registers)
       int tb0;
@@ -562,10 +574,10 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
 #pragma unroll
         for (int l = 0; l < 3; ++l) bq[l] = *reinterpret_cast<const ev4i*>(&tb[l][o]);
       };
-      auto products = [&](const ev4i (&bq)[3], int kc, ev4i (&sa)[NS]) {
+      auto products = [&](const ev4i (&bq)[3], const ev4i (&Ax)[XL][2], int kc, ev4i (&sa)[NS]) {
         // (a product's sum is never the previous product's)
         auto mac = [&](int t, int xa) {
-          sa[xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[t], A[xa][kc], sa[xa + t], 0, 0, 0);
+          sa[xa + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bq[t], Ax[xa][kc], sa[xa + t], 0, 0, 0);
         };
 #pragma unroll
         for (int xa = XL - 1; xa >= 0; --xa) mac(2, xa);
@@ -576,7 +588,7 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
 #pragma unroll
         for (int xa = 1; xa < XL; ++xa) mac(0, xa);
       };
-      auto to_u = [&](const ev4i (&sa)[NS], int ct) {
+      auto to_u = [&](const ev4i (&sa)[NS], int j, int ct) {
         const float4 is4 = *reinterpret_cast<const float4*>(&tab_is[16 * ct + 4 * kg]);
         const float isv[4] = {is4.x, is4.y, is4.z, is4.w};
 #pragma unroll
@@ -593,27 +605,47 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
             const int h1 = sa[1][i] * 256 + sa[0][i];
             H = fma(fma((double)h5, 65536.0, (double)h3), 65536.0, (double)h1);
           }
-          uv[ct][i] = (float)H * isv[i];
-          am = fmaxf(am, fabsf(uv[ct][i]));          // (u = 0 on dropped channels)
+          float u = (float)H * isv[i];
+          asm volatile("" : "+v"(u));              // (kept here: sunk to its uses, the sums live on)
+          uv[j][ct][i] = u;
+          ams[j] = fmaxf(ams[j], fabsf(uv[j][ct][i]));          // (u = 0 on dropped channels)
         }
       };
       {
-        ev4i bq[2][3], sa[2][NS];
+        constexpr int NB = TG == 1 ? 2 : 1;
+        ev4i bq[2][3], sa[NB][TG][NS];
         load_b(0, bq[0]);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int ct = q >> 1, kc = q & 1;
           if (q + 1 < 16) load_b(q + 1, bq[(q + 1) & 1]);
           __builtin_amdgcn_sched_barrier(0);            // (the reads stay ahead of the products)
-          if (kc == 0) {
 #pragma unroll
-            for (int kk = 0; kk < NS; ++kk) sa[ct & 1][kk] = (ev4i){0, 0, 0, 0};
+          for (int j = 0; j < TG; ++j) {
+            if (kc == 0) {
+#pragma unroll
+              for (int kk = 0; kk < NS; ++kk) sa[ct % NB][j][kk] = (ev4i){0, 0, 0, 0};
+            }
+            products(bq[q & 1], A[j], kc, sa[ct % NB][j]);
           }
-          products(bq[q & 1], kc, sa[ct & 1]);
-          if (kc == 1 && ct > 0) to_u(sa[(ct - 1) & 1], ct - 1);
+          if (TG == 2 && kc == 1) {
+            to_u(sa[0][0], 0, ct);
+            to_u(sa[0][TG - 1], TG - 1, ct);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (TG == 1 && kc == 1 && ct > 0) to_u(sa[(ct - 1) % NB][0], 0, ct - 1);
         }
-        to_u(sa[1], 7);
+        if (TG == 1) to_u(sa[1 % NB][0], 0, 7);
       }
+      // (the elements of the next unit, while the codes of this one are formed)
+      if constexpr (TG == 2) fetch(u + ustep, 0);
+#pragma unroll 1
+      for (int j = 0; j < TG; ++j) {
+      const int g = g0 + j, k = kx[0];
+      const bool k_ok = k >= 0 && k <= 100, cert = certs[0];
+      const float Ej = Et[0], am = ams[0];
+      const int tu = 16 * g + n;
+      const bool valid = tu >= lo && tu < hi;
       // (4) The token's scale (its 128 channels: 4 lanes), then its codes: channels
       //     16 ct + 4 kg .. + 3 are consecutive in the record, one bit field of <= 32 bits.
       const float amax_r = ldexpf(enc_cross_row_max(am), -k);
@@ -625,7 +657,7 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
         // |H - H_exact| <= eH (with the (1 + 2^-20) of the fp32 products below); the range of
         // the exact max |r| widened by the fp32 roundings must round to one fp16 scale.
         // Only tokens with E > 0 need the certificate.
-        const float eH = opaque((Et + 0x1p-143f) * (1.f + 0x1p-16f) * 0x1p22f * (1.f + 0x1p-20f));
+        const float eH = opaque((Ej + 0x1p-143f) * (1.f + 0x1p-16f) * 0x1p22f * (1.f + 0x1p-20f));
         float alo = 0.f, ahi = 0.f;
 #pragma unroll
         for (int ct = 0; ct < 8; ++ct) {
@@ -633,16 +665,16 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
           const float isv[4] = {is4.x, is4.y, is4.z, is4.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            ahi = fmaxf(ahi, fmaf(eH, isv[i], fabsf(uv[ct][i])));
-            alo = fmaxf(alo, fmaf(-eH, isv[i], fabsf(uv[ct][i])));
+            ahi = fmaxf(ahi, fmaf(eH, isv[i], fabsf(uv[0][ct][i])));
+            alo = fmaxf(alo, fmaf(-eH, isv[i], fabsf(uv[0][ct][i])));
           }
         }
         const float lo_r = ldexpf(enc_cross_row_max(alo), -k) - 0x1p-21f * amax_r;
         const float hi_r = ldexpf(enc_cross_row_max(ahi), -k) + 0x1p-21f * amax_r + 0x1p-140f;
         const bool a_unc = __half_as_ushort(token_alpha(fmaxf(lo_r, 0.f))) !=
                            __half_as_ushort(token_alpha(hi_r));
-        ea = Et > 0.f ? eH * inv_ak : -1.f;
-        bad |= Et > 0.f && a_unc;
+        ea = Ej > 0.f ? eH * inv_ak : -1.f;
+        bad |= Ej > 0.f && a_unc;
       }
       uint32_t field[8];
       auto codes_of = [&](auto certify, auto mid_rise) {
@@ -670,7 +702,7 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
             // v_cvt_rpi_i32_f32 (checked on the hardware against floor(xq) + (frac >= 1/2):
             // boundary values within 64 ulps of k and k + 1/2 for |k| <= 130, 2^24 values in
             // all).  Dropped channels have u = 0 and contribute code 0.
-            const float xq = (uv[ct][i] * inv_ak) * p2[i];
+            const float xq = (uv[0][ct][i] * inv_ak) * p2[i];
             const float xc = __builtin_amdgcn_fmed3f(xq, -p2[i], hv[i]);
             int code;
             if constexpr (MR)
@@ -711,6 +743,18 @@ __global__ __launch_bounds__(64 * kMW<BF16>) void encode_mfma_kernel(
       }
       if (valid && kg == 0)
         alpha[(int64_t)head * cap + ubase + tu] = redo ? kRedo : __half_as_ushort(a16);
+      // The next group's values move up (one copy of the code above).
+      if constexpr (TG == 2) {
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) uv[0][ct][i] = uv[1][ct][i];
+        ams[0] = ams[1];
+        kx[0] = kx[1];
+        Et[0] = Et[1];
+        certs[0] = certs[1];
+      }
+      }
     }
     // (5) The unit out of the wave's rows, each word cleared once read.
     wave_lds_sync();
@@ -981,8 +1025,8 @@ aatc_status launch_encode(const void* params, int n_heads, const void* x, aatc_d
                          (hipStream_t)stream, params, x, n_tok, x_tok_stride, (int)layout,
                          static_cast<uint8_t*>(codes), alpha, cap, pos);
     };
-    if (x_dtype == AATC_BF16) bulk(encode_mfma_kernel<true>, kMW<true>);
-    else bulk(encode_mfma_kernel<false>, kMW<false>);
+    if (x_dtype == AATC_BF16) bulk(encode_mfma_kernel<true>, kMW);
+    else bulk(encode_mfma_kernel<false>, kMW);
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     // The tokens whose certificate failed, exactly (stream order: after the kernel above).
     // 2048 tokens per workgroup when that gives every compute unit one (a scan of mostly
