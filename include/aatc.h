@@ -302,10 +302,12 @@ aatc_status aatc_decode_attention(const void* dev_params_k, const void* dev_para
  * are projected, quantized and appended), followed by aatc_decode_attention with the
  * same arguments; codes, scales and outputs are identical to that sequence of calls.
  * Sequences with seq_len[b] = 0 append nothing.  With G <= 8 and records of at most
- * 96 bytes, or G <= 4 and records of at most 128, it is one launch: every workgroup of a
+ * 96 bytes (values not much wider than the keys when G > 4: their sums share LDS), or G <= 4
+ * and records of at most 128, it is one launch: every workgroup of a
  * (sequence, KV head) computes a share of the new token's exact transform coefficients
  * into the workspace, and the workgroup that merges the partials quantizes and stores the
- * token and adds its term to the attention.  Other shapes run the per-token encode before the decode launch.
+ * token and adds its term to the attention.  Other shapes run the per-token encode before
+ * the decode launch.
  *
  * x_k, x_v   device [batch][n_kv_heads][d] new key / value token of each sequence,
  *            x_dtype F32 or BF16.

@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "decode_plan.h"
 #include "encode_core.h"
 #include "launch.h"
 #include "params.h"
@@ -33,7 +34,6 @@ namespace {
 constexpr int kThreads = 256;                    // generic kernel: four waves
 constexpr int kSplit = 512;                      // tokens per workgroup, generic kernel
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxNH = 8;                        // head slots of the MFMA kernel
 constexpr int kRsrcWord3 = 0x00020000;           // raw buffer descriptor word 3 (gfx950)
 constexpr int kCoherent = 16;                    // cache policy sc1: device-coherent access
 constexpr int kMergeU = 8;                       // split partials in flight per merging thread
@@ -625,11 +625,8 @@ struct WideMerge {
   static constexpr int kSa = kWt + 2 * NH * SB;
   static constexpr int kFin = kSa + 2 * NH;
   static constexpr int kRed = (kFin + 4 * NH + 3) / 4 * 4;
-  static constexpr int kFloats = kRed + 4 * NTHR;
+  static_assert(NTHR == kMfmaThreads && kRed + 4 * NTHR == wide_merge_floats(NH), "merge scratch");
 };
-
-template <int NTHR, int NH>
-constexpr size_t wide_merge_lds_bytes() { return WideMerge<NTHR, NH>::kFloats * sizeof(float); }
 
 template <int NTHR, int NH, class Hook>
 __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Partial* parts,
@@ -989,6 +986,7 @@ struct AppendScratch {                 // LDS region of its own
   float znew[16];                      // the token's log2-domain score per head
   uint32_t ea16[2];                    // fp16 scales
 };
+static_assert((sizeof(AppendScratch) + 15) / 16 * 16 == kAppendScratchBytes, "append scratch");
 
 // r = h~ / s of F transformed coefficients of the appended token (the encode kernels'
 // arithmetic, reductions interleaved), from this lane's two elements of the token (raw
@@ -2403,14 +2401,11 @@ class LdsLimit {
   std::atomic<size_t> set_[kDevices] = {};
 };
 
-constexpr int kComputeUnits = 256;
-
 template <int NT, int NTILE, int NP, bool APPEND>
 static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
-  constexpr int NH = 4 * NT, NTHR = 512, S = 128 * NTILE;
+  constexpr int NTHR = kMfmaThreads, S = 128 * NTILE;
   const int64_t chunks = (a.cap + S - 1) / S;
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
-  if (rows * chunks > (1 << 30)) return AATC_E_UNSUPPORTED;
   // One workgroup per compute unit: a row's chunks in runs of equal length when every chunk
   // can have a workgroup, or the batch is one sequence (its rows are equally long); otherwise
   // runs dealt by the sequences' lengths, at least two workgroups per row.
@@ -2431,39 +2426,17 @@ static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
       grid = rows;
     }
   }
-  // LDS: key records | value tiles | alpha^K | alpha^V   (front, also the merge scratch) |
-  // query limb planes | channel weights | value operands | [O' if it does not fit over the
-  // key records].  The cache streams into LDS while the query planes are built, so the
-  // planes' scratch shares the value-operand region (written only after the planes).  The transfers write
-  // whole 1 KiB blocks of the cache regions.
-  const size_t qc_bytes = (size_t)NH * kD * sizeof(float);
-  if (((size_t)S * a.rk) % 1024 || ((size_t)S * a.rv) % 1024 || (2 * S) % 1024)
-    return AATC_E_UNSUPPORTED;
-  a.off_v = S * a.rk;
-  a.off_ak = a.off_v + S * a.rv;
-  a.off_av = a.off_ak + 2 * S;
-  size_t front = (size_t)a.off_av + 2 * S;
-  front = std::max(front, wide_merge_lds_bytes<NTHR, NH>());
-  front = round256(front);
-  a.off_ql = (int)front;
-  a.off_qc = a.off_ql + 4 * NH * 2 * NP * 64;
-  a.off_pb = a.off_qc + (int)qc_bytes;
-  size_t off = (size_t)a.off_pb + std::max((size_t)(S / 64) * NT * 64 * 16, qc_bytes);
-  a.ob_stride = 8 * a.rv;
-  // O' per (half, head, value bit).
-  const size_t ob_bytes = (size_t)2 * NH * a.ob_stride * 4;
-  const size_t es_bytes = APPEND ? (sizeof(AppendScratch) + 15) / 16 * 16 : 0;
-  constexpr size_t kLdsMax = 160 * 1024 - 2 * 1024;   // (static LDS: under 2 KiB)
-  if (ob_bytes <= (size_t)S * a.rk) {
-    a.off_ob = 0;
-  } else {
-    a.off_ob = (int)off;
-    off += ob_bytes;
-  }
-  a.off_es = (int)off;
-  off += es_bytes;
-  const size_t lds = off;
-  if (lds > kLdsMax) return AATC_E_UNSUPPORTED;
+  const MfmaLds l = mfma_lds(NT, NTILE, NP, a.rk, a.rv, APPEND);
+  a.off_v = l.off_v;
+  a.off_ak = l.off_ak;
+  a.off_av = l.off_av;
+  a.off_ql = l.off_ql;
+  a.off_qc = l.off_qc;
+  a.off_pb = l.off_pb;
+  a.off_ob = l.off_ob;
+  a.ob_stride = l.ob_stride;
+  a.off_es = l.off_es;
+  const size_t lds = l.total;
   const uint32_t shape = (uint32_t)a.G | (uint32_t)a.hg << 8 | (even ? 0x10000u : 0u) |
                          (a.q_dtype == AATC_BF16 ? 0x20000u : 0u);
   auto launch = [&](auto kernel, LdsLimit& limit) {
@@ -2478,10 +2451,9 @@ static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
              : launch(decode_mfma_kernel<NT, NTILE, NP, APPEND, false>, limit_run);
 }
 
-// NP: record dwords per lane group of the key operands (16 NP bytes of record).
 template <int NT, int NTILE, bool APPEND>
-static aatc_status launch_mfma_np(const DecodeArgs& a, hipStream_t st) {
-  switch ((a.rk / 4 + 3) / 4) {
+static aatc_status launch_mfma_np(const DecodeArgs& a, int np, hipStream_t st) {
+  switch (np) {
     case 1: return launch_mfma<NT, NTILE, 1, APPEND>(a, st);
     case 2: return launch_mfma<NT, NTILE, 2, APPEND>(a, st);
     case 3: return launch_mfma<NT, NTILE, 3, APPEND>(a, st);
@@ -2489,19 +2461,12 @@ static aatc_status launch_mfma_np(const DecodeArgs& a, hipStream_t st) {
   }
 }
 
-// Chunk size: 1024 tokens while that still gives every compute unit a workgroup, else 512 (a
-// chunk's products take as long as its tokens are many, and a short context leaves compute
-// units without a chunk: 777 tokens, 8 KV heads take 15.7 us); records over 96 bytes in all
-// take 512 (LDS).
 template <int NT, bool APPEND>
-static aatc_status launch_mfma_nt(const DecodeArgs& a, hipStream_t st) {
-  if (a.rk > 64 || a.rv > 64)
-    return a.rk <= 96 && a.rv <= 96 ? launch_mfma<NT, 4, 6, APPEND>(a, st)
-                                    : launch_mfma<1, 4, 8, APPEND>(a, st);
-  const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
-  if (a.rk + a.rv > 96 || rows * ((a.cap + 1023) / 1024) < kComputeUnits)
-    return launch_mfma_np<NT, 4, APPEND>(a, st);
-  return launch_mfma_np<NT, 8, APPEND>(a, st);
+static aatc_status launch_mfma_nt(const DecodeArgs& a, const MfmaPlan& p, hipStream_t st) {
+  if (p.np == 8) return launch_mfma<1, 4, 8, APPEND>(a, st);      // (four heads)
+  if (p.np == 6) return launch_mfma<NT, 4, 6, APPEND>(a, st);
+  return p.ntile == 8 ? launch_mfma_np<NT, 8, APPEND>(a, p.np, st)
+                      : launch_mfma_np<NT, 4, APPEND>(a, p.np, st);
 }
 
 aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
@@ -2522,11 +2487,19 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
   if (cap * std::max(rk, rv) >= ((int64_t)1 << 31)) return AATC_E_UNSUPPORTED;
   if ((cap / kMinSplit + 1) * G * (int64_t)sizeof(Partial) >= ((int64_t)1 << 31))
     return AATC_E_UNSUPPORTED;
+  // Everything that can refuse the call comes before the first launch.
+  const bool mfma = rk <= kMfmaRecord && rv <= kMfmaRecord;
+  const MfmaPlan plan = mfma_plan(rk, rv, G, (int64_t)batch * n_kv_heads, cap, x_k != nullptr);
+  if (mfma && (int64_t)batch * n_kv_heads * plan.hg * ((cap + 511) / 512) > (1 << 30))
+    return AATC_E_UNSUPPORTED;
+  const size_t lds = std::max((size_t)G * (kSplit + 8 * std::max(rk, rv)) * sizeof(float),
+                              merge_lds_bytes(G, kThreads));      // (wider records)
+  if (!mfma && lds > 160 * 1024 - 24 * 1024) return AATC_E_UNSUPPORTED;
+  if (seg_k && (seg_cap > kSegMax || x_k)) return AATC_E_UNSUPPORTED;
   // The full-precision segment's partials first (stream order makes them visible to the
   // merging workgroups of the launch below).
   const Partial* seg = nullptr;
   if (seg_k) {
-    if (seg_cap > kSegMax || x_k) return AATC_E_UNSUPPORTED;
     Partial* sp = reinterpret_cast<Partial*>(ws + wl.seg);
     hipLaunchKernelGGL(segment_partial_kernel, dim3((unsigned)(batch * n_kv_heads)),
                        dim3(kSegThreads), 0, st, n_q_heads, n_kv_heads, q, (int)q_dtype, seg_k, seg_v, (int)seg_dtype, seg_len, seg_cap,
@@ -2534,14 +2507,9 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     seg = sp;
   }
-  // The matrix-core kernel takes records of up to 128 bytes, eight query heads of a KV head
-  // per workgroup (four for records over 96 bytes, by LDS) and the rest as further workgroups.
-  // Its fused append covers one workgroup row per KV head; other shapes run the per-token
-  // encode first.
-  const bool mfma = rk <= 128 && rv <= 128;
-  const int heads = rk > 96 || rv > 96 ? 4 : kMaxNH;
-  const bool fused = mfma && G <= heads;
-  if (x_k && !fused) {
+  // A new token's append is part of the matrix-core launch where that has one workgroup row per
+  // KV head; other shapes run the per-token encode first.
+  if (x_k && !(mfma && plan.fused)) {
     aatc_status e = launch_encode_last(params_k, n_kv_heads, batch, x_k, x_dtype,
                                        AATC_LAYOUT_RECORDS, const_cast<void*>(k_codes),
                                        const_cast<uint16_t*>(k_alpha), cap, rk, seq_len, stream);
@@ -2574,20 +2542,16 @@ aatc_status launch_decode(const void* params_k, const void* params_v, int batch,
     a.n_q_heads = n_q_heads;
     a.n_kv_heads = n_kv_heads;
     a.G = G;
-    a.hg = G <= 4 ? 1 : (G + heads - 1) / heads;
+    a.hg = plan.hg;
     a.q_dtype = (int)q_dtype;
     a.rk = rk;
     a.rv = rv;
     a.scale_log2e = softmax_scale * kLog2e;
-    const bool narrow = G <= 4 || heads == 4;          // four head slots per workgroup
-    if (x_k && fused)
-      return narrow ? launch_mfma_nt<1, true>(a, st) : launch_mfma_nt<2, true>(a, st);
-    return narrow ? launch_mfma_nt<1, false>(a, st) : launch_mfma_nt<2, false>(a, st);
+    if (plan.fused)
+      return plan.nt == 1 ? launch_mfma_nt<1, true>(a, plan, st) : launch_mfma_nt<2, true>(a, plan, st);
+    return plan.nt == 1 ? launch_mfma_nt<1, false>(a, plan, st) : launch_mfma_nt<2, false>(a, plan, st);
   }
   const int n_splits = (int)((cap + kSplit - 1) / kSplit);
-  size_t lds = std::max((size_t)G * (kSplit + 8 * std::max(rk, rv)) * sizeof(float),
-                        merge_lds_bytes(G, kThreads));
-  if (lds > 160 * 1024 - 24 * 1024) return AATC_E_UNSUPPORTED;
   static LdsLimit limit;
   if (!limit.ensure((const void*)decode_split_kernel, lds)) return AATC_E_DEVICE;
   dim3 grid((unsigned)n_splits, (unsigned)n_kv_heads, (unsigned)batch);

@@ -1,0 +1,92 @@
+// Shape decisions of the matrix-core decode kernel, made on the host before anything is
+// launched: query heads and tokens per workgroup, and the dynamic LDS layout.  Plain C++.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "params.h"
+
+namespace aatc {
+
+constexpr int kMaxNH = 8;                        // most query heads of a workgroup
+constexpr int kMfmaThreads = 512;                // eight waves
+constexpr int kMfmaRecord = 128;                 // widest record of the matrix-core kernel
+constexpr int kComputeUnits = 256;
+constexpr size_t kMfmaLdsMax = 160 * 1024 - 2 * 1024;   // (static LDS: under 2 KiB)
+constexpr size_t kAppendScratchBytes = 1104;     // AppendScratch, rounded to 16 bytes
+
+// The LDS floats of the merge (see WideMerge): T_V operands, two batches of split weights and
+// rescales, (M, L, bad) per head, and one float4 per thread.
+constexpr size_t wide_merge_floats(int nh) {
+  const int ng = kMfmaThreads / (nh * (kD / 4)), sb = 8 * ng;
+  const int fin = 3 * (4 * 64 * 8) / 2 + 2 * nh * sb + 2 * nh;
+  return (size_t)((fin + 4 * nh + 3) / 4 * 4 + 4 * kMfmaThreads);
+}
+
+// Dynamic LDS: key records | value tiles | alpha^K | alpha^V   (front, also the merge scratch) |
+// query limb planes | channel weights | value operands | [O' if it does not fit over the key
+// records] | [append scratch].  The cache streams into LDS while the query planes are built, so
+// the planes' scratch shares the value-operand region (written only after the planes).  The
+// transfers write whole 1 KiB blocks of the cache regions.
+struct MfmaLds {
+  int off_v, off_ak, off_av, off_ql, off_qc, off_pb, off_ob, ob_stride, off_es;
+  size_t total;
+  bool fits() const { return total <= kMfmaLdsMax; }
+};
+
+inline MfmaLds mfma_lds(int nt, int ntile, int np, int rk, int rv, bool append) {
+  const int nh = 4 * nt, s = 128 * ntile;
+  const size_t qc_bytes = (size_t)nh * kD * sizeof(float);
+  MfmaLds l;
+  l.off_v = s * rk;
+  l.off_ak = l.off_v + s * rv;
+  l.off_av = l.off_ak + 2 * s;
+  const size_t front = std::max((size_t)l.off_av + 2 * s, wide_merge_floats(nh) * sizeof(float));
+  l.off_ql = (int)((front + 255) / 256 * 256);
+  l.off_qc = l.off_ql + 4 * nh * 2 * np * 64;
+  l.off_pb = l.off_qc + (int)qc_bytes;
+  size_t off = (size_t)l.off_pb + std::max((size_t)(s / 64) * nt * 64 * 16, qc_bytes);
+  l.ob_stride = 8 * rv;
+  const size_t ob_bytes = (size_t)2 * nh * l.ob_stride * 4;    // O' per (half, head, value bit)
+  l.off_ob = ob_bytes <= (size_t)s * rk ? 0 : (int)off;
+  if (l.off_ob) off += ob_bytes;
+  l.off_es = (int)off;
+  l.total = off + (append ? kAppendScratchBytes : 0);
+  return l;
+}
+
+// How a call runs on the matrix-core kernel (records of at most kMfmaRecord bytes).
+struct MfmaPlan {
+  int nt;         // workgroups take 4 nt query heads of a KV head ...
+  int hg;         // ... in hg groups
+  int ntile;      // 128 ntile tokens per chunk
+  int np;         // record dwords per lane group of the key operands (16 np bytes of record)
+  bool fused;     // an append runs inside the decode launch (one workgroup row per KV head)
+};
+
+// Heads: eight per workgroup when there are more than four, records are at most 96 bytes and LDS
+// holds them, else four (over 96 bytes LDS holds four; and so with values much wider than the
+// keys, where the value sums find no room over the key records: 64-byte keys with 96-byte values
+// need 172 KiB for eight heads, 118 for four).  Four heads and 512 tokens fit every pair of records.
+// Tokens: 1024 per chunk while that still gives every compute unit a workgroup and fits, else 512
+// (a chunk's products take as long as its tokens are many, and a short context leaves compute
+// units without a chunk: 777 tokens, 8 KV heads take 15.7 us); records over 96 bytes in all take
+// 512 (LDS).
+inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, bool append) {
+  MfmaPlan p;
+  const int wide = std::max(rk, rv);
+  p.np = wide > 96 ? 8 : wide > 64 ? 6 : (rk / 4 + 3) / 4;
+  p.nt = G > 4 && wide <= 96 &&
+         mfma_lds(2, 4, p.np, rk, rv, append && G <= kMaxNH).fits() ? 2 : 1;
+  p.hg = (G + 4 * p.nt - 1) / (4 * p.nt);
+  p.fused = append && p.hg == 1;
+  const bool many = kv_rows * p.hg * ((cap + 1023) / 1024) >= kComputeUnits;
+  p.ntile = p.np <= 4 && rk + rv <= 96 && many &&
+            mfma_lds(p.nt, 8, p.np, rk, rv, p.fused).fits() ? 8 : 4;
+  return p;
+}
+
+}  // namespace aatc

@@ -1,0 +1,33 @@
+// Host build of the decode's shape decisions (decode_plan.h) for the CPU tests.
+#include "decode_plan.h"
+
+using namespace aatc;
+
+// Pairs of record sizes for which the plan does not fit the kernel: LDS over the limit, the value
+// sums or the regions out of place, or heads and records that its instances do not take.
+extern "C" int plan_misfits(int G, int64_t kv_rows, int64_t cap, int append) {
+  int bad = 0;
+  for (int rk = 4; rk <= kMfmaRecord; rk += 4)
+    for (int rv = 4; rv <= kMfmaRecord; rv += 4) {
+      const MfmaPlan p = mfma_plan(rk, rv, G, kv_rows, cap, append != 0);
+      const MfmaLds l = mfma_lds(p.nt, p.ntile, p.np, rk, rv, p.fused);
+      const int nh = 4 * p.nt, s = 128 * p.ntile;
+      bool ok = l.fits() && (p.nt == 1 || p.nt == 2) && (p.ntile == 4 || p.ntile == 8);
+      ok = ok && nh * p.hg >= G && nh * (p.hg - 1) < G;              // every head, no empty group
+      ok = ok && (!p.fused || (append && p.hg == 1));
+      ok = ok && 16 * p.np >= rk && (p.np <= 4 || p.ntile == 4) && (p.np < 8 || p.nt == 1);
+      ok = ok && l.off_v >= s * rk && l.off_ak >= l.off_v + s * rv && l.off_ql >= l.off_av + 2 * s;
+      const size_t ob = (size_t)2 * nh * 8 * rv * 4;
+      ok = ok && (l.off_ob == 0 ? ob <= (size_t)s * rk : l.off_ob + ob <= l.total);
+      ok = ok && (!p.fused || l.off_es + kAppendScratchBytes <= l.total);
+      bad += !ok;
+    }
+  return bad;
+}
+
+// The plan of one call: nt | hg << 8 | ntile << 16 | np << 24.
+extern "C" int plan_of(int rk, int rv, int G, int64_t kv_rows, int64_t cap, int append, int* fused) {
+  const MfmaPlan p = mfma_plan(rk, rv, G, kv_rows, cap, append != 0);
+  *fused = p.fused;
+  return p.nt | p.hg << 8 | p.ntile << 16 | p.np << 24;
+}
