@@ -765,8 +765,9 @@ __device__ __forceinline__ void merge_if_last_wide(int G, int n_splits, const Pa
       const v4f f = fin[hh];
       float M = f[0], Ls = f[1];
       hook.fold1(hh, c, M, Ls, a);
-      TvMfma::put(ob, hh, c, f[2] != 0.f ? NAN : (Ls > 0.f ? a / Ls : 0.f),
-                  triple);
+      // (0 only for an empty row: a NaN among the scores, from a NaN or infinite query, leaves
+      // the maximum and the integer sums without a trace, but not L)
+      TvMfma::put(ob, hh, c, f[2] != 0.f || Ls != Ls ? NAN : (Ls > 0.f ? a / Ls : 0.f), triple);
     }
   }
   __syncthreads();
@@ -941,7 +942,7 @@ struct SegHook {
   __device__ void weigh(int h, bool first, float& M, float& Ls, V& acc) const {
     const float ms = seg[h].m;
     float f = 0.f;
-    if (ms != -INFINITY) {
+    if (seg[h].l != 0.f) {             // (0 for an empty segment; NaN scores are kept)
       const float mn = fmaxf(M, ms);
       const float sa = exp2f(M - mn), sb = exp2f(ms - mn);
       acc = acc * sa;
