@@ -429,8 +429,9 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t first = pos / kTile, last = (pos + n_tok - 1) / kTile;
   const int64_t n_units = 2 * (last - first + 1);
-  if (hp->max_bits > 8) {
-    // Codes wider than 8 bits need not fit a four-channel field: every token goes to the
+  if (hp->max_bits > 8 || hp->record_bytes > 4 * kNarrowWords) {
+    // Codes wider than 8 bits need not fit a four-channel field, and records padded past those
+    // of 8-bit codes (to the widest head of their tensor) not the rows: every token goes to the
     // exact routine of encode_fixup_kernel (uniform over the grid).
     for (int64_t i = (int64_t)blockIdx.x * kMThreads + tid; i < n_tok;
          i += (int64_t)gridDim.x * kMThreads)
