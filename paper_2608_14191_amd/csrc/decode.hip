@@ -1367,21 +1367,19 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(
   }
 }
 
-// Deals the chunks of S tokens of a ragged batch to the workgroups: every workgroup computes
-// the same quota q, the smallest run length that a closed form finds to fit the grid (the
-// average, or with every row's last run taken as full), and finds its row and run from the
-// prefix sums over the sequences (64 per pass, one per lane).  A row has max(1, ceil(chunks /
-// q)) runs; workgroups past the last run return false.  The host gives the grid more
-// workgroups than rows.
+// Deals the chunks of S tokens of a ragged batch to the workgroups: every workgroup chooses the
+// same run length (choose_runs) and finds its row and run from the prefix sums over the
+// sequences (64 per pass, one per lane).  A row has max(1, ceil(chunks / q)) runs; workgroups
+// without a run return false.  The host gives the grid at least as many workgroups as rows.
 __device__ inline int clamped_chunks(int len, int64_t cap, int S, int app) {
   return max(1, ((int)min<int64_t>(max(len, 0), cap) - app + S - 1) / S);
 }
 template <int S, bool APPEND>
-__device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batch, int rps, int lb,
+__device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batch, int rps,
                                    int& vrow, int& split, int& ns, int& per, int& len_raw) {
   const int lane = threadIdx.x & 63;                 // (rps: rows per sequence)
-  const int grid = (int)gridDim.x;
   int nch = 0, len = 0, tot = 0;
+  float most = 0.f;                                  // (chunks of a row stay below 2^24)
   auto load = [&](int b0) {                          // this lane's sequence b0 + lane
     len = seq_len[min(b0 + lane, batch - 1)];
     nch = b0 + lane < batch ? clamped_chunks(len, cap, S, APPEND ? 1 : 0) : 0;
@@ -1389,18 +1387,19 @@ __device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batc
   for (int b0 = 0; b0 < batch; b0 += 64) {
     load(b0);
     tot += __builtin_amdgcn_readfirstlane(wave_sum_i32(nch));
+    most = fmaxf(most, wave_max_dpp((float)nch));
   }
-  tot *= rps;
-  int q = (tot + grid - 1) / grid;
-  {
-    int cnt = 0;                                     // workgroups that q takes
+  const int longest = __builtin_amdgcn_readfirstlane((int)most);
+  const RunPlan p = choose_runs(tot * rps, batch * rps, longest, (int)gridDim.x, [&](int q) {
+    int cnt = 0;
     for (int b0 = 0; b0 < batch; b0 += 64) {
       if (batch > 64) load(b0);
       cnt += __builtin_amdgcn_readfirstlane(wave_sum_i32((nch + q - 1) / q));
     }
-    // sum ceil(nch / q) <= tot / q + rows: this q always fits
-    if (cnt * rps > grid) q = (tot + grid - batch * rps - 1) / (grid - batch * rps);
-  }
+    return cnt * rps;
+  });
+  const int q = p.q, lb = run_of_block((int)blockIdx.x, p.runs);
+  if (lb < 0) return false;
   int left = lb;
   for (int b0 = 0; b0 < batch; b0 += 64) {
     if (batch > 64) load(b0);
@@ -1513,24 +1512,22 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
   // per KV head (bits 0-7), their groups (8-15), evenly dealt (16), bf16 queries (17).
   const int all_heads = (int)(shape & 0xff), hg = (int)((shape >> 8) & 0xff);
   const bool even = ONE || (shape & 0x10000u) != 0, q_bf = (shape & 0x20000u) != 0;
-  // XCD-aware order (grid a multiple of 8): workgroups are dealt to the 8 XCDs round
-  // robin, so consecutive runs of a (sequence, KV head) are given block ids that land on
-  // one XCD.
-  const int nb8 = (int)(gridDim.x >> 3);
-  const int lb = (gridDim.x & 7) ? (int)blockIdx.x
-                                 : (int)(blockIdx.x & 7) * nb8 + (int)(blockIdx.x >> 3);
   // The workgroup's row (sequence, KV head, group of NH query heads), its run of `per`
   // chunks and the row's number of runs.  Evenly dealt: every row has the same number of
   // workgroups (known without a load).  Otherwise by the lengths (assign_runs).
   int vrow, split, ns, per, len_raw;
   if (even) {
+    // XCD-aware order (grid a multiple of 8): workgroups are dealt to the 8 XCDs round robin,
+    // so consecutive runs of a (sequence, KV head) are given block ids that land on one XCD.
+    const int nb8 = (int)(gridDim.x >> 3);
+    const int lb = (gridDim.x & 7) ? (int)blockIdx.x
+                                   : (int)(blockIdx.x & 7) * nb8 + (int)(blockIdx.x >> 3);
     vrow = lb / n_splits;                            // (32-bit: rows x splits < 2^30)
     split = lb - vrow * n_splits;
     // (one sequence: known without a division)
     len_raw = seq_len[batch == 1 ? 0 : vrow / (n_kv_heads * hg)];   // gates the cache loads
   } else {
-    if (!assign_runs<S, APPEND>(seq_len, a.cap, batch, n_kv_heads * hg, lb, vrow, split, ns, per,
-                                len_raw))
+    if (!assign_runs<S, APPEND>(seq_len, a.cap, batch, n_kv_heads * hg, vrow, split, ns, per, len_raw))
       return;
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -2409,7 +2406,7 @@ static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
   // One workgroup per compute unit: a row's chunks in runs of equal length when every chunk
   // can have a workgroup, or the batch is one sequence (its rows are equally long); otherwise
-  // runs dealt by the sequences' lengths, at least two workgroups per row.
+  // runs dealt by the sequences' lengths.
   int64_t grid;
   bool even = a.batch == 1 || rows * chunks <= kComputeUnits;
   int n_splits = 0;                                   // workgroups per row (even)
@@ -2419,13 +2416,7 @@ static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
     grid = rows * n_splits;
   } else {
     a.max_splits = (int)chunks;
-    grid = std::min(rows * chunks, std::max<int64_t>(kComputeUnits, 2 * rows));
-    // (rows x 1 chunk: one run each, which the closed form of assign_runs needs no slack for)
-    if (grid <= rows) {
-      even = true;
-      n_splits = a.max_splits = 1;
-      grid = rows;
-    }
+    grid = ragged_grid(rows, chunks);
   }
   const MfmaLds l = mfma_lds(NT, NTILE, NP, a.rk, a.rv, APPEND);
   a.off_v = l.off_v;

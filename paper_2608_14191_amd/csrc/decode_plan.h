@@ -1,5 +1,6 @@
-// Shape decisions of the matrix-core decode kernel, made on the host before anything is
-// launched: query heads and tokens per workgroup, and the dynamic LDS layout.  Plain C++.
+// Shape decisions of the matrix-core decode kernel: on the host, before anything is launched,
+// query heads and tokens per workgroup, the dynamic LDS layout and the grid; in every workgroup,
+// from the lengths, the runs of a ragged batch.  Plain C++.
 #pragma once
 
 #include <stddef.h>
@@ -8,6 +9,12 @@
 #include <algorithm>
 
 #include "params.h"
+
+#if defined(__HIPCC__)
+#define AATC_PLAN_HD __host__ __device__
+#else
+#define AATC_PLAN_HD
+#endif
 
 namespace aatc {
 
@@ -87,6 +94,71 @@ inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, b
   p.ntile = p.np <= 4 && rk + rv <= 96 && many &&
             mfma_lds(p.nt, 8, p.np, rk, rv, p.fused).fits() ? 8 : 4;
   return p;
+}
+
+// Ragged batches: a row's chunks go in runs of q, a workgroup each, q chosen by every workgroup
+// from the lengths.  A compute unit holds one workgroup at a time, so runs that take r rounds of
+// the chip last about r (q + 1) chunk times (building a run's query planes and merging it cost
+// about a chunk's time).  The smallest q whose runs fit the grid of r rounds is taken for the
+// cheapest r: a run longer than needed costs every compute unit, and with more rows than half the
+// compute units two rounds of long runs can cost more than one (17 sequences of 16384 down to
+// 5800 tokens, 8 KV heads: 8 chunks a run, 59 us; 12 by a closed form over two rounds, 146).
+struct RunPlan {
+  int q, runs;                          // chunks per run, runs of the batch
+};
+
+// count(q): the runs of at most q chunks that the batch takes (falling in q).  tot: chunks of
+// all rows, longest: of one row, limit: workgroups, at least as many as rows.
+template <class Count>
+AATC_PLAN_HD inline RunPlan smallest_runs(int tot, int rows, int longest, int limit, Count count) {
+  int lo = (tot + limit - 1) / limit;   // (the average: no smaller one fits)
+  RunPlan p{lo, count(lo)};
+  if (p.runs <= limit) return p;
+  // sum ceil(n / q) <= tot / q + rows
+  const int closed = limit > rows ? (tot + limit - rows - 1) / (limit - rows) : longest;
+  int hi = closed < longest ? closed : longest;
+  p.runs = -1;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2, n = count(mid);
+    if (n <= limit) hi = mid, p.runs = n;
+    else lo = mid;
+  }
+  p.q = hi;
+  if (p.runs < 0) p.runs = count(hi);
+  return p;
+}
+
+template <class Count>
+AATC_PLAN_HD inline RunPlan choose_runs(int tot, int rows, int longest, int grid, Count count) {
+  RunPlan best{1, 0};
+  int64_t cost = INT64_MAX;
+  for (int r = (rows + kComputeUnits - 1) / kComputeUnits; kComputeUnits * (r - 1) < grid; ++r) {
+    const int limit = grid < kComputeUnits * r ? grid : kComputeUnits * r;
+    if (cost <= (int64_t)r * ((tot + limit - 1) / limit + 1)) break;   // (more rounds cost no less)
+    const RunPlan p = smallest_runs(tot, rows, longest, limit, count);
+    if ((int64_t)r * (p.q + 1) < cost) {
+      cost = (int64_t)r * (p.q + 1);
+      best = p;
+    }
+  }
+  return best;
+}
+
+// Workgroups of a ragged launch (a multiple of 8): one round while that gives every row two runs,
+// else one round more than the rows need, for choose_runs to take or leave (workgroups without a
+// run exit).
+inline int64_t ragged_grid(int64_t rows, int64_t chunks) {
+  const int64_t rounds = 2 * rows <= kComputeUnits ? 1 : (rows + kComputeUnits - 1) / kComputeUnits + 1;
+  return (std::min(rows * chunks, kComputeUnits * rounds) + 7) / 8 * 8;
+}
+
+// The run of a workgroup, -1 for none.  Workgroups are dealt to the 8 XCDs round robin:
+// consecutive runs (of one row, mostly) go to one XCD, and every XCD gets the same share of the
+// runs (dealt by the grid instead, the workgroups without a run were those of the last XCDs, and
+// the others took two rounds).
+AATC_PLAN_HD inline int run_of_block(int block, int runs) {
+  const int share = (runs + 7) / 8, i = block >> 3, run = (block & 7) * share + i;
+  return i < share && run < runs ? run : -1;
 }
 
 }  // namespace aatc

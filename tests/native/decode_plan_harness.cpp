@@ -31,3 +31,21 @@ extern "C" int plan_of(int rk, int rv, int G, int64_t kv_rows, int64_t cap, int 
   *fused = p.fused;
   return p.nt | p.hg << 8 | p.ntile << 16 | p.np << 24;
 }
+
+// The runs of a ragged batch: rows of nch[i] chunks (rps rows of each), `chunks` of capacity.
+// Returns the run length; *grid and *runs as launched and as dealt.
+extern "C" int runs_of(const int* nch, int batch, int rps, int64_t chunks, int64_t* grid, int* runs) {
+  const int rows = batch * rps;
+  *grid = ragged_grid(rows, chunks);
+  int tot = 0, longest = 0;
+  for (int i = 0; i < batch; ++i) tot += nch[i] * rps, longest = std::max(longest, nch[i]);
+  const RunPlan p = choose_runs(tot, rows, longest, (int)*grid, [&](int q) {
+    int n = 0;
+    for (int i = 0; i < batch; ++i) n += (nch[i] + q - 1) / q;
+    return n * rps;
+  });
+  *runs = p.runs;
+  return p.q;
+}
+
+extern "C" int block_run(int block, int runs) { return run_of_block(block, runs); }

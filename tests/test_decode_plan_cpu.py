@@ -2,6 +2,7 @@
 record sizes up to 128 bytes has a plan that fits the matrix-core kernel, at every number of query
 heads per KV head."""
 import ctypes
+import heapq
 import os
 import subprocess
 
@@ -41,3 +42,58 @@ def test_chosen_plans(lib, rk, rv, G, append, nt, hg, ntile, fused):
     f = ctypes.c_int()
     p = lib.plan_of(rk, rv, G, 64, 32768, append, ctypes.byref(f))
     assert (p & 255, p >> 8 & 255, p >> 16 & 255, f.value) == (nt, hg, ntile, fused)
+
+
+def _deal(lib, nch, rps, chunks):
+    arr = (ctypes.c_int * len(nch))(*nch)
+    grid, runs = ctypes.c_int64(), ctypes.c_int()
+    lib.runs_of.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
+                            ctypes.c_void_p, ctypes.c_void_p]
+    q = lib.runs_of(arr, len(nch), rps, chunks, ctypes.byref(grid), ctypes.byref(runs))
+    return q, grid.value, runs.value
+
+
+def _rounds(lib, nch, rps, q, grid, runs):
+    """The time of the dealt runs in chunk times: every XCD's 32 compute units take its workgroups
+    in order, a run costs its chunks and one more."""
+    length = []
+    for c in nch:
+        n = -(-c // q)
+        length += ([q] * (n - 1) + [c - (n - 1) * q]) * rps   # (order within a sequence: any)
+    units = [[0.0] * 32 for _ in range(8)]
+    for heap in units:
+        heapq.heapify(heap)
+    for block in range(grid):
+        r = lib.block_run(block, runs)
+        if r >= 0:
+            heap = units[block % 8]
+            heapq.heapreplace(heap, heap[0] + length[r] + 1)
+    return max(max(h) for h in units)
+
+
+LENGTHS = {"even": lambda i, b, n: n, "third": lambda i, b, n: max(1, n - i * 2 * n // (3 * b)),
+           "random": lambda i, b, n: 1 + (7919 * i + 13 * n) % n, "one": lambda i, b, n: n if i == 0 else 1,
+           "two": lambda i, b, n: n if i % 2 else max(1, n // 2)}
+
+
+@pytest.mark.parametrize("rps", [4, 8, 16])
+@pytest.mark.parametrize("kind", list(LENGTHS))
+def test_runs_of_a_ragged_batch(lib, kind, rps):
+    for b in list(range(2, 20)) + [24, 31, 32, 33, 40, 48, 65, 70, 130]:
+        for n in (1, 2, 3, 5, 8, 16, 33, 64, 128):
+            nch = [LENGTHS[kind](i, b, n) for i in range(b)]
+            rows, chunks = b * rps, 2 * n                # (capacity above the longest)
+            if rows * chunks <= 256:
+                continue                                 # (dealt evenly)
+            q, grid, runs = _deal(lib, nch, rps, chunks)
+            count = rps * sum(-(-c // q) for c in nch)
+            assert grid % 8 == 0 and rows <= grid <= max(256, rows + 512) and runs == count <= grid
+            blocks = [lib.block_run(i, runs) for i in range(grid)]
+            assert sorted(x for x in blocks if x >= 0) == list(range(runs))
+            share = [sum(x >= 0 for x in blocks[x8::8]) for x8 in range(8)]
+            assert max(share) <= -(-runs // 8)
+            # no worse than a workgroup for every chunk, which repeats the planes and the merge
+            # (two chunk times each); one long sequence among one-chunk ones fills one XCD first
+            rounds = -(-rps * sum(nch) // 256)
+            slack = 1.8 if kind == "one" else 1.1
+            assert _rounds(lib, nch, rps, q, grid, runs) <= slack * 2 * rounds + 1, (b, n, q, grid, runs)
