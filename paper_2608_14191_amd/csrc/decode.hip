@@ -995,7 +995,8 @@ static_assert((sizeof(AppendScratch) + 15) / 16 * 16 == kAppendScratchBytes, "ap
 // X_j = rint(x_j 2^S) with max |X| in [2^21, 2^22), H = sum_j X_j Tq_jc exact (each lane's
 // two products below 2^45, the wave sums taken as 24-bit halves in int32), h~ =
 // fl32(H 2^-(S+22)).  eh = E 2^-S (1 + 2^-16), E = sum_j |x_j 2^S - X_j|, bounds |h - h~|
-// for the exact h (eh = 0: h~ is exact).
+// for the exact h (eh = 0: h~ is exact; NaN or infinite with a NaN or infinite element, and where
+// 2^S is below 1 and E could underflow).
 template <int F>
 __device__ inline void append_coefficients(const uint32_t (&x)[F][2], const int (&t)[F][2],
                                            int x_dtype, const float (&inv_s)[F], float (&out)[F],
@@ -1030,7 +1031,7 @@ __device__ inline void append_coefficients(const uint32_t (&x)[F][2], const int 
   for (int f = 0; f < F; ++f) {
     const double H = fma((double)hl[2 * f], 16777216.0, (double)hl[2 * f + 1]);
     out[f] = integer_result(H, shift[f]) * inv_s[f];
-    eh[f] = ldexpf(E[f] * (1.f + 0x1p-16f), -shift[f]);
+    eh[f] = shift[f] < 0 ? INFINITY : ldexpf(E[f] * (1.f + 0x1p-16f), -shift[f]);
   }
 }
 
@@ -1093,7 +1094,7 @@ struct AppendHook {
       // holds; otherwise (rarely) the exact routine recomputes them.
       const float ehw = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(eh)));
       const HeadParams* ep = et ? ehp[1] : ehp[0];
-      if (ehw > 0.f && !wave_certify(ep, r2, ehw)) {
+      if (!(ehw <= 0.f) && !wave_certify(ep, r2, ehw)) {
         const void* xr = et ? xrow[1] : xrow[0];
         float xl[2];
 #pragma unroll
@@ -1902,7 +1903,8 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
       shift[t] = token_shift(wave_max_dpp(fmaxf(fabsf(xa), fabsf(xb))));
       const float va = ldexpf(xa, shift[t]), vb = ldexpf(xb, shift[t]);
       const float ra = rintf(va), rb = rintf(vb);
-      eh[t] = ldexpf(wave_sum_dpp(fabsf(va - ra) + fabsf(vb - rb)) * (1.f + 0x1p-16f), -shift[t]);
+      const float E = wave_sum_dpp(fabsf(va - ra) + fabsf(vb - rb));
+      eh[t] = shift[t] < 0 ? INFINITY : ldexpf(E * (1.f + 0x1p-16f), -shift[t]);
       xi[t * kD + lane] = (int)ra;                   // (every transfer wave writes the same values)
       xi[t * kD + lane + 64] = (int)rb;
     }

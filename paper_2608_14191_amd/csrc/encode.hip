@@ -140,8 +140,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // take a fourth limb, max |x_j| 2^S in [2^29, 2^30): twelve products, and a bound 2^8 smaller
 // that fails under 0.3 % (3001 tokens x 8 heads, K and V at 4 bits: 5040 us before).  Their H
 // can pass 2^53: it is formed in fp64 within 2^7, which the bound includes.
-// Tokens that fail, and tokens whose k is out of range, get the scale mark kRedo;
-// encode_fixup_kernel, launched next on the stream, encodes them exactly.
+// Tokens that fail, and tokens with NaN or infinite elements or whose k is out of range (below 22
+// the scale 2^S is below 1 and E could underflow), get the scale mark kRedo; encode_fixup_kernel,
+// launched next on the stream, encodes them exactly.
 //
 // A workgroup of twelve waves (eight for fp32) shares the limb tables of one KV head's transform (48 KiB of
 // LDS, built once).  After that each wave works alone, with no workgroup barrier, on
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
         bool maybe = false;
         const float xmax = chunk_stats<BF16>(cur, maybe);
         const int S = token_shift(xmax) + 8 * (XL - 3);
-        kx[j] = S + kTFrac;
+        kx[j] = xmax < INFINITY ? S + kTFrac : -1;
         const XScale sc(min(max(S, -kTFrac), 100 - kTFrac));
         certs[j] = __builtin_amdgcn_ballot_w64(maybe) != 0ull;
         Et[j] = 0.f;
@@ -554,7 +555,8 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
           float E;
           chunk_limbs(cur, sc, A[j], E);
           // (2^-14: the roundings of H in fp64, in units of 2^22)
-          Et[j] = xmax > 0.f ? enc_cross_row_sum(E) + 0x1p-14f : 0.f;
+          const float Es = enc_cross_row_sum(E);
+          Et[j] = xmax > 0.f || Es != 0.f ? Es + 0x1p-14f : 0.f;
         }
       }
       if constexpr (TG == 1) fetch(g0 == 0 ? u : u + ustep, g0 == 0 ? 1 : 0);
@@ -643,8 +645,10 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
 #pragma unroll 1
       for (int j = 0; j < TG; ++j) {
       const int g = g0 + j, k = kx[0];
-      const bool k_ok = k >= 0 && k <= 100, cert = certs[0];
+      const bool cert = certs[0];
       const float Ej = Et[0], am = ams[0];
+      // (E is NaN with a NaN or infinite element)
+      const bool k_ok = k >= kTFrac && k <= 100 && Ej < INFINITY;
       const int tu = 16 * g + n;
       const bool valid = tu >= lo && tu < hi;
       // (4) The token's scale (its 128 channels: 4 lanes), then its codes: channels

@@ -362,7 +362,9 @@ void group_encode_mfma_kernel(const void* __restrict__ params, const void* __res
     const float amax_r = ldexpf(am, -k);
     const __half a16 = token_alpha(amax_r);
     const float inv_ak = ldexpf(inverse_alpha(a16), -k);
-    bool bad = k < 0 || k > 100;
+    // (below 22 the scale 2^S is below 1 and E could underflow; eH is NaN with a NaN or infinite
+    // element)
+    bool bad = !(mx < INFINITY && k >= kTFrac && k <= 100 && eH[tt] < INFINITY);
     if (eH[tt] > 0.f) {
       const float lo_r = ldexpf(lo, -k) - 0x1p-21f * amax_r;
       const float hi_r = ldexpf(hi, -k) + 0x1p-21f * amax_r + 0x1p-140f;
