@@ -1438,8 +1438,8 @@ __device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batc
 // Both contractions run on v_mfma_i32_16x16x64_i8 over the bits of the codes.
 //  * Keys: D[token, (head, limb)] = sum_bits bit(token) * Qlimb[bit, (head, limb)].
 //    One record dword w (32 bits of one token) expands to MFMA bytes by
-//    r_d = w & (0x01010101 << d): byte j of r_d is 2^d * bit (8j + d).  The factor 2^d
-//    (and the sign of int8 0x80 for d = 7) is folded into the query weights, which are
+//    r_d = (w >> (d & 4)) & (0x01010101 << (d & 3)): byte j of r_d is 2^(d & 3) * bit (8j + d).
+//    The factor 2^(d & 3) is folded into the query weights, which are
 //    32-bit fixed point split into four int8 limbs: four heads times four limbs fill
 //    the 16 MFMA columns.  Lane (column (h, L), row group g) of the result holds limb L
 //    of the scores of tokens 4g .. 4g + 3; a reduce-scatter over the lane quad leaves
@@ -1810,9 +1810,8 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
     }
     // Record bit v = 32 D + 8 j + d  ->  K-step 2 (D % NP) + d / 4, lane group D / NP,
     // byte 4 (d % 4) + j of the 16-byte operand; dwords RWK .. 4 NP - 1 get weight 0.
-    // Weight 2^(k + 1 - b) Q_c / 2^d, negated for the sign bit and for d = 7 (int8 0x80 =
-    // -128); the four limbs of the four bits j = 0..3 are transposed into one dword per
-    // limb plane.
+    // Weight 2^(k + 1 - b) Q_c / 2^(d & 3), negated for the sign bit; the four limbs of the four
+    // bits j = 0..3 are transposed into one dword per limb plane.
     for (int i = tid; i < 4 * NH * 2 * 4 * (4 * NP - RWK); i += NTC) {
       const int D = RWK + i / (4 * NH * 2 * 4), rest = i % (4 * NH * 2 * 4);
       const int plane = rest / 8, st = 2 * (D % NP) + ((rest >> 2) & 1);
@@ -1856,8 +1855,8 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t ent = ((j < 2 ? desc[r].x : desc[r].y) >> (16 * (j & 1))) & 0xffffu;
-        int fx = (int)rintf(ldexpf(qv_[r][j], (int)((ent >> 8) & 15) - kDescBias + fe - d));
-        if ((((ent >> 14) & 1) != 0) != (d == 7)) fx = -fx;
+        int fx = (int)rintf(ldexpf(qv_[r][j], (int)((ent >> 8) & 15) - kDescBias + fe - (d & 3)));
+        if ((ent >> 14) & 1) fx = -fx;
         x[j] = (ent & 0x8000u) ? pack_limbs(fx) : 0u;
       }
       // x[j] = (limb 0..3 of bit j)  ->  y[L] = (limb L of bits 0..3)
@@ -2063,8 +2062,12 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
         const uint32_t w = wd[u][P];
         a0[u] = (v4i){(int)(w & 0x01010101u), (int)(w & 0x02020202u), (int)(w & 0x04040404u),
                       (int)(w & 0x08080808u)};
-        a1[u] = (v4i){(int)(w & 0x10101010u), (int)(w & 0x20202020u), (int)(w & 0x40404040u),
-                      (int)(w & 0x80808080u)};
+        // (shifted down: with the factors 2^4 .. 2^7 left in the bytes their weights kept only 23
+        // to 26 bits below the head's largest, and tokens far outside the calibration's
+        // distribution, whose scale times that weight is many times their score, lost precision)
+        const uint32_t v = w >> 4;
+        a1[u] = (v4i){(int)(v & 0x01010101u), (int)(v & 0x02020202u), (int)(v & 0x04040404u),
+                      (int)(v & 0x08080808u)};
       }
 #pragma unroll
       for (int rt = 0; rt < NT; ++rt)
