@@ -2409,11 +2409,10 @@ static aatc_status launch_mfma(DecodeArgs a, hipStream_t st) {
   constexpr int NTHR = kMfmaThreads, S = 128 * NTILE;
   const int64_t chunks = (a.cap + S - 1) / S;
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.hg;
-  // One workgroup per compute unit: a row's chunks in runs of equal length when every chunk
-  // can have a workgroup, or the batch is one sequence (its rows are equally long); otherwise
-  // runs dealt by the sequences' lengths.
+  // About one workgroup per compute unit: a row's chunks in runs of equal length, or runs dealt by
+  // the sequences' lengths.
   int64_t grid;
-  bool even = a.batch == 1 || rows * chunks <= kComputeUnits;
+  const bool even = evenly_dealt(a.batch, rows, chunks);
   int n_splits = 0;                                   // workgroups per row (even)
   if (even) {
     n_splits = (int)std::min(chunks, std::max<int64_t>(1, kComputeUnits / rows));

@@ -96,6 +96,15 @@ inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, b
   return p;
 }
 
+// Whether the launch deals every row the same number of workgroups, which need no length for it:
+// when every chunk of the capacity can have one on its own compute unit, the batch is one sequence
+// (its rows are equally long), or a row is one chunk.  (Dealt by the lengths, one-chunk rows wait
+// for them before their first other load: 64 sequences of 512 tokens, 8 KV heads, capacity 1024,
+// 29.9 us against 27.7.)
+inline bool evenly_dealt(int batch, int64_t rows, int64_t chunks) {
+  return batch == 1 || chunks == 1 || rows * chunks <= kComputeUnits;
+}
+
 // Ragged batches: a row's chunks go in runs of q, a workgroup each, q chosen by every workgroup
 // from the lengths.  A compute unit holds one workgroup at a time, so runs that take r rounds of
 // the chip last about r (q + 1) chunk times (building a run's query planes and merging it cost

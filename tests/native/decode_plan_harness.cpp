@@ -49,3 +49,5 @@ extern "C" int runs_of(const int* nch, int batch, int rps, int64_t chunks, int64
 }
 
 extern "C" int block_run(int block, int runs) { return run_of_block(block, runs); }
+
+extern "C" int dealt_evenly(int batch, int64_t rows, int64_t chunks) { return evenly_dealt(batch, rows, chunks); }

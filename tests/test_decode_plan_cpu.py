@@ -97,3 +97,11 @@ def test_runs_of_a_ragged_batch(lib, kind, rps):
             rounds = -(-rps * sum(nch) // 256)
             slack = 1.8 if kind == "one" else 1.1
             assert _rounds(lib, nch, rps, q, grid, runs) <= slack * 2 * rounds + 1, (b, n, q, grid, runs)
+
+
+@pytest.mark.parametrize("batch,rows,chunks,even", [
+    (1, 8, 4096, 1), (4, 32, 8, 1), (4, 32, 9, 0), (64, 512, 1, 1), (64, 512, 2, 0), (40, 320, 1, 1)])
+def test_rows_of_one_chunk_wait_for_no_length(lib, batch, rows, chunks, even):
+    """Rows of one chunk, however many, are dealt without the lengths."""
+    lib.dealt_evenly.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
+    assert lib.dealt_evenly(batch, rows, chunks) == even
