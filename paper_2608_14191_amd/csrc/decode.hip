@@ -464,12 +464,10 @@ struct TvMfma {
   }
 };
 
-// Extra work of the merging workgroup (the fused append supplies one, below).
+// Extra work of the merging workgroup (the segment and the fused append supply one, below).
 struct NoHook {
   __device__ void prefetch() {}
-  __device__ void during_loads() {}
   __device__ void encode() {}
-  __device__ void publish() {}
   __device__ void fold(int, int, float&, float&, v4f&) const {}
   __device__ void fold1(int, int, float&, float&, float&) const {}
   __device__ float add1(int, int, float o) const { return o; }
@@ -477,17 +475,15 @@ struct NoHook {
   __device__ void finish() {}
 };
 
-// Called by every workgroup after it stored its partial with device-coherent stores.
-// The last of a (sequence, KV head) to arrive merges the split partials.  The hook's
-// loads go out ahead of the partials', its during_loads() (encode(), then the barrier of
-// publish()) runs while they are in flight, fold() adds one more (score, value) term per output
-// slot, add1() one more term after the inverse transform, finish() runs at the end.
-template <int NTHR, bool TV, bool ONE_PASS = false, class Hook = NoHook>
+// Called by every workgroup of the generic kernel after it stored its partial with
+// device-coherent stores.  The last of a (sequence, KV head) to arrive merges the split partials;
+// the hook's fold() adds one more (score, value) term per output slot, add1() one more term after
+// the inverse transform.
+template <int NTHR, class Hook>
 __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int64_t row, int G,
                                               int n_splits, const Partial* partials,
                                               unsigned* counters, float* out_rows, float* lds,
                                               Hook& hook) {
-  constexpr int NCB = NTHR / 32;          // column blocks of the T_V product
   __shared__ unsigned last_s;
   const int tid = threadIdx.x;
   __builtin_amdgcn_s_waitcnt(0);          // this thread's partial stores have completed
@@ -500,25 +496,22 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
                                   __HIP_MEMORY_SCOPE_AGENT);
   const HeadParams* hv = head_params(params_v, kvh);
   TvBlock<NTHR> tv;
-  if (TV) tv.load(hv);
+  tv.load(hv);
   if (tid == 0) last_s = (prev == (unsigned)n_splits - 1u) ? 1u : 0u;
   __syncthreads();
   if (!last_s) return;
-  hook.prefetch();
-  __builtin_amdgcn_sched_barrier(0);
   float* cm = lds;                                         // [NTHR] group maxima
   float* cl = cm + NTHR;                                   // [NTHR] group sums
   v4f* cacc = reinterpret_cast<v4f*>(cl + NTHR);           // [NTHR]
   float* osum = reinterpret_cast<float*>(cacc + NTHR);     // [G][kD]
-  float* ored = osum + G * kD;                             // [NCB][G][kD]
+  float* ored = osum + G * kD;                             // [NTHR / 32][G][kD]
   const __amdgpu_buffer_rsrc_t prs =
       make_rsrc(partials + row * n_splits * G, (uint32_t)(n_splits * G * sizeof(Partial)));
 
   // (a) Online merge over the splits: slot (head, float4 column) per thread; groups of
   //     threads take interleaved splits and combine at the end.
-  // (ONE_PASS: G kD / 4 <= NTHR, one slot per thread, no loop.)
   const int slots = G * (kD / 4);
-  for (int base = 0; base < (ONE_PASS ? 1 : slots); base += NTHR) {
+  for (int base = 0; base < slots; base += NTHR) {
     const int width = min(slots - base, NTHR);
     const int ngroups = NTHR / width;
     const int slot = base + tid % width, grp = tid / width;
@@ -554,7 +547,6 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
       }
     };
     issue(grp);
-    if (base == 0) hook.during_loads();
     consume(grp);
     for (int s0 = grp + kMergeU * ngroups; s0 < n_splits; s0 += kMergeU * ngroups) {
       issue(s0);
@@ -586,15 +578,10 @@ __device__ __forceinline__ void merge_if_last(const void* params_v, int kvh, int
     }
     __syncthreads();
   }
-  // (b) o = T_V o~ (transformed-domain partials), or o~ itself.
-  if constexpr (TV) {
-    tv.apply(osum, ored, G, [&](int h, int j, float o) {
-      out_rows[(int64_t)h * kD + j] = hook.add1(h, j, o);
-    });
-  } else {
-    for (int i = tid; i < G * kD; i += NTHR) out_rows[i] = osum[i];
-  }
-  hook.finish();
+  // (b) o = T_V o~.
+  tv.apply(osum, ored, G, [&](int h, int j, float o) {
+    out_rows[(int64_t)h * kD + j] = hook.add1(h, j, o);
+  });
   if (tid == 0) counters[row * kCtrStride] = 0u;
 }
 
@@ -935,9 +922,7 @@ struct SegHook {
   const Partial* seg;                  // this row's partials
   float* w;                            // LDS: the segment's final weight per head
   __device__ void prefetch() {}
-  __device__ void during_loads() {}
   __device__ void encode() {}
-  __device__ void publish() {}
   template <class V>
   __device__ void weigh(int h, bool first, float& M, float& Ls, V& acc) const {
     const float ms = seg[h].m;
@@ -1071,14 +1056,7 @@ struct AppendHook {
   }
 
   // The token's codes, scales, score per head and transformed value, each tensor by one
-  // wave (wave reductions only); the barrier of publish() makes them visible.
-  __device__ void during_loads() {
-    encode();
-    publish();
-  }
-  __device__ void publish() {
-    if (on) __syncthreads();           // (uniform over the workgroup)
-  }
+  // wave (wave reductions only); the merge's next barrier makes them visible.
   __device__ void encode() {
     if (!on) return;                   // uniform over the workgroup
     float qk[2][NH];                   // (read here: no LDS round trip behind a branch later)
@@ -1144,18 +1122,6 @@ struct AppendHook {
   // The token's log2-domain score for head h.
   __device__ float znew(int h) const { return sc->znew[h]; }
 
-  __device__ void fold(int h, int c4, float& M, float& Ls, v4f& acc) const {
-    if (!on) return;
-    const float ms = znew(h);
-    const v4f v = reinterpret_cast<const v4f*>(sc->vnew)[c4];
-    const float mn = fmaxf(M, ms);
-    const float sa = exp2f(M - mn), sb = exp2f(ms - mn);
-    acc = acc * sa + v * sb;
-    Ls = Ls * sa + sb;
-    M = mn;
-  }
-
-  __device__ float add1(int, int, float o) const { return o; }
   __device__ v4f add4(int, int, v4f o) const { return o; }
   __device__ void fold1(int h, int c, float& M, float& Ls, float& acc) const {
     if (!on) return;
@@ -1359,11 +1325,11 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(
   if (seg) {
     __shared__ float seg_w[kMaxGroup];
     SegHook sh{seg + kv_row * G, seg_w};
-    merge_if_last<kThreads, true>(params_v, kvh, kv_row, G, n_splits, partials, counters,
+    merge_if_last<kThreads>(params_v, kvh, kv_row, G, n_splits, partials, counters,
                                   out_rows, dyn, sh);
   } else {
     NoHook none;
-    merge_if_last<kThreads, true>(params_v, kvh, kv_row, G, n_splits, partials, counters,
+    merge_if_last<kThreads>(params_v, kvh, kv_row, G, n_splits, partials, counters,
                                   out_rows, dyn, none);
   }
 }

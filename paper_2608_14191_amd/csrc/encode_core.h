@@ -81,7 +81,7 @@ __device__ inline float wave_max64(float v) {
 // The exact fallback for one channel by a whole wave (every lane active): lane l holds
 // elements l + 64 i of the token, tcol points at the channel's column of the integer
 // transform.  Every lane adds its products to an exact accumulator of its own; the words are
-// summed over the wave (integers: |w| < 2^39 for up to 512 products) and rounded once.  (One
+// summed over the wave (integers: |w| < 2^41 for up to 512 products) and rounded once.  (One
 // lane walking the column took a round trip per entry: 70 us for 128.)
 template <int N>
 __device__ inline float exact_dot_wave(const float (&xl)[N], const int32_t* tcol) {

@@ -1,6 +1,6 @@
 // Exact fp32 rounding of a dot product with the stored transform, for the rare tokens whose
 // fast-path result cannot be certified.  Plain C++ usable on the host and the device: a
-// fixed-point accumulator wide enough to hold any sum of 128 products of a finite fp32
+// fixed-point accumulator wide enough to hold any sum of 512 products of an fp32
 // number and a multiple of 2^-22 of magnitude at most 1, with no rounding at all, then
 // one rounding to fp32 (nearest, ties to even, with subnormals), as IEEE 754 defines it.
 #pragma once
@@ -18,8 +18,9 @@ namespace aatc {
 
 // Accumulator value = sum_i word_i 2^(32 i - kAccLsb).  A product x Tq 2^-22 with
 // x = m 2^e (m < 2^24, e >= -149) and |Tq| <= 2^22 is an integer < 2^46 times 2^(e - 22),
-// and e - 22 >= -171; the sum of 128 of them is below 2^(46 + 104 - 22 + 7) = 2^135, so
-// bits -171 .. 135 (307 bits with the sign) fit in ten words.
+// and e - 22 >= -171; e is at most 104, or 105 for the bits of a NaN or an infinity.  The sum of
+// 512 of them is below 2^(46 + 105 - 22 + 9) = 2^138, so bits -171 .. 138 (310 bits with the sign)
+// fit in ten words.
 constexpr int kAccWords = 10;
 constexpr int kAccLsb = 171;
 
@@ -32,7 +33,7 @@ AATC_HD inline uint32_t acc_word(const uint32_t (&u)[kAccWords], int i) {
   return r;
 }
 
-// Adds x Tq 2^-22 (x any finite fp32 value, |Tq| <= 2^22) to the accumulator, exactly.
+// Adds x Tq 2^-22 (|Tq| <= 2^22) to the accumulator, exactly; exponent 255 is read like any other.
 AATC_HD inline void acc_add(int64_t (&w)[kAccWords], float xv, int32_t t) {
   uint32_t bits;
   __builtin_memcpy(&bits, &xv, 4);
@@ -41,14 +42,14 @@ AATC_HD inline void acc_add(int64_t (&w)[kAccWords], float xv, int32_t t) {
   const int e = ef ? (int)ef - 150 : -149;            // x = +-m 2^e
   const uint64_t p = m * (uint64_t)(t < 0 ? -(int64_t)t : (int64_t)t);   // < 2^46
   const bool neg = ((bits >> 31) != 0u) != (t < 0);
-  const int k = e - 22 + kAccLsb;                     // bit position of p's lsb, 0 .. 253
+  const int k = e - 22 + kAccLsb;                     // bit position of p's lsb, 0 .. 254
 #pragma unroll
   for (int i = 0; i < kAccWords; ++i) {
     const int sh = k - 32 * i;
     uint64_t s = 0;
     if (sh >= 0 && sh < 32) s = (p << sh) & 0xffffffffull;
     else if (sh < 0 && sh > -64) s = (p >> (-sh)) & 0xffffffffull;
-    w[i] += neg ? -(int64_t)s : (int64_t)s;           // |w_i| < 2^39
+    w[i] += neg ? -(int64_t)s : (int64_t)s;           // |w_i| < 2^41 after 512 products
   }
 }
 
@@ -94,18 +95,6 @@ AATC_HD inline float acc_round(int64_t (&w)[kAccWords]) {
   if (round_bit && (sticky || (mant & 1u))) ++mant;   // may carry to 2^24: still exact
   const float r = ldexpf((float)mant, L - kAccLsb);   // inf beyond the fp32 range
   return neg ? -r : r;
-}
-
-// fl32(sum_{j < n} x_j Tq_j 2^-22) exactly rounded.  x_j = xf(j) (any finite fp32 value),
-// Tq_j = tq(j) (integers, |Tq_j| <= 2^22), n <= 128.
-template <typename XF, typename TQ>
-AATC_HD inline float exact_dot_q22(XF xf, TQ tq, int n) {
-  int64_t w[kAccWords];
-#pragma unroll
-  for (int i = 0; i < kAccWords; ++i) w[i] = 0;
-#pragma unroll 1
-  for (int j = 0; j < n; ++j) acc_add(w, xf(j), tq(j));
-  return acc_round(w);
 }
 
 }  // namespace aatc

@@ -78,3 +78,22 @@ def test_cancellation_and_overflow(lib):
         assert _same(got, want), (trial, got, want)
     big = np.full(128, 3.0e38, dtype=np.float32)
     assert np.isinf(_call(lib, big, np.full(128, 1 << 22, np.int32)))
+
+
+@pytest.mark.parametrize("n", [128, 512])
+def test_every_lane_full(lib, n):
+    """Tokens of one KV head and of the largest group: the widest sums, ties among them."""
+    rng = np.random.default_rng(n)
+    for trial in range(60):
+        x = (rng.standard_normal(n) * np.exp2(rng.integers(-150, 127, n).astype(float))).astype(np.float32)
+        if trial % 3 == 0:
+            x = np.full(n, 3.4e38 if trial % 2 else 2.0 ** -149, dtype=np.float32)
+        tq = rng.integers(-(1 << 22), (1 << 22) + 1, n).astype(np.int32)
+        if trial % 4 == 0:
+            tq[:] = (1 << 22) * rng.choice([-1, 1], n)
+        if trial % 5 == 0:                               # a tie decided by the last element
+            x[:] = 0
+            x[0], x[1], x[-1] = 1.0, 2.0 ** -24, rng.choice([-1, 0, 1]) * 2.0 ** -149
+            tq[[0, 1, -1]] = 1 << 22
+        got, want = _call(lib, x, tq), _want(x, tq)
+        assert _same(got, want), (trial, got, want)
