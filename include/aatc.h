@@ -300,7 +300,8 @@ aatc_status aatc_decode_attention(const void* dev_params_k, const void* dev_para
  * Equivalent to aatc_encode of x_k into (k_codes, k_alpha) and of x_v into (v_codes,
  * v_alpha) at position seq_len[b] - 1 of every sequence b (Alg. 1: the new key and value
  * are projected, quantized and appended), followed by aatc_decode_attention with the
- * same arguments; codes, scales and outputs are identical to that sequence of calls.
+ * same arguments: codes and scales are identical to that sequence of calls, outputs within
+ * fp32 rounding (in one launch the new token enters the softmax as a term of its own).
  * Sequences with seq_len[b] = 0 append nothing.  With G <= 8 and records of at most
  * 96 bytes (values not much wider than the keys when G > 4: their sums share LDS), or G <= 4
  * and records of at most 128, it is one launch: every workgroup of a

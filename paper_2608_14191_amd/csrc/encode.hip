@@ -144,9 +144,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // the scale 2^S is below 1 and E could underflow), get the scale mark kRedo; encode_fixup_kernel,
 // launched next on the stream, encodes them exactly.
 //
-// A workgroup of twelve waves (eight for fp32) shares the limb tables of one KV head's transform (48 KiB of
-// LDS, built once).  After that each wave works alone, with no workgroup barrier, on
-// 32-token units (half a 64-token tile): two groups of 16 tokens against all 128 channels,
+// A workgroup of eight waves shares the limb tables of one KV head's transform (48 KiB of LDS,
+// built once).  After that each wave works alone, with no workgroup barrier, on 32-token units (half a 64-token tile): two groups of 16 tokens against all 128 channels,
 // codes OR-ed into the wave's own LDS record rows, then the unit's records, or its half of
 // the tile's bit-transposed words, written out.  Lane 16 kg + n holds token n's elements
 // j = 64 kc + 16 kg .. + 15 (kc = 0, 1): the B operand columns; the A operand lane

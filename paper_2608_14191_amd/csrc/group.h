@@ -61,8 +61,10 @@ inline const GroupParams* group_params(const void* block, int g) {
 // [batch][n_groups][n_splits][heads][kGPH + d] (m, l, the merge's arrival count, unused to a
 // 128-byte header, o~[d]: every o~ row starts on a 128-byte line), then for the matrix-core
 // split the weights as fp16 operands [batch][n_groups][d / 32][hi, lo][64 lanes]
-// [8] (16 head slots) and their per-head power-of-two exponents [batch][n_groups][16], then
-// the merged transformed-domain outputs o~ [batch][n_groups * heads][d].
+// [8] (the first 16 head slots) and their per-head power-of-two exponents [batch][n_groups][16],
+// then `ot` [batch][n_groups * heads][d] floats: for more than 16 heads per group the operands and
+// exponents of the other slots, and after the split half of the merge's output shares (the other
+// half lies over W).
 constexpr int kGSplit = 256;                 // tokens per decode split
 constexpr int kGPH = 32;                     // header floats of a split partial row
 

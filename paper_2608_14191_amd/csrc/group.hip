@@ -610,12 +610,12 @@ struct GroupDecodeArgs {
   uint16_t* wop;                 // the weights as fp16 operands of the matrix-core split
   int32_t* wexp;                 //   and their per-head exponents (written when wops)
   int wops;
-  float* otl;                    // merged o~ per (sequence, query head)
+  float* otl;                    // the region `ot`: second head tile's operands, output shares
 };
 
 // The fp16 operands and exponents of a head tile (16 query heads) of one (sequence, group).
-// The second tile (more than 16 heads) lies in the merged outputs' region, which is written
-// only after the split: 64 d bytes and 16 exponents of the 4 d heads >= 68 d bytes there.
+// The second tile (more than 16 heads) lies in the output shares' region, which the merge writes,
+// after the split: 64 d bytes and 16 exponents of the 4 d heads >= 68 d bytes there.
 __device__ inline uint16_t* wop_tile(const GroupDecodeArgs& a, size_t gset, int d, int tile) {
   return tile == 0 ? a.wop + gset * (d / 32) * (2 * 64 * 8)
                    : reinterpret_cast<uint16_t*>(a.otl + gset * a.heads * d);
@@ -1487,7 +1487,7 @@ __global__ __launch_bounds__(kGWideThreads) void group_split_mfma_kernel(GroupDe
 // adds the shares in order.  (Coherent accesses and a relaxed count need no cache write-back: a
 // release before each arrival had made this 31 us.  Two launches, sums then transform, took
 // 5.8 + 5.8 us, 6.0 + 9.6 for 112 heads.)
-// A share's 128 outputs lie in the chunk's 64 floats of the head's rows of the o~ and of the
+// A share's 128 outputs lie in the chunk's 64 floats of the head's rows of `ot` and of the
 // weight region (read last by the split kernel, so no line of theirs is cached here); the
 // arrival count in the header of the head's first partial row, cleared by the query kernel.
 constexpr int kGMergeThreads = 256;
@@ -1638,9 +1638,11 @@ struct GroupLds {
   }
 };
 
-// Whether the matrix-core split fits (its LDS, and that of the VALU body it falls back to
-// for codes over 12 bits, with 16 NHT head slots); *lds gets the size, and the result is true
-// when both record sets fit at once (DUAL).
+// Whether the matrix-core split fits: its LDS, and that of the VALU body which a workgroup of the
+// same launch takes for codes over 12 bits (the widths lie on the device), with 16 NHT head slots.
+// At 512 channels the VALU body ends it at records of 99 dwords with one tile (6.19 bits per channel)
+// and 51 with two (3.19); the operands alone would hold 113 and 81.  *lds gets the size, and the
+// result is true when both record sets fit at once (DUAL).
 template <int NC, int NHT>
 bool group_mfma_fit(int rwk, int rwv, size_t* lds) {
   constexpr int D = 64 * NC, NQ = 16 * NHT;
