@@ -646,8 +646,8 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
       const int g = g0 + j, k = kx[0];
       const bool cert = certs[0];
       const float Ej = Et[0], am = ams[0];
-      // (E is NaN with a NaN or infinite element)
-      const bool k_ok = k >= kTFrac && k <= 100 && Ej < INFINITY;
+      // (fp32: E is NaN with a NaN element, which the maximum passes over; bf16 takes it by the bits)
+      const bool k_ok = k >= kTFrac && k <= 100 && (BF16 || Ej < INFINITY);
       const int tu = 16 * g + n;
       const bool valid = tu >= lo && tu < hi;
       // (4) The token's scale (its 128 channels: 4 lanes), then its codes: channels
