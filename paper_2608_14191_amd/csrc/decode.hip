@@ -1404,12 +1404,13 @@ __device__ inline bool assign_runs(const int32_t* seq_len, int64_t cap, int batc
 // Both contractions run on v_mfma_i32_16x16x64_i8 over the bits of the codes.
 //  * Keys: D[token, (head, limb)] = sum_bits bit(token) * Qlimb[bit, (head, limb)].
 //    One record dword w (32 bits of one token) expands to MFMA bytes by
-//    r_d = (w >> (d & 4)) & (0x01010101 << (d & 3)): byte j of r_d is 2^(d & 3) * bit (8j + d).
-//    The factor 2^(d & 3) is folded into the query weights, which are
+//    r_d = w & (0x01010101 << d): byte j of r_d is 2^d * bit (8j + d).  The factor 2^d
+//    (and the sign of int8 0x80 for d = 7) is folded into the query weights, which are
 //    32-bit fixed point split into four int8 limbs: four heads times four limbs fill
 //    the 16 MFMA columns.  Lane (column (h, L), row group g) of the result holds limb L
 //    of the scores of tokens 4g .. 4g + 3; a reduce-scatter over the lane quad leaves
-//    lane L with the full score of token 4g + L.
+//    lane L with the full score of token 4g + L.  (FINE: the upper four bits of each byte are
+//    shifted down first, factor 2^(d & 3).)
 //  * Values: D[bit, (head, limb)] = sum_tokens bit(token) * Plimb[token, (head, limb)]
 //    with P = 2^(z - m) alpha^V in 32-bit fixed point (one exponent per workgroup).
 //    The value tiles store the bit of token 16 d + 4 g + i at bit 8 i + 2 g + d % 2 of
@@ -1448,6 +1449,15 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
   constexpr int S = NW * TW;          // tokens per chunk
   constexpr int NCH = S / 64;         // 64-token blocks per chunk
   constexpr int CPW = NTILE / 4;      // blocks per wave
+  // With factors up to 2^7 in the bytes the weights of d = 7 keep 23 bits below the head's largest,
+  // and tokens far outside the calibration's distribution, whose scale times that largest weight is
+  // many times their score, lose precision: up to 6.6e-5 of an output.  FINE (27 bits, 6e-6) for
+  // the shapes that had fp32 scores before they came here, at most 9e-6: records over 64 bytes, and
+  // more than eight heads, which without an append share the instances of the fewer (a segmented
+  // step 29.3 -> 29.6 us).  The others never had more: one instruction per dword there took 4 x
+  // 131072 tokens from 85.6 to 87.1 us.
+  constexpr bool FINE = NP > 4 || !APPEND;
+  constexpr int DM = FINE ? 3 : 7;    // the factor of bit d: 2^(d & DM)
   // The cache streams straight into LDS.  For the first chunk the upper half of the waves
   // issues the transfers; the lower half builds the query planes meanwhile (a wave whose
   // loads wait for queue space can do nothing else).
@@ -1776,8 +1786,9 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
     }
     // Record bit v = 32 D + 8 j + d  ->  K-step 2 (D % NP) + d / 4, lane group D / NP,
     // byte 4 (d % 4) + j of the 16-byte operand; dwords RWK .. 4 NP - 1 get weight 0.
-    // Weight 2^(k + 1 - b) Q_c / 2^(d & 3), negated for the sign bit; the four limbs of the four
-    // bits j = 0..3 are transposed into one dword per limb plane.
+    // Weight 2^(k + 1 - b) Q_c / 2^(d & DM), negated for the sign bit and for a factor of 2^7 (int8
+    // 0x80 = -128); the four limbs of the four bits j = 0..3 are transposed into one dword per
+    // limb plane.
     for (int i = tid; i < 4 * NH * 2 * 4 * (4 * NP - RWK); i += NTC) {
       const int D = RWK + i / (4 * NH * 2 * 4), rest = i % (4 * NH * 2 * 4);
       const int plane = rest / 8, st = 2 * (D % NP) + ((rest >> 2) & 1);
@@ -1821,8 +1832,8 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t ent = ((j < 2 ? desc[r].x : desc[r].y) >> (16 * (j & 1))) & 0xffffu;
-        int fx = (int)rintf(ldexpf(qv_[r][j], (int)((ent >> 8) & 15) - kDescBias + fe - (d & 3)));
-        if ((ent >> 14) & 1) fx = -fx;
+        int fx = (int)rintf(ldexpf(qv_[r][j], (int)((ent >> 8) & 15) - kDescBias + fe - (d & DM)));
+        if ((((ent >> 14) & 1) != 0) != ((d & DM) == 7)) fx = -fx;
         x[j] = (ent & 0x8000u) ? pack_limbs(fx) : 0u;
       }
       // x[j] = (limb 0..3 of bit j)  ->  y[L] = (limb L of bits 0..3)
@@ -2028,12 +2039,8 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
         const uint32_t w = wd[u][P];
         a0[u] = (v4i){(int)(w & 0x01010101u), (int)(w & 0x02020202u), (int)(w & 0x04040404u),
                       (int)(w & 0x08080808u)};
-        // (shifted down: with the factors 2^4 .. 2^7 left in the bytes their weights kept only 23
-        // to 26 bits below the head's largest, and tokens far outside the calibration's
-        // distribution, whose scale times that weight is many times their score, lost precision)
-        const uint32_t v = w >> 4;
-        a1[u] = (v4i){(int)(v & 0x01010101u), (int)(v & 0x02020202u), (int)(v & 0x04040404u),
-                      (int)(v & 0x08080808u)};
+        const uint32_t v = FINE ? w >> 4 : w, m = FINE ? 0x01010101u : 0x10101010u;
+        a1[u] = (v4i){(int)(v & m), (int)(v & (m << 1)), (int)(v & (m << 2)), (int)(v & (m << 3))};
       }
 #pragma unroll
       for (int rt = 0; rt < NT; ++rt)
