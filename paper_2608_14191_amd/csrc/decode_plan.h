@@ -100,9 +100,21 @@ inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, b
 // when every chunk of the capacity can have one on its own compute unit, the batch is one sequence
 // (its rows are equally long), or a row is one chunk.  (Dealt by the lengths, one-chunk rows wait
 // for them before their first other load: 64 sequences of 512 tokens, 8 KV heads, capacity 1024,
-// 29.9 us against 27.7.)
+// 29.9 us against 27.7.)  And when the rows alone take four rounds of the chip or more and no row
+// can be longer than that in chunks: one run per row balances then within the last row's length,
+// and reading the lengths of a thousand sequences in every workgroup costs more (2048 sequences of
+// 300 tokens, 8 KV heads, capacity 2048: 2397 us, 799 now).
 inline bool evenly_dealt(int batch, int64_t rows, int64_t chunks) {
-  return batch == 1 || chunks == 1 || rows * chunks <= kComputeUnits;
+  return batch == 1 || chunks == 1 || rows * chunks <= kComputeUnits ||
+         (rows >= 4 * kComputeUnits && kComputeUnits * chunks <= rows);
+}
+
+// ceil(n / q) for 0 <= n < 2^20, 1 <= q < 2^20, rq = 1 / q within a few ulps: the product is within
+// one of the quotient (2^21 (2^-23 + 2^-22)), the remainder says which way.
+AATC_PLAN_HD inline int runs_of_row(int n, int q, float rq) {
+  const int a = n + q - 1;
+  const int t = (int)((float)a * rq), r = a - t * q;
+  return t + (r >= q ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
 // Ragged batches: a row's chunks go in runs of q, a workgroup each, q chosen by every workgroup

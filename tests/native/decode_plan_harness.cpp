@@ -1,4 +1,7 @@
 // Host build of the decode's shape decisions (decode_plan.h) for the CPU tests.
+#include <cmath>
+#include <cstdlib>
+
 #include "decode_plan.h"
 
 using namespace aatc;
@@ -51,3 +54,18 @@ extern "C" int runs_of(const int* nch, int batch, int rps, int64_t chunks, int64
 extern "C" int block_run(int block, int runs) { return run_of_block(block, runs); }
 
 extern "C" int dealt_evenly(int batch, int64_t rows, int64_t chunks) { return evenly_dealt(batch, rows, chunks); }
+
+// Pairs (n, q) for which runs_of_row is not ceil(n / q), with 1 / q off by ulps either way.
+extern "C" int64_t wrong_quotients(int n_max, int q_max, int step_n, int step_q, int ulps) {
+  int64_t bad = 0;
+  for (int q = 1; q < q_max; q += q < 64 ? 1 : step_q)
+    for (int e = -ulps; e <= ulps; ++e) {
+      float rq = 1.f / (float)q;
+      for (int k = 0; k < std::abs(e); ++k) rq = std::nextafterf(rq, e > 0 ? 2.f : 0.f);
+      for (int n = 0; n < n_max; n += step_n)
+        for (int m = n; m < n + 2; ++m) bad += runs_of_row(m, q, rq) != (m + q - 1) / q;
+      for (int k = 1; (int64_t)k * q < n_max && k < 2000; ++k)
+        for (int m = k * q - 1; m <= k * q + 1; ++m) bad += runs_of_row(m, q, rq) != (m + q - 1) / q;
+    }
+  return bad;
+}

@@ -100,8 +100,16 @@ def test_runs_of_a_ragged_batch(lib, kind, rps):
 
 
 @pytest.mark.parametrize("batch,rows,chunks,even", [
-    (1, 8, 4096, 1), (4, 32, 8, 1), (4, 32, 9, 0), (64, 512, 1, 1), (64, 512, 2, 0), (40, 320, 1, 1)])
-def test_rows_of_one_chunk_wait_for_no_length(lib, batch, rows, chunks, even):
-    """Rows of one chunk, however many, are dealt without the lengths."""
+    (1, 8, 4096, 1), (4, 32, 8, 1), (4, 32, 9, 0), (64, 512, 1, 1), (64, 512, 2, 0), (40, 320, 1, 1),
+    (128, 1024, 4, 1), (128, 1024, 5, 0), (1000, 1000, 2, 0), (2048, 16384, 64, 1)])
+def test_rows_that_wait_for_no_length(lib, batch, rows, chunks, even):
+    """Rows of one chunk, however many, and many rows of few chunks are dealt without the lengths."""
     lib.dealt_evenly.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
     assert lib.dealt_evenly(batch, rows, chunks) == even
+
+
+def test_quotients_of_runs(lib):
+    """The run count of a row without an integer division, over all its range."""
+    lib.wrong_quotients.restype = ctypes.c_int64
+    for n_max, q_max, step_n, step_q in ((4096, 4096, 1, 1), (1 << 20, 1 << 20, 9973, 8191)):
+        assert lib.wrong_quotients(n_max, q_max, step_n, step_q, 2) == 0
