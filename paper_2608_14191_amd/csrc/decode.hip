@@ -1900,11 +1900,19 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
   };
 
   // Fused append with fewer than 32 runs: the coefficients that the plane-building waves do
-  // not cover, one per lane of the transfer waves (index i = KF + lane): exact integer sums
-  // over the lane's column of Tq, with the tokens' integers in LDS.  (One coefficient per wave
-  // at a time took 40 us for a row of one run: a round trip and a wave reduction each.)
-  float r_tail = 0.f, eh_tail = 0.f;
-  const int d_tail = split + ns * ((wave & (NWC - 1)) + NWC * (KF + lane));
+  // not cover (k = NWC KF, ..), one per lane of the last transfer wave, or of the last two for
+  // fewer than four runs (and two per lane for one run): exact integer sums over the lane's column
+  // of Tq, with the tokens' integers in LDS.  These waves issue no cache transfers, behind which
+  // their loads would wait: dealt over all four they held up the join until the value tiles were in
+  // (20000 tokens, 8 KV heads, capacity 32768: 18.5 us, 15.7 now; 8192 of 8192: 16.3, 13.7).  (One coefficient
+  // per wave at a time took 40 us for a row of one run: a round trip and a wave reduction each.)
+  const int n_tail = !APPEND || ns * NWC * KF >= 2 * kD ? 0 : ns >= 4 ? 1 : 2;   // tail waves
+  const bool tail_wave = wave >= NW - n_tail;
+  const int tail_rounds = ns == 1 ? 2 : 1;
+  float r_tail[2] = {0.f, 0.f}, eh_tail[2] = {0.f, 0.f};
+  auto tail_dot = [&](int r) {                       // (2 kD and more: none)
+    return split + ns * (NWC * KF + 64 * (NW - 1 - wave + n_tail * r) + lane);
+  };
   auto tail_coefficients = [&]() {
     int* xi = reinterpret_cast<int*>(smem + a.off_es);   // [2][kD] (the merge's scratch later)
     int shift[2];
@@ -1918,32 +1926,37 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
       const float ra = rintf(va), rb = rintf(vb);
       const float E = wave_sum_dpp(fabsf(va - ra) + fabsf(vb - rb));
       eh[t] = shift[t] < 0 ? INFINITY : ldexpf(E * (1.f + 0x1p-16f), -shift[t]);
-      xi[t * kD + lane] = (int)ra;                   // (every transfer wave writes the same values)
+      xi[t * kD + lane] = (int)ra;                   // (every tail wave writes the same values)
       xi[t * kD + lane + 64] = (int)rb;
     }
-    const bool tv = (d_tail & kD) != 0;              // value channel (past 2 kD: unused)
-    const HeadParams* eh_p = tv ? hv : hk;
-    const int c = d_tail & (kD - 1);
-    const int4* tc = reinterpret_cast<const int4*>(eh_p->Tqt + c * kD);
-    const int4* xq = reinterpret_cast<const int4*>(xi + (tv ? kD : 0));
-    const float isv = eh_p->inv_s[c];
-    long long H = 0;
 #pragma unroll
-    for (int jb = 0; jb < kD / 4; jb += 16) {
-      int4 t4[16];
+    for (int r = 0; r < 2; ++r) {
+      if (r >= tail_rounds) break;                   // (uniform)
+      const int d = tail_dot(r);
+      const bool tv = (d & kD) != 0;                 // value channel (past 2 kD: unused)
+      const HeadParams* eh_p = tv ? hv : hk;
+      const int c = d & (kD - 1);
+      const int4* tc = reinterpret_cast<const int4*>(eh_p->Tqt + c * kD);
+      const int4* xq = reinterpret_cast<const int4*>(xi + (tv ? kD : 0));
+      const float isv = eh_p->inv_s[c];
+      long long H = 0;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) t4[q] = tc[jb + q];
+      for (int jb = 0; jb < kD / 4; jb += 16) {
+        int4 t4[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int4 x4 = xq[jb + q];
-        H += (long long)x4.x * t4[q].x;
-        H += (long long)x4.y * t4[q].y;
-        H += (long long)x4.z * t4[q].z;
-        H += (long long)x4.w * t4[q].w;
+        for (int q = 0; q < 16; ++q) t4[q] = tc[jb + q];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int4 x4 = xq[jb + q];
+          H += (long long)x4.x * t4[q].x;
+          H += (long long)x4.y * t4[q].y;
+          H += (long long)x4.z * t4[q].z;
+          H += (long long)x4.w * t4[q].w;
+        }
       }
+      r_tail[r] = integer_result((double)H, tv ? shift[1] : shift[0]) * isv;
+      eh_tail[r] = tv ? eh[1] : eh[0];
     }
-    r_tail = integer_result((double)H, tv ? shift[1] : shift[0]) * isv;
-    eh_tail = tv ? eh[1] : eh[0];
   };
 
   // (3) Front.  The plane-building and the issuing waves take separate arms up to the
@@ -1968,10 +1981,12 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
   } else {
     plain_barrier();
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    issue_keys(c0, wave - NWC, NW - NWC);
-    const int nv_mine = issue_values(c0, wave - NWC, NW - NWC);
-    if (APPEND && ns * NWC * KF < 2 * kD) tail_coefficients();
-    wait_vmcnt(nv_mine);                             // key records and scales landed
+    if (APPEND && tail_wave) {
+      tail_coefficients();
+    } else {
+      issue_keys(c0, wave - NWC, NW - NWC - n_tail);
+      wait_vmcnt(issue_values(c0, wave - NWC, NW - NWC - n_tail));   // key records and scales landed
+    }
   }
   __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
   plain_barrier();
@@ -2299,10 +2314,15 @@ void decode_mfma_kernel(const int32_t* seq_len, const void* params_k, const void
         if (adk[f] < 2 * kD && (adk[f] & (kD - 1)) == 0 && lane == 0)
           buf_store4_coherent(reh[f], rrs, (uint32_t)(4 * (2 * kD + adk[f] / kD)));
       }
-    } else if (ns * NWC * KF < 2 * kD && d_tail < 2 * kD) {
-      buf_store4_coherent(r_tail, rrs, (uint32_t)(4 * d_tail));
-      if ((d_tail & (kD - 1)) == 0)
-        buf_store4_coherent(eh_tail, rrs, (uint32_t)(4 * (2 * kD + d_tail / kD)));
+    } else if (tail_wave) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int d = tail_dot(r);
+        if (r >= tail_rounds || d >= 2 * kD) continue;
+        buf_store4_coherent(r_tail[r], rrs, (uint32_t)(4 * d));
+        if ((d & (kD - 1)) == 0)
+          buf_store4_coherent(eh_tail[r], rrs, (uint32_t)(4 * (2 * kD + d / kD)));
+      }
     }
   }
   const int v_maxb = hdr_s[1];
