@@ -78,10 +78,11 @@ struct MfmaPlan {
 // holds them, else four (over 96 bytes LDS holds four; and so with values much wider than the
 // keys, where the value sums find no room over the key records: 64-byte keys with 96-byte values
 // need 172 KiB for eight heads, 118 for four).  Four heads and 512 tokens fit every pair of records.
-// Tokens: 1024 per chunk while that still gives every compute unit a workgroup and fits, else 512
-// (a chunk's products take as long as its tokens are many, and a short context leaves compute
-// units without a chunk: 777 tokens, 8 KV heads take 15.7 us); records over 96 bytes in all take
-// 512 (LDS).
+// Tokens: 512 per chunk while the capacity's chunks all find a compute unit of their own and a row
+// has at most 64 of them, else 1024 (a chunk's products take as long as its tokens are many: 16384
+// tokens, 8 KV heads, 12.8 us against 14.5; but runs of two 512-token chunks take longer than one of
+// 1024, 24000 tokens 16.4 against 14.5, and one workgroup merges a row's partials, 131072 tokens of
+// one KV head with 8 query heads 35.5 against 27.6); records over 96 bytes in all take 512 (LDS).
 inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, bool append) {
   MfmaPlan p;
   const int wide = std::max(rk, rv);
@@ -90,8 +91,8 @@ inline MfmaPlan mfma_plan(int rk, int rv, int G, int64_t kv_rows, int64_t cap, b
          mfma_lds(2, 4, p.np, rk, rv, append && G <= kMaxNH).fits() ? 2 : 1;
   p.hg = (G + 4 * p.nt - 1) / (4 * p.nt);
   p.fused = append && p.hg == 1;
-  const bool many = kv_rows * p.hg * ((cap + 1023) / 1024) >= kComputeUnits;
-  p.ntile = p.np <= 4 && rk + rv <= 96 && many &&
+  const bool few = kv_rows * p.hg * ((cap + 511) / 512) <= kComputeUnits && cap <= 32 * 1024;
+  p.ntile = p.np <= 4 && rk + rv <= 96 && !few &&
             mfma_lds(p.nt, 8, p.np, rk, rv, p.fused).fits() ? 8 : 4;
   return p;
 }
