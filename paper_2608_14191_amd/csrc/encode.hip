@@ -144,8 +144,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // the scale 2^S is below 1 and E could underflow), get the scale mark kRedo; encode_fixup_kernel,
 // launched next on the stream, encodes them exactly.
 //
-// A workgroup of eight waves shares the limb tables of one KV head's transform (48 KiB of LDS,
-// built once).  After that each wave works alone, with no workgroup barrier, on 32-token units (half a 64-token tile): two groups of 16 tokens against all 128 channels,
+// A workgroup of eight or twelve waves shares the limb tables of one KV head's transform (48 KiB of
+// LDS, built once).  After that each wave works alone, with no workgroup barrier, on 32-token units (half a 64-token tile): two groups of 16 tokens against all 128 channels,
 // codes OR-ed into the wave's own LDS record rows, then the unit's records, or its half of
 // the tile's bit-transposed words, written out.  Lane 16 kg + n holds token n's elements
 // j = 64 kc + 16 kg .. + 15 (kc = 0, 1): the B operand columns; the A operand lane
@@ -158,9 +158,11 @@ __global__ __launch_bounds__(kEncThreads) void encode_exact_kernel(
 // channel tile ct and k half kc sit at ((2 ct + kc) 64 + l) 16, so every operand read is one
 // contiguous 1 KiB per wave (no bank conflicts).
 constexpr int kTbBytes = 8 * 2 * 64 * 16;        // one limb of the 128 x 128 transform
-// Waves per matrix-core workgroup: two per SIMD (two bf16 token groups, or one of fp32 with
-// its fourth limb, take more than the 168 registers that three would leave each).
+// Waves per matrix-core workgroup: two per SIMD (two bf16 token groups per operand read, or one of
+// fp32 with its fourth limb, take more than the 168 registers that three leave each), or three with
+// one bf16 group.
 constexpr int kMW = 8;
+constexpr int kMWide = 12;
 constexpr int kUnit = 32;                         // tokens per wave work unit
 constexpr int kNarrowWords = kD * 8 / 32;         // largest record of codes up to 8 bits
 constexpr int kStage = kNarrowWords + 1;          // LDS record row stride (one word of padding)
@@ -401,14 +403,17 @@ __device__ inline void limb_bytes4(const int (&v)[4], uint32_t (&out)[3]) {
            __builtin_amdgcn_perm(y2[3], y2[2], 0x06020c0cu);
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
+// TG: token groups that share an operand read.  Two (bf16): half the LDS reads of the transform's
+// limbs, longer chains of products between them; two waves per SIMD hold 223 registers: 65536 tokens
+// x 8 heads, K and V, 271 -> 249 us, 252 -> 245 on a faster clock.
+template <bool BF16, int MW, int TG>
+__global__ __launch_bounds__(64 * MW) void encode_mfma_kernel(
     const void* __restrict__ params, const void* __restrict__ x, int64_t n_tok,
     int64_t x_stride, int layout, uint8_t* __restrict__ codes, uint16_t* __restrict__ alpha,
     int64_t cap, int64_t pos) {
   __shared__ __align__(16) int8_t tb[3][kTbBytes];         // [limb][ct][kc][lane][16]
-  constexpr int kMThreads = 64 * kMW;
-  __shared__ uint32_t stage[kMW][kUnit][kStage];     // each wave's record rows
+  constexpr int kMThreads = 64 * MW;
+  __shared__ uint32_t stage[MW][kUnit][kStage];     // each wave's record rows
   // Channel tables, read by the lanes that hold channels 16 ct + 4 kg + i.
   __shared__ __align__(16) float tab_is[kD];               // 1 / s_c
   __shared__ __align__(16) float tab_p2[kD];               // 2^(b_c - 1) (1 for b_c = 0)
@@ -487,11 +492,11 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
     tab_bias[tid] = bias;
     tab_msb[tid] = msb;
   }
-  for (int i = tid; i < kMW * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
+  for (int i = tid; i < MW * kUnit * kStage; i += kMThreads) (&stage[0][0][0])[i] = 0u;
   __syncthreads();                                 // (the last workgroup barrier)
 
-  const int64_t ustep = (int64_t)gridDim.x * kMW;
-  int64_t u = (int64_t)blockIdx.x * kMW + wave;
+  const int64_t ustep = (int64_t)gridDim.x * MW;
+  int64_t u = (int64_t)blockIdx.x * MW + wave;
   if (u >= n_units) return;
   uint32_t (*rows)[kStage] = stage[wave];
   // Where this lane's eight fields go in a record row: byte offset of the first word (bits
@@ -506,10 +511,6 @@ __global__ __launch_bounds__(64 * kMW) void encode_mfma_kernel(
   // Token t = 64 first + 32 v + 16 g + n of unit v (32 v + 16 g + n past the first tile);
   // the loads run one group ahead.
   const int64_t t0 = first * kTile + n;
-  // Token groups that share an operand read.  bf16: both of a unit (half the LDS reads of the
-  // transform's limbs, longer chains of products between them; two waves per SIMD hold 221
-  // registers: 65536 tokens x 8 heads, K and V, 271 -> 249 us, 252 -> 245 on a faster clock).  fp32: one (four limbs).
-  constexpr int TG = BF16 ? 2 : 1;
   Chunk<BF16> nxt[TG];
   auto fetch = [&](int64_t v, int g0) {
 #pragma unroll
@@ -1022,19 +1023,33 @@ aatc_status launch_encode(const void* params, int n_heads, const void* x, aatc_d
                        ((size_t)x_tok_stride * esize) % 16 == 0;
   if (aligned) {
     // About one workgroup per compute unit over all KV heads.
+    auto blocks = [&](int waves) {
+      return std::min<int64_t>(std::max(1, 256 / n_heads), (2 * n_tiles + waves - 1) / waves);
+    };
+    auto rounds = [&](int waves) {                 // units of the busiest wave
+      const int64_t step = blocks(waves) * waves;
+      return (2 * n_tiles + step - 1) / step;
+    };
     auto bulk = [&](auto kernel, int waves) {
-      const int64_t per_head = std::min<int64_t>(std::max(1, 256 / n_heads),
-                                                 (2 * n_tiles + waves - 1) / waves);
-      hipLaunchKernelGGL(kernel, dim3((unsigned)per_head, (unsigned)n_heads), dim3(64 * waves), 0,
+      hipLaunchKernelGGL(kernel, dim3((unsigned)blocks(waves), (unsigned)n_heads), dim3(64 * waves), 0,
                          (hipStream_t)stream, params, x, n_tok, x_tok_stride, (int)layout,
                          static_cast<uint8_t*>(codes), alpha, cap, pos);
     };
-    if (x_dtype == AATC_BF16) bulk(encode_mfma_kernel<true>, kMW);
-    else bulk(encode_mfma_kernel<false>, kMW);
+    // bf16: eight waves with both token groups of a unit per operand read, or twelve with one (a
+    // round of a unit per wave takes 1.4 to 1.5 times as long) where a round of the eight would be
+    // mostly empty: 20000 tokens, 4 KV heads, 2 rounds or 1, 41 us or 33; 24576 x 8, 3 or 2, 57 or
+    // 55; 40000 x 64, 40 or 27, 552 or 571; 65536 x 8, 8 or 6, 115 or 120.
+    if (x_dtype == AATC_BF16) {
+      if (3 * rounds(kMWide) <= 2 * rounds(kMW)) bulk(encode_mfma_kernel<true, kMWide, 1>, kMWide);
+      else bulk(encode_mfma_kernel<true, kMW, 2>, kMW);
+    } else {
+      bulk(encode_mfma_kernel<false, kMW, 1>, kMW);
+    }
     if (hipGetLastError() != hipSuccess) return AATC_E_DEVICE;
     // The tokens whose certificate failed, exactly (stream order: after the kernel above).
-    // 2048 tokens per workgroup when that gives every compute unit one (a scan of mostly
-    // unmarked tokens), else 64, so that a short call's marked tokens spread over the chip.
+    // 2048 tokens per workgroup, or 256, where that gives every compute unit one (a scan of mostly
+    // unmarked tokens), else 64, so that a short call's marked tokens spread over the chip (20000
+    // tokens x 4 or 8 heads: 9.2 and 10.8 us with 64, 7.4 and 9.4 with 2048, 8.0 and 8.6 with 256).
     auto fixup = [&](auto kernel, int tokens) {
       const dim3 fgrid((unsigned)((n_tok + tokens - 1) / tokens), (unsigned)n_heads);
       hipLaunchKernelGGL(kernel, fgrid, dim3(kFixThreads), 0, (hipStream_t)stream, params, x,
@@ -1042,6 +1057,7 @@ aatc_status launch_encode(const void* params, int n_heads, const void* x, aatc_d
                          static_cast<uint8_t*>(codes), alpha, cap, pos);
     };
     if ((n_tok / 2048) * n_heads >= 256) fixup(encode_fixup_kernel<2048>, 2048);
+    else if ((n_tok / 256) * n_heads >= 256) fixup(encode_fixup_kernel<256>, 256);
     else fixup(encode_fixup_kernel<64>, 64);
     return hipGetLastError() == hipSuccess ? AATC_OK : AATC_E_DEVICE;
   }
