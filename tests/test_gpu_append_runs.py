@@ -49,6 +49,12 @@ def test_short_in_a_large_capacity(n, append):
     _check([n], 32768, append, n_q_heads=16, n_kv_heads=8)
 
 
+@pytest.mark.parametrize("n", [513, 1025, 1537, 2049])
+def test_widest_records(n):
+    """128-byte records: the most transfers per wave in flight, on two or three waves."""
+    _check([n], (n + 63) // 64 * 64, True, avg_bits=8.0, b_max=16, n_q_heads=4, n_kv_heads=1)
+
+
 def test_ragged_runs():
     _check([1, 1500, 4000, 64, 20000, 700, 513], 20032, True, n_q_heads=8, n_kv_heads=2)
     _check([5000, 300], 5056, True, avg_bits=6.0, b_max=12, n_q_heads=7, n_kv_heads=1)
